@@ -79,7 +79,7 @@ enum { ORTHO_PASS = 0, ORTHO_RESIDENT = 1, ORTHO_ONE_REDUCE = 2 };
 
 int pick_ortho(const rok_ctx* c, int M, bool mgs_only) {
     const long N = c->G.N;
-    const bool resident_ok = rok::mgs_resident_per(N) > 0 && rok::mgs_resident_available();
+    const bool resident_ok = rok::mgs_resident_fits(N) && rok::mgs_resident_available();
     if (mgs_only) return (c->mgs_path != ROK_MGS_PER_PASS && resident_ok) ? ORTHO_RESIDENT : ORTHO_PASS;
     switch (c->mgs_path) {
         case ROK_MGS_PER_PASS: return ORTHO_PASS;
@@ -696,7 +696,7 @@ rok_status rok_eigs(rok_ctx* c, const double* y, const double* v0, int k, int m,
     W2.H = (double*)(p + L.work + 2 * L.basis + L.coef);
     // the resident kernel holds a column of H in LDS (at most ROK_MAX_M entries): larger bases
     // take the pass-by-pass kernels
-    const bool resident = c->mgs_path != ROK_MGS_PER_PASS && Mp <= ROK_MAX_M && rok::mgs_resident_per(N) > 0 &&
+    const bool resident = c->mgs_path != ROK_MGS_PER_PASS && Mp <= ROK_MAX_M && rok::mgs_resident_fits(N) &&
                           rok::mgs_resident_available();
     if (c->mgs_path == ROK_MGS_RESIDENT && !resident) return ROK_EUNSUPPORTED;
     auto mgs = [&](const rok::Work& Wx, int j, double* vnext) -> hipError_t {

@@ -139,6 +139,72 @@ template <typename S> __device__ __forceinline__ S narrow(typename Wide<S>::type
 // of 17 vectors of 84 M doubles).  Not for stencil staging, whose halos hit in L2.
 __device__ __forceinline__ double ld_stream(const double* p) { return __builtin_nontemporal_load(p); }
 
+// The value of v held by lane `lane` (uniform across the wave) of the calling wave.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), lane);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+// Lane i's register moved down by H lanes without going through LDS (a wave
+// shuffle by ds_bpermute takes about 60 cycles, these a few): the value of lane
+// i + H for the lanes i with i mod 2H < H, which is all a halving tree uses
+// (the other lanes get some value of the wave, or zero).  H = 32, 16: swaps of
+// wave halves and row pairs; 8 to 1: data-parallel moves within a row of 16.
+template <int H>
+__device__ __forceinline__ int lane_down_word(int x) {
+    static_assert(H == 32 || H == 16 || H == 8 || H == 4 || H == 2 || H == 1, "a power of two below 64");
+    if constexpr (H == 32) return (int)__builtin_amdgcn_permlane32_swap(x, x, false, false)[1];
+    else if constexpr (H == 16) return (int)__builtin_amdgcn_permlane16_swap(x, x, false, false)[1];
+    else return __builtin_amdgcn_update_dpp(0, x, 0x100 + H, 0xf, 0xf, true);   // row_shl:H
+}
+
+template <int H>
+__device__ __forceinline__ double lane_down(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = lane_down_word<H>((int)(b & 0xffffffffLL)), hi = lane_down_word<H>((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+// One level of two halving trees at once: a_i + a_{i+H} in the lanes i with
+// i mod 2H < H, b_{i-H} + b_i in the others.
+template <int H>
+__device__ __forceinline__ double swap_add(double a, double b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const int xl = (int)(x & 0xffffffffLL), xh = (int)(x >> 32), yl = (int)(y & 0xffffffffLL), yh = (int)(y >> 32);
+    int pl, ph, ql, qh;
+    if constexpr (H == 32 || H == 16) {
+        // the upper part of the first register changes places with the lower part of the second
+        const auto l = (H == 32) ? __builtin_amdgcn_permlane32_swap(xl, yl, false, false)
+                                 : __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
+        const auto h = (H == 32) ? __builtin_amdgcn_permlane32_swap(xh, yh, false, false)
+                                 : __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
+        pl = (int)l[0]; ql = (int)l[1];
+        ph = (int)h[0]; qh = (int)h[1];
+    } else {
+        static_assert(H == 8 || H == 16 || H == 32, "the levels that rotate by half a row or more");
+        const bool up = (threadIdx.x & 8) != 0;
+        pl = up ? yl : xl;
+        ph = up ? yh : xh;
+        // row_ror:8: the lane 8 away in the row of 16
+        ql = __builtin_amdgcn_update_dpp(0, up ? xl : yl, 0x128, 0xf, 0xf, true);
+        qh = __builtin_amdgcn_update_dpp(0, up ? xh : yh, 0x128, 0xf, 0xf, true);
+    }
+    return __longlong_as_double(((long long)ph << 32) | (long long)(unsigned)pl) +
+           __longlong_as_double(((long long)qh << 32) | (long long)(unsigned)ql);
+}
+
+// The in-wave levels h = 32 .. 1 of a halving tree; the sum is in lane 0.
+__device__ __forceinline__ double wave_sum(double v) {
+    v = v + lane_down<32>(v);
+    v = v + lane_down<16>(v);
+    v = v + lane_down<8>(v);
+    v = v + lane_down<4>(v);
+    v = v + lane_down<2>(v);
+    return v + lane_down<1>(v);
+}
+
 // Pairwise halving tree over groups of 256 consecutive threads of a block:
 // with x_i the value of lane i of a group, computes s_i <- s_i + s_{i+h} for
 // h = 128, 64, ..., 1 (i < h) and returns s_0 in lane 0 of each group (other
@@ -156,9 +222,7 @@ __device__ __forceinline__ double tree256(double v, double* s) {
     }
     __syncthreads();
     if (lane < 64) {
-        v = v + s[tid + 64];
-#pragma unroll
-        for (int h = 32; h > 0; h >>= 1) v = v + __shfl_down(v, h, 64);
+        v = wave_sum(v + s[tid + 64]);
     }
     return v;
 }
@@ -190,9 +254,7 @@ __device__ __forceinline__ void tree256_chunks(const double (&v)[N], int nact, d
         if (tid < 64) {
 #pragma unroll
             for (int c = 0; c < K; ++c) {
-                x[c] = x[c] + s[c][tid + 64];
-#pragma unroll
-                for (int h = 32; h > 0; h >>= 1) x[c] = x[c] + __shfl_down(x[c], h, 64);
+                x[c] = wave_sum(x[c] + s[c][tid + 64]);
             }
         }
         if (tid == 0) {

@@ -37,8 +37,8 @@ struct Work {
     double* sig;      // M + 1 basis scales: column c of V holds v_c / sig[c] (1 unless normalisation is deferred)
     double* partials; // npart x kRedBlocks reduction partials
     int npart;
-    double* gpart;    // 2 x kRedBlocks partials exchanged inside the resident MGS kernel
-    unsigned* bar;    // grid barrier counters (kBarWords unsigned, zeroed by launch_init)
+    double* gpart;    // the exchange slots of the resident MGS kernels (kExchangeSlots, emptied by launch_init; M > 0)
+    unsigned* bar;    // exchange words of the resident MGS kernels (kBarWords unsigned, zeroed by launch_init)
     // full-length vectors (double, N each)
     double* w;        // Arnoldi work vector
     double* V;        // M columns (rok_step only; rok_arnoldi uses the caller's V)
@@ -48,7 +48,10 @@ struct Work {
 
 constexpr int kRedBlocks = 1024;   // reduction grid (fixed: it fixes the summation order)
 constexpr int kRedThreads = 256;
-constexpr int kBarWords = 1024;   // grid-barrier state (4 KiB)
+constexpr int kBarWords = 1024;   // exchange state (4 KiB)
+constexpr int kExchangeCopies = 8;   // copies of the exchange slots of the resident MGS kernels
+constexpr int kExchangeSlots = 3 * kExchangeCopies * kRedThreads;   // three buffers
+constexpr unsigned long long kExchangeEmpty = 0x7ff4000000000ea5ull;   // an empty exchange slot: a signalling NaN
 
 size_t work_small_bytes(int M, int s);
 size_t work_bytes(long N, int M, int s, bool step);
@@ -77,7 +80,7 @@ hipError_t launch_ls_column(const Work& W, const double* w, const double* V, lon
 // H[j+1][j] = ||w||, finished from `partials`, the breakdown test of column j and sig[j+1] = 1 / ||w|| (one block)
 hipError_t launch_norm_scale(const Work& W, const double* partials, int M, int j, hipStream_t st);
 // Resident-w MGS for one column (rok_mgs.hip).
-int mgs_resident_per(long n);
+bool mgs_resident_fits(long n);
 bool mgs_resident_available();
 hipError_t launch_mgs_resident(const Work& W, const double* w, const double* V, long n, int M, int j, double* vnext,
                                hipStream_t st);

@@ -179,8 +179,9 @@ __global__ __launch_bounds__(kRedThreads) void k_norm_scale(const double* partia
 }
 
 __global__ void k_init(double* H, int nh, double* phi, double* lam, int nsm, double* scal, int* ints, int meff0,
-                       unsigned* bar, double* sig, int nsig) {
+                       unsigned* bar, unsigned long long* slots, int nslot, double* sig, int nsig) {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
+    for (int e = t; e < nslot; e += gridDim.x * blockDim.x) slots[e] = kExchangeEmpty;
     for (int e = t; e < kBarWords; e += gridDim.x * blockDim.x) bar[e] = 0u;
     for (int e = t; e < nsig; e += gridDim.x * blockDim.x) sig[e] = 1.0;
     for (int e = t; e < nh; e += gridDim.x * blockDim.x) H[e] = 0.0;
@@ -259,14 +260,6 @@ __global__ __launch_bounds__(kRedThreads) void k_lu(const double* H, int M, doub
 struct GamRow {
     double g[kMaxStages];
 };
-
-// The value of v held by lane `lane` (uniform across the wave) of the calling wave.
-__device__ __forceinline__ double lane_value(double v, int lane) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), lane);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
 
 // phi_i = V^T F_i finished from the projection partials (all columns at once,
 // canonical order per column), then
@@ -498,7 +491,7 @@ size_t work_small_bytes(int M, int s) {
     b += al256(sizeof(double) * Mm * Mm);                        // L
     b += al256(sizeof(double) * (Mm + 1));                       // sig
     b += al256(sizeof(double) * (size_t)npart(M) * kRedBlocks);  // partials
-    b += al256(sizeof(double) * 2 * kRedBlocks);                 // gpart
+    b += al256(sizeof(double) * (M > 0 ? kExchangeSlots : 0));   // gpart
     b += al256(sizeof(unsigned) * kBarWords);                    // barrier
     return b;
 }
@@ -528,7 +521,7 @@ Work carve(void* base, long N, int M, int s, bool step) {
     W.sig = (double*)p;      p += al256(sizeof(double) * (Mm + 1));
     W.partials = (double*)p; p += al256(sizeof(double) * (size_t)npart(M) * kRedBlocks);
     W.npart = npart(M);
-    W.gpart = (double*)p;    p += al256(sizeof(double) * 2 * kRedBlocks);
+    W.gpart = (double*)p;    p += al256(sizeof(double) * (M > 0 ? kExchangeSlots : 0));
     W.bar = (unsigned*)p;    p += al256(sizeof(unsigned) * kBarWords);
     size_t vec = al256(sizeof(double) * (size_t)N);
     W.w = (double*)p;        p += vec;
@@ -588,7 +581,7 @@ hipError_t launch_init(const Work& W, int M, int s, hipStream_t st) {
     int Mm = M > 0 ? M : 1;
     int ss = s > 0 ? s : 1;
     hipLaunchKernelGGL(k_init, dim3(16), dim3(256), 0, st, W.H, (Mm + 1) * Mm, W.phi, W.lam, ss * Mm, W.scal, W.ints,
-                       M, W.bar, W.sig, Mm + 1);
+                       M, W.bar, (unsigned long long*)W.gpart, M > 0 ? kExchangeSlots : 0, W.sig, Mm + 1);
     return hipGetLastError();
 }
 

@@ -1,24 +1,58 @@
 // Modified Gram-Schmidt for one Arnoldi column with the work vector resident
-// in registers (Sec. 2.2.2, modified Arnoldi).
+// on chip (Sec. 2.2.2, modified Arnoldi).
 //
 // The column's passes h_ij = <v_i, w>, w <- w - h_ij v_i (i = 0..j) and the
 // norm h_{j+1,j} = ||w|| are dependent global reductions.  Launched as one
 // kernel per pass, each pass streams w in and out (4 vectors of traffic);
-// here one cooperative kernel keeps w in registers for the whole column, so a
-// pass reads only v_i, and the blocks meet at an in-kernel barrier after each
-// partial sum.
+// here one kernel keeps w on chip for the whole column, so a pass reads only
+// v_i, and its blocks exchange their sums after each pass.
 //
-// Summation order is the canonical one of the per-pass kernels: thread t of
-// the grid (256 blocks x 1024 threads = 262144 lanes) is lane t, it adds the
-// elements t, t + T, t + 2T, ... in index order, each group of 256
-// consecutive lanes is combined by the halving tree into one of 1024
-// partials, and every block finishes the sum from all 1024 partials in the
-// same order, so all blocks hold bit-identical h_ij.
+// Summation order is the canonical one of the per-pass kernels: 262144 lanes,
+// lane t adds the elements t, t + T, t + 2T, ... (T = 262144) in index order,
+// each group of 256 consecutive lanes is combined by the halving tree into one
+// of 1024 partials, lane t of 256 adds partials t, t + 256, t + 512, t + 768 in
+// order, and the halving tree over those 256 lanes gives the sum.  Which block
+// holds which group does not enter the result.  A grid of NB blocks (a power
+// of two) gives block b the groups g = b (mod NB): their partials are whole
+// subtrees of the final tree, so a block hands on ONE value (its 256 / NB
+// final lanes, already combined down to lane b) and NB values finish the sum.
 //
-// Cross-block traffic inside the kernel is limited to the 1024 partials and
-// the barrier counters, all accessed with agent-scope atomics (coherent
-// across XCDs without an L2 write-back); every spin is bounded and reports a
-// status flag instead of hanging.
+// Exchange (NB > 1): no counters and no barrier.  Each block stores its value
+// into its slot of one of three buffers; wave 0 of every block polls all NB
+// slots until none holds the empty mark (a signalling-NaN bit pattern, which no
+// sum can produce) and then finishes the tree from the registers it polled
+// into: one store and one load across the chip, where arriving at a two-level
+// counter barrier and then loading 1024 partials took five dependent ones.
+// A buffer has kCopies copies of its slots, written together and polled by
+// one block in kCopies each: 256 blocks polling the same 16 cache lines queue
+// up at the few memory channels that hold them (a sum over 256 blocks with no
+// loads in flight: 3.1 us with one copy, 2.2 with 4, 1.8 with 8, 2.0 with 16,
+// 2.2 with 32; over 64 blocks 2.9, 2.2, 1.9, 1.8, 1.8).
+// After exchange p every block has finished exchange p - 1, so a block empties its
+// slots of buffer (p - 1) mod 3 then; they are written again in exchange p + 2.
+// The exchange number continues from launch to launch (kBarPhase; the slots
+// of the last exchange of a launch are emptied by the first of the next, which
+// between two launch_init has at least as many blocks).
+// All of it uses agent-scope atomics (coherent across XCDs without an L2
+// write-back); every spin is bounded and reports a status flag instead of
+// hanging.
+//
+// Loads of the next basis vector: in flight, they delay the exchange's store
+// and polls, which queue behind them.  Half are issued before the block's
+// tree, which they overlap, and the rest when the block's value is out (an extra
+// block barrier tells the other waves).  Pass time with 8 elements per thread, 256 blocks: everything
+// before the tree 4.0 us, half before and half after the sum 3.7 us, this way 3.3 us.
+//
+// Grids by size (n elements; a block has 1024 threads):
+//   n <= 8192            one block, no exchange: up to 8 elements per thread
+//   n <= 65536           eight blocks, up to 8 elements per thread
+//   n <= 4194304         256 blocks, up to 16 elements per thread, cooperative
+// An exchange needs all blocks of its grid resident.  256 blocks fill the
+// chip, so only a cooperative launch guarantees that (it costs about 15 us
+// more than a plain one); eight blocks do not need it: a device
+// runs at most one kernel per hardware queue at a time (streams on one queue
+// are serialised; 4 queues by default, 32 at most), so at most 32 x 8 = 256
+// blocks wait in exchanges, one per CU, and every other kernel drains.
 //
 // The same machinery runs the reverse of a column for the discrete adjoint
 // of the step (k_mgs_rev_resident below): the normalisation and the passes
@@ -30,7 +64,10 @@
 namespace rok {
 
 constexpr int kPT = 1024;                       // threads per block
-constexpr int kPB = kRedBlocks * kRedThreads / kPT;  // 256 blocks
+constexpr int kLanes = kRedBlocks * kRedThreads;     // canonical lanes (262144)
+constexpr int kBigGrid = kLanes / kPT;               // 256 blocks: the cooperative grid
+constexpr int kMidGrid = 8;                          // the plain grid (see above)
+constexpr int kCopies = kExchangeCopies;             // copies of the exchange slots
 constexpr double kBreakdownTolR = 1e-13;
 constexpr long kSpinLimit = 1L << 22;
 // s_waitcnt operand with vmcnt = 0 and the other counters at their maximum
@@ -39,172 +76,265 @@ constexpr int kWaitVmcnt0 = 0x0F70;
 
 #define AGENT __HIP_MEMORY_SCOPE_AGENT
 
-// Grid barrier, two levels: the blocks are split into kBarGroups groups;
-// the last arrival of a group bumps the top counter, the last arrival at the
-// top bumps the generation everyone waits on.  Counters sit on separate
-// 128-byte lines.  bar (unsigned): [g * 32] group g arrivals, [kBarTop] top
-// arrivals, [kBarGen] generation, [kBarErr] error.  Run by thread 0 only;
-// returns true if the barrier failed (spin limit).
-constexpr int kBarGroups = 16;
-constexpr int kBarTop = kBarGroups * 32;
-constexpr int kBarGen = kBarTop + 32;
-constexpr int kBarErr = kBarGen + 32;
+// exchange words in Work::bar (unsigned): the number of the next exchange modulo 3, and the error word
+constexpr int kBarPhase = 0;
+constexpr int kBarErr = 32;
 
-__device__ __forceinline__ bool grid_arrive_wait(unsigned* bar) {
-    const unsigned per_group = gridDim.x / kBarGroups;
-    const unsigned grp = blockIdx.x / per_group;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    unsigned g = __hip_atomic_load(bar + kBarGen, __ATOMIC_RELAXED, AGENT);
-    unsigned a = __hip_atomic_fetch_add(bar + grp * 32, 1u, __ATOMIC_RELAXED, AGENT);
-    bool released = false;
-    if (a == per_group - 1) {
-        __hip_atomic_store(bar + grp * 32, 0u, __ATOMIC_RELAXED, AGENT);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        unsigned t = __hip_atomic_fetch_add(bar + kBarTop, 1u, __ATOMIC_RELAXED, AGENT);
-        if (t == kBarGroups - 1) {
-            __hip_atomic_store(bar + kBarTop, 0u, __ATOMIC_RELAXED, AGENT);
+// The lanes of a block: thread tid of block b holds, for k < K and c < C, the
+// element of lane (g * 256 + (tid & 255)), chunk c, of group
+// g = b + NB (tid / 256 + 4 k).  E = K C elements per thread.
+template <int NB_, int K_, int C_>
+struct Lanes {
+    static constexpr int NB = NB_, K = K_, C = C_, E = K_ * C_;
+    static_assert(NB * 4 * K <= kRedBlocks, "groups past the canonical 1024");
+    static_assert(C == 1 || 4 * K * NB == kRedBlocks, "chunks only where every lane of the grid is held");
+    static __device__ __forceinline__ int base() {
+        return (blockIdx.x + NB * (threadIdx.x >> 8)) * kRedThreads + (threadIdx.x & (kRedThreads - 1));
+    }
+    static constexpr __device__ int step(int x) { return (x / C) * (NB * kPT) + (x % C) * kLanes; }
+};
+
+// In-wave halving of K values at once: value k's six levels s_i + s_{i+h}, h = 32,
+// 16, 8, 4, 2, 1.  While several values are left, a level leaves one value in the
+// lanes without bit h and another in the lanes with it (one exchange and one
+// addition for both); the additions are those of each value's own tree.
+// Afterwards the sum of value k is in lane tree_lane(k) (K <= 8).
+__host__ __device__ constexpr int tree_lane(int k) { return 32 * (k & 1) + 16 * ((k >> 1) & 1) + 8 * ((k >> 2) & 1); }
+
+template <int K>
+__device__ __forceinline__ double wave_tree(double (&v)[K]) {
+    static_assert(K == 1 || K == 2 || K == 4 || K == 8, "a power of two up to 8");
+    double a[(K + 1) / 2], b[(K + 3) / 4], r;
+#pragma unroll
+    for (int k = 0; k < (K + 1) / 2; ++k) {
+        if constexpr (K >= 2) a[k] = swap_add<32>(v[2 * k], v[2 * k + 1]);
+        else a[0] = v[0] + lane_down<32>(v[0]);
+    }
+#pragma unroll
+    for (int k = 0; k < (K + 3) / 4; ++k) {
+        if constexpr (K >= 4) b[k] = swap_add<16>(a[2 * k], a[2 * k + 1]);
+        else b[0] = a[0] + lane_down<16>(a[0]);
+    }
+    if constexpr (K == 8) r = swap_add<8>(b[0], b[1]);
+    else r = b[0] + lane_down<8>(b[0]);
+    r = r + lane_down<4>(r);
+    r = r + lane_down<2>(r);
+    r = r + lane_down<1>(r);
+    return r;
+}
+
+// LDS of one exchange: the block trees' cross-wave levels (SK values per thread), the group sums, the result
+template <int K>
+struct ExLds {
+    static constexpr int SK = K;
+    static_assert(K <= 8, "the block trees' LDS");
+    double s[SK][kPT];
+    double gs[4 * K];
+    double out;
+    int err;
+};
+
+// The block's value of one canonical sum: acc[k] is this thread's lane sum of
+// its group k.  Returned in wave 0 (every lane); other waves return garbage.
+// The cross-wave levels of a 256-lane tree, s_i + s_{i+128} then s_i + s_{i+64}, are
+// (x_i + x_{i+128}) + (x_{i+64} + x_{i+192}), taken by one wave after one block barrier.
+template <class L>
+__device__ __forceinline__ double block_value(double (&acc)[L::K], ExLds<L::K>& X) {
+    constexpr int K = L::K, SK = ExLds<K>::SK;
+    const int tid = threadIdx.x, lane = tid & 63;
+    auto quad = [&](int k, int sub) -> double {
+        const double* p = X.s[k] + sub * kRedThreads + lane;
+        return (p[0] + p[128]) + (p[64] + p[192]);
+    };
+    if constexpr (K == 1 && 4 * L::NB == kRedBlocks) {
+        // the four sub-blocks' groups are the four partials of one final lane: wave 0 takes all four
+        X.s[0][tid] = acc[0];
+        __syncthreads();
+        double p = 0.0;
+        if (tid < 64) {
+            double v[4] = {quad(0, 0), quad(0, 1), quad(0, 2), quad(0, 3)};
+            const double t = wave_tree<4>(v);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) p = p + lane_value(t, tree_lane(q));
+        }
+        return p;
+    } else {
+        // the 4 K trees are dealt over the 16 waves: wave 4 sub + q takes those of sub-block sub with k = q (mod 4)
+#pragma unroll
+        for (int k = 0; k < SK; ++k) X.s[k][tid] = acc[k];
+        __syncthreads();
+        constexpr int P = K < 4 ? 1 : K / 4;   // trees per wave
+        const int kw = (tid >> 6) & 3, sub = tid >> 8;
+        if (K >= 4 || kw < K) {
+            double v[P];
+#pragma unroll
+            for (int q = 0; q < P; ++q) v[q] = quad(kw + 4 * q, sub);
+            const double t = wave_tree<P>(v);
+#pragma unroll
+            for (int q = 0; q < P; ++q)
+                if (lane == tree_lane(q)) X.gs[sub + 4 * (kw + 4 * q)] = t;
+        }
+        __syncthreads();
+        double x = 0.0;
+        if (tid < 64) {
+            // group m = r + R q of the block is partial q of its final lane r
+            constexpr int R = kRedThreads / L::NB, Q = (4 * K + R - 1) / R;
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (lane < R && lane + R * q < 4 * K) x = x + X.gs[lane + R * q];
+            double v[1] = {x};   // lanes past the last hold 0: their levels add +0.0
+            x = lane_value(wave_tree<1>(v), 0);
+        }
+        return x;
+    }
+}
+
+// An empty slot: a signalling NaN, which arithmetic never returns (a partial of these very bits, which could
+// only be passed through from the caller's data, is published as another NaN).
+constexpr unsigned long long kEmptySlot = kExchangeEmpty;
+
+// Canonical sum over the grid of the lane sums acc[k]; every thread gets it in
+// *out.  phase: the exchange's number modulo 3, advanced.  mid() runs in the
+// waves 1-15 once the block's value is out, after() in wave 0 once the other
+// blocks' values have arrived (its loads would otherwise delay the polls:
+// loads return in order).  One block alone calls neither.  False (in every thread of the
+// block) if the exchange failed.
+template <class L, typename Mid, typename After>
+__device__ __forceinline__ bool grid_sum(double (&acc)[L::K], ExLds<L::K>& X, double* slots, int& phase, unsigned* bar,
+                                         double* out, Mid mid, After after) {
+    constexpr int NB = L::NB;
+    const int tid = threadIdx.x;
+    double v = block_value<L>(acc, X);
+    if constexpr (NB == 1) {
+        if (tid == 0) X.out = v;
+        __syncthreads();
+        *out = X.out;
+        return true;
+    } else {
+        constexpr int kBuf = kCopies * kRedThreads;   // slots of one buffer
+        unsigned long long* buf = (unsigned long long*)slots + phase * kBuf;
+        if (tid < 64) {
+            // the slots emptied after the last exchange are seen empty before this value is seen
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __hip_atomic_fetch_add(bar + kBarGen, 1u, __ATOMIC_RELAXED, AGENT);
-            released = true;
-        }
-    }
-    if (!released) {
-        long spins = 0;
-        while (__hip_atomic_load(bar + kBarGen, __ATOMIC_RELAXED, AGENT) == g) {
-            if (++spins > kSpinLimit) {
-                __hip_atomic_store(bar + kBarErr, 1u, __ATOMIC_RELAXED, AGENT);
-                break;
+            __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+            if (tid < kCopies) {
+                unsigned long long u = (unsigned long long)__double_as_longlong(v);
+                if (u == kEmptySlot) u = 0x7ff8000000000000ull;
+                __hip_atomic_store(buf + tid * kRedThreads + blockIdx.x, u, __ATOMIC_RELAXED, AGENT);
             }
-            __builtin_amdgcn_s_sleep(1);
         }
+        __syncthreads();
+        if (tid >= 64) {
+            mid();
+        } else {
+            const unsigned long long* mine = buf + (blockIdx.x % kCopies) * kRedThreads;
+            constexpr int Q = (NB + 63) / 64;
+            unsigned long long u[Q];
+            long spins = 0;
+            int err = 0;
+            for (;;) {
+                bool miss = false;
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const int b = tid + 64 * q;
+                    u[q] = (NB >= 64 || b < NB) ? __hip_atomic_load(mine + b, __ATOMIC_RELAXED, AGENT) : 0ull;
+                }
+#pragma unroll
+                for (int q = 0; q < Q; ++q) miss = miss || u[q] == kEmptySlot;
+                if (!__any(miss)) break;
+                if (++spins > kSpinLimit ||
+                    ((spins & 1023) == 0 && __hip_atomic_load(bar + kBarErr, __ATOMIC_RELAXED, AGENT))) {
+                    if (tid == 0) __hip_atomic_store(bar + kBarErr, 1u, __ATOMIC_RELAXED, AGENT);
+                    err = 1;
+                    break;
+                }
+            }
+            after();
+            double x;
+            if constexpr (Q == 4)   // final lanes t and t + 128, then t and t + 64
+                x = (__longlong_as_double((long long)u[0]) + __longlong_as_double((long long)u[2])) +
+                    (__longlong_as_double((long long)u[1]) + __longlong_as_double((long long)u[3]));
+            else
+                x = __longlong_as_double((long long)u[0]);   // lanes past NB hold 0
+            static_assert(Q == 4 || Q == 1, "256 blocks, or at most 64");
+            double t[1] = {x};
+            v = lane_value(wave_tree<1>(t), 0);
+            if (tid < kCopies)
+                __hip_atomic_store((unsigned long long*)slots + (phase == 0 ? 2 : phase - 1) * kBuf + tid * kRedThreads +
+                                       blockIdx.x,
+                                   kEmptySlot, __ATOMIC_RELAXED, AGENT);
+            if (tid == 0) {
+                X.out = v;
+                X.err = err;
+            }
+        }
+        __syncthreads();
+        phase = phase == 2 ? 0 : phase + 1;
+        *out = X.out;
+        return X.err == 0;
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    return __hip_atomic_load(bar + kBarErr, __ATOMIC_RELAXED, AGENT) != 0;
 }
 
-// Canonical sum of the lane values `acc` over the grid, in two halves so the
-// caller can issue independent loads in between: publish() combines the
-// block's lanes into its four 256-lane group sums (left in LDS), collect()
-// stores them, waits for every block and finishes the sum (every block
-// obtains the same bits).  Only wave 0 touches global memory in collect(),
-// so the other waves may keep loads in flight across it.
-// part: 2 x kRedBlocks doubles, `phase` selects the half.
-__device__ __forceinline__ void publish(double acc, double* s, double* gs) {
-    const int tid = threadIdx.x;
-    const double g = tree256(acc, s);
-    if ((tid & (kRedThreads - 1)) == 0) gs[tid / kRedThreads] = g;
-}
-
-// Wave 0 stores the block's four partials, runs the barrier and then
-// finishes the sum alone: lane l holds the canonical lanes t = l + 64 m
-// (m = 0..3), each the in-order sum of partials t, t + 256, t + 512, t + 768;
-// the first two levels of the halving tree (t += t + 128, then t += t + 64)
-// are additions within the lane and the last six are shuffles, the same
-// operations in the same order as the block tree.  after_loads() runs in
-// wave 0 once the partial loads are issued (the caller's prefetch: loads
-// complete in order, so the sum does not wait for them).
-// Returns false (in every thread of the block) if the barrier failed.
-template <typename AfterLoads>
-__device__ __forceinline__ bool collect(double* part, int phase, unsigned* bar, const double* gs, double* out,
-                                        AfterLoads after_loads) {
-    const int tid = threadIdx.x;
-    __shared__ double s_out;
-    __shared__ int s_err;
-    static_assert(kPT == kRedBlocks && kRedThreads == 256, "one partial per thread, 256-lane groups");
-    __syncthreads();
-    if (tid < 64) {
-        if (tid < kPT / kRedThreads)
-            __hip_atomic_store(part + phase * kRedBlocks + blockIdx.x * (kPT / kRedThreads) + tid, gs[tid],
-                               __ATOMIC_RELAXED, AGENT);
-        // the partials must have reached the coherent level before the arrival
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-        int err = 0;
-        if (tid == 0) err = grid_arrive_wait(bar) ? 1 : 0;
-        err = __shfl(err, 0, 64);
-        if (tid == 0) s_err = err;
-        if (!err) {
-            const double* p = part + phase * kRedBlocks;
-            double pv[16];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) pv[q] = __hip_atomic_load(p + tid + 64 * q, __ATOMIC_RELAXED, AGENT);
-            after_loads();
-            double a[4];
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                double x = 0.0;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) x = x + pv[m + 4 * r];
-                a[m] = x;
-            }
-            a[0] = a[0] + a[2];
-            a[1] = a[1] + a[3];
-            double v = a[0] + a[1];
-#pragma unroll
-            for (int h = 32; h > 0; h >>= 1) v = v + __shfl_down(v, h, 64);
-            if (tid == 0) s_out = v;
-        }
-    }
-    __syncthreads();
-    if (s_err) return false;
-    *out = s_out;
-    return true;
+// A failed exchange: the results are invalid; later columns do nothing.
+__device__ __forceinline__ void exchange_failed(int* ints, bool stop) {
+    if (threadIdx.x != 0) return;
+    if (stop) __hip_atomic_store(ints + 1, 1, __ATOMIC_RELAXED, AGENT);
+    __hip_atomic_fetch_or(ints + 2, (int)ROK_FLAG_BARRIER, __ATOMIC_RELAXED, AGENT);
 }
 
 // Buffer descriptor word 3 for raw (untyped, unswizzled) loads on gfx9-class
 // devices: data format 32 (a zero format would make every access out of range).
 constexpr int kBufWord3 = 0x00020000;
 
-// Sixteenths of the next basis vector the waves 1-15 load before a pass's
-// exchange (the rest right after it).  Measured at 1024^2, column time in
-// HIP events: all before 105.7 us, half 103.4 us, a quarter 105.1 us, none
-// 106.0 us.
-constexpr int kPrefetchEarly = 8;
+// Loads of the basis vectors: the share (in sixteenths) of the next vector that the waves 1-15 load before
+// a pass's block tree, the rest when the block's value is out, and the cache hint (2: non-temporal).  Past 2 M
+// elements (16 per thread) the basis is larger than the last-level cache: non-temporal, and a quarter early
+// (1024^2 step: 3038 us; half early 3083, none 3075, half early with plain loads 3101).  Below, plain loads, whose
+// lines a later column finds again, and half early (64^3 basis of 24: 3327 us; none early 3544, all
+// early 3599, half early with the non-temporal hint 3556).
+template <class L>
+struct Fetch {
+    static constexpr bool kLarge = L::E >= 16;
+    static constexpr int kHint = kLarge ? 2 : 0;
+    static constexpr int kEarly = L::NB == 1 ? 16 : (kLarge ? 4 : 8);
+};
 
-// x[k] = src[t + k T] for the chunks of lane t that lie below n, +0.0 past
-// the end.  Raw buffer loads with the range n * 8 bytes: an offset past the
+// x[i] = the lane's element i of src where it lies below n, +0.0 past the end,
+// for X0 <= i < X1 (the rest of x untouched).  Raw buffer loads with the range
+// n * 8 bytes: an offset past the
 // range reads as zero without touching memory, so the loads need no per-lane
 // condition (no exec-masked branches, whose joins would make the compiler
 // wait for every outstanding load, prefetches included).  All offsets are in
-// the lane's offset register, which is what the range check covers.
-// chunks k0 <= k < k1 only (the rest of x untouched)
-template <int PER, int K0, int K1, int AUX>
-__device__ __forceinline__ void load_chunks(const double* __restrict__ src, long n, int t, double (&x)[PER]) {
-    constexpr int T = kPB * kPT;
+// the lane's offset register, which is what the range check covers; an opaque
+// base offset has the element offsets formed next to each load instead of
+// being held in registers across the whole kernel.
+template <class L, int X0, int X1, int AUX>
+__device__ __forceinline__ void load_range(const double* __restrict__ src, long n, double (&x)[L::E]) {
     const __amdgpu_buffer_rsrc_t r =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(src), (short)0, (int)(n * 8), kBufWord3);
-    int off = t * 8;
+    int off = L::base() * 8;
     asm volatile("" : "+v"(off));
 #pragma unroll
-    for (int k = K0; k < K1; ++k)
-        x[k] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off + k * T * 8, 0, AUX));
+    for (int i = X0; i < X1; ++i)
+        x[i] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off + L::step(i) * 8, 0, AUX));
 }
 
-template <int PER, int AUX = 0>
-__device__ __forceinline__ void load_lane(const double* __restrict__ src, long n, int t, double (&x)[PER]) {
-    constexpr int T = kPB * kPT;
-    const __amdgpu_buffer_rsrc_t r =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(src), (short)0, (int)(n * 8), kBufWord3);
-    // an opaque base offset: the chunk offsets are formed next to each load
-    // instead of being held in registers across the whole kernel
-    int off = t * 8;
-    asm volatile("" : "+v"(off));
-#pragma unroll
-    for (int k = 0; k < PER; ++k)
-        x[k] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off + k * T * 8, 0, AUX));
+template <class L, int AUX = 0>
+__device__ __forceinline__ void load_lane(const double* __restrict__ src, long n, double (&x)[L::E]) {
+    load_range<L, 0, L::E, AUX>(src, n, x);
 }
 
-// dst[t + k T] = x[k] for the chunks of lane t below n (raw buffer stores
+// dst's elements of the lane = x where they lie below n (raw buffer stores
 // with the range n * 8 bytes: stores past it are dropped).
-template <int PER>
-__device__ __forceinline__ void store_lane(double* __restrict__ dst, long n, int t, const double (&x)[PER]) {
-    constexpr int T = kPB * kPT;
+template <class L>
+__device__ __forceinline__ void store_lane(double* __restrict__ dst, long n, const double (&x)[L::E]) {
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(dst, (short)0, (int)(n * 8), kBufWord3);
     using B64 = decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0));
-    int off = t * 8;
+    int off = L::base() * 8;
     asm volatile("" : "+v"(off));
 #pragma unroll
-    for (int k = 0; k < PER; ++k)
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(B64, x[k]), r, off + k * T * 8, 0, 0);
+    for (int i = 0; i < L::E; ++i)
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(B64, x[i]), r, off + L::step(i) * 8, 0, 0);
 }
 
 // Work vector storage of one lane: registers, or (PER = 16, where three
@@ -221,78 +351,79 @@ struct LaneVec {
     }
 };
 
-template <int PER>
+template <class L>
 __global__ __launch_bounds__(kPT) void k_mgs_resident(const double* wsrc, const double* V, long n, int M, int j,
-                                                     double* H, double* vnext, int* ints, double* part,
+                                                     double* H, double* vnext, int* ints, double* slots,
                                                      unsigned* bar) {
-    constexpr bool LDSW = PER >= 16;
-    __shared__ double s[kPT];
-    __shared__ double s_w[LDSW ? PER * kPT : 1];
-    __shared__ int s_stop;
-    if (threadIdx.x == 0) s_stop = ints[1];
+    constexpr int E = L::E, K = L::K, C = L::C;
+    constexpr bool LDSW = E >= 16;
+    __shared__ ExLds<K> X;
+    __shared__ double s_w[LDSW ? E * kPT : 1];
+    __shared__ int s_stop, s_phase;
+    if (threadIdx.x == 0) {
+        s_stop = ints[1];
+        s_phase = L::NB > 1 ? (int)bar[kBarPhase] : 0;
+    }
     __syncthreads();
     if (s_stop) return;
-    constexpr long T = (long)kPB * kPT;
-    const int t = blockIdx.x * kPT + threadIdx.x;
-    const int nk = (t < n) ? (int)((n - 1 - t) / T) + 1 : 0;   // chunks of lane t inside the vector
-    // Wave 0 runs the grid barrier; the other waves issue the loads of the
-    // next basis vector as soon as its register array is free (right after
-    // the pass's update), so they stay in flight across the block tree and
-    // the exchange, and wave 0 issues its own behind the loads of the
-    // partials.  A pass then costs about max(load, tree + exchange).  Two
-    // basis-vector arrays alternate: at pass i one holds v_{i-1} (for the
-    // update w -= h v_{i-1}) and v_{i+1} is loaded into it after use.
-    const bool prefetch = threadIdx.x >= 64;
+    int phase = s_phase;
+    // Two basis-vector arrays alternate: at pass i one holds v_{i-1} (for the
+    // update w -= h v_{i-1}) and v_{i+1} is loaded into it after use: by the
+    // waves 1-15 before and during the exchange, by wave 0, which polls, when
+    // its polls are done (one block alone: by every wave at once).
+    const bool prefetch = L::NB == 1 || threadIdx.x >= 64;
     // Lanes past the end hold +0.0: their products are +0.0 and adding +0.0
     // to a lane sum that starts at +0.0 leaves it unchanged.
-    LaneVec<PER, LDSW> w;
+    LaneVec<E, LDSW> w;
     w.l = s_w;
     {
-        double x[PER];
-        load_lane<PER>(wsrc, n, t, x);
+        double x[E];
+        load_lane<L>(wsrc, n, x);
 #pragma unroll
-        for (int k = 0; k < PER; ++k) w.set(k, x[k]);
+        for (int i = 0; i < E; ++i) w.set(i, x[i]);
     }
-    double A[PER], B[PER];
-    load_lane<PER, 2>(V, n, t, A);
+    double A[E], B[E];
+    load_lane<L, Fetch<L>::kHint>(V, n, A);
     __shared__ double s_hcol[kMaxM + 1];
-    __shared__ double s_gs[kPT / kRedThreads];
-    int phase = 0;
     double h = 0.0;
     bool failed = false;
     auto none = [] {};
     // Pass i with cur = v_i and prev = v_{i-1}: w -= h_{i-1} prev (i > 0),
     // h_i = <v_i, w>, then prev <- v_{i+1}.
-    auto pass = [&](int i, double (&cur)[PER], double (&prev)[PER]) {
-        double acc = 0.0;
+    auto pass = [&](int i, double (&cur)[E], double (&prev)[E]) {
+        double acc[K];
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            double wk = w.get(k);
-            if (i > 0) {
-                wk = wk - h * prev[k];
-                w.set(k, wk);
+        for (int k = 0; k < K; ++k) {
+            acc[k] = 0.0;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const int x = k * C + c;
+                double wk = w.get(x);
+                if (i > 0) {
+                    wk = wk - h * prev[x];
+                    w.set(x, wk);
+                }
+                acc[k] = acc[k] + cur[x] * wk;
             }
-            acc = acc + cur[k] * wk;
         }
-        // the sum is complete before the loads are issued: otherwise the
+        // the sums are complete before the loads are issued: otherwise the
         // products sink past the (conditional) loads and the merge after them
         // waits for every outstanding load, the prefetch included
-        asm volatile("" : "+v"(acc) : : "memory");
+#pragma unroll
+        for (int k = 0; k < K; ++k) asm volatile("" : "+v"(acc[k]) : : "memory");
         const bool more = i < j;
-        // waves 1-15: the first kPrefetchEarly sixteenths of v_{i+1} before the exchange, the
-        // rest after it (the exchange's loads queue behind whatever stream is in flight)
-        constexpr int KS = (PER * kPrefetchEarly) / 16;
-        if (more && prefetch) load_chunks<PER, 0, KS, 2>(V + (long)(i + 1) * n, n, t, prev);
-        publish(acc, s, s_gs);
-        // unconditional (v_j again after the last pass, 64 lanes' worth), so
-        // that the sum's waits count exactly these loads behind the partials
-        auto wave0_prefetch = [&] { load_lane<PER, 2>(V + (long)(more ? i + 1 : j) * n, n, t, prev); };
-        if (!collect(part, phase, bar, s_gs, &h, wave0_prefetch)) {
+        constexpr int XS = (E * Fetch<L>::kEarly) / 16, kHint = Fetch<L>::kHint;
+        const double* next = V + (long)(more ? i + 1 : j) * n;
+        if (more && prefetch) load_range<L, 0, XS, kHint>(next, n, prev);
+        auto mid = [&] {
+            if (more) load_range<L, XS, E, kHint>(next, n, prev);
+        };
+        // unconditional (v_j again after the last pass, 64 lanes' worth): no branch around the loads
+        auto after = [&] { load_lane<L, kHint>(next, n, prev); };
+        if (!grid_sum<L>(acc, X, slots, phase, bar, &h, mid, after)) {
             failed = true;
             return;
         }
-        phase ^= 1;
-        if (more && prefetch) load_chunks<PER, KS, PER, 2>(V + (long)(i + 1) * n, n, t, prev);
         if (threadIdx.x == 0) s_hcol[i] = h;
         if (blockIdx.x == 0 && threadIdx.x == 0) H[i * M + j] = h;
     };
@@ -306,31 +437,36 @@ __global__ __launch_bounds__(kPT) void k_mgs_resident(const double* wsrc, const 
         ++i;
     }
     if (failed) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            ints[1] = 1;
-            ints[2] |= ROK_FLAG_BARRIER;
-        }
+        exchange_failed(ints, true);
+        return;
+    }
+    auto keep_phase = [&] {   // every block has read the word: all have taken part in an exchange since
+        if (L::NB > 1 && blockIdx.x == 0 && threadIdx.x == 0) bar[kBarPhase] = (unsigned)phase;
+    };
+    if (j + 1 >= M) {
+        keep_phase();
         return;
     }
     // last update w -= h_j v_j (v_j is A after an even number of passes, else B)
     const bool inA = (j % 2) == 0;
-    double acc = 0.0;
+    double acc[K];
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const double wk = w.get(k) - h * (inA ? A[k] : B[k]);
-        w.set(k, wk);
-        acc = acc + wk * wk;
-    }
-    if (j + 1 >= M) return;
-    publish(acc, s, s_gs);
-    double nn;
-    if (!collect(part, phase, bar, s_gs, &nn, none)) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            ints[1] = 1;
-            ints[2] |= ROK_FLAG_BARRIER;
+    for (int k = 0; k < K; ++k) {
+        acc[k] = 0.0;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int x = k * C + c;
+            const double wk = w.get(x) - h * (inA ? A[x] : B[x]);
+            w.set(x, wk);
+            acc[k] = acc[k] + wk * wk;
         }
+    }
+    double nn;
+    if (!grid_sum<L>(acc, X, slots, phase, bar, &nn, none, none)) {
+        exchange_failed(ints, true);
         return;
     }
+    keep_phase();
     const double hn = sqrt(nn);
     double c = 0.0;
     for (int q = 0; q <= j; ++q) c = c + s_hcol[q] * s_hcol[q];
@@ -346,9 +482,10 @@ __global__ __launch_bounds__(kPT) void k_mgs_resident(const double* wsrc, const 
         if (!(hn == hn) || hn == __builtin_inf()) ints[2] |= ROK_FLAG_NONFINITE;
     }
     if (brk) return;
+    double v[E];
 #pragma unroll
-    for (int k = 0; k < PER; ++k)
-        if (k < nk) vnext[t + k * T] = w.get(k) / hn;
+    for (int x = 0; x < E; ++x) v[x] = w.get(x) / hn;
+    store_lane<L>(vnext, n, v);
 }
 
 // Reverse of one Arnoldi column (the discrete adjoint of its modified
@@ -365,17 +502,19 @@ __global__ __launch_bounds__(kPT) void k_mgs_resident(const double* wsrc, const 
 // Every dot product is the canonical sum (the same lane order and finish as
 // the per-pass reverse kernels, whose results this reproduces bit for bit).
 // Nothing runs for j >= M_eff or after a failed in-kernel barrier.
-template <int PER>
+template <class L>
 __global__ __launch_bounds__(kPT) void k_mgs_rev_resident(const double* wsrc, const double* V, double* Vbar,
                                                          const double* H, const double* Hbar, long n, int M, int j,
-                                                         double* wbar_out, int* ints, double* part, unsigned* bar) {
-    __shared__ double s[kPT];
-    __shared__ double s_gs[kPT / kRedThreads];
-    __shared__ int s_m, s_bad;
+                                                         double* wbar_out, int* ints, double* slots,
+                                                         unsigned* bar) {
+    constexpr int E = L::E, K = L::K, C = L::C;
+    __shared__ ExLds<K> X;
+    __shared__ int s_m, s_bad, s_phase;
     __shared__ double s_h[kMaxM + 1], s_hb[kMaxM + 1];   // column j of H and Hbar
     if (threadIdx.x == 0) {
         s_m = ints[0];
         s_bad = (ints[2] & ROK_FLAG_BARRIER) != 0;
+        s_phase = L::NB > 1 ? (int)bar[kBarPhase] : 0;
     }
     if (threadIdx.x < M && threadIdx.x <= j + 1) {
         s_h[threadIdx.x] = H[threadIdx.x * M + j];
@@ -384,66 +523,63 @@ __global__ __launch_bounds__(kPT) void k_mgs_rev_resident(const double* wsrc, co
     __syncthreads();
     const int m = s_m;
     if (j >= m || s_bad) return;
-    const int t = blockIdx.x * kPT + threadIdx.x;
-    const bool prefetch = threadIdx.x >= 64;
     const bool nrm = j + 1 < m;
-    double w[PER], wb[PER], A[PER], B[PER], vb[PER];
-    int phase = 0;
+    double w[E], wb[E], A[E], B[E], vb[E];
+    int phase = s_phase;
     double d = 0.0;
     bool failed = false;
-    // canonical sum of the lane values acc; loads(): the caller's prefetch,
-    // issued by waves 1.. before the block tree and by wave 0 behind the partials
-    auto exchange = [&](double acc, auto loads) {
-        asm volatile("" : "+v"(acc) : : "memory");
-        if (prefetch) loads();
-        publish(acc, s, s_gs);
-        if (!collect(part, phase, bar, s_gs, &d, loads)) failed = true;
-        phase ^= 1;
+    // canonical sum of the lane sums acc; loads(): the caller's prefetch, issued
+    // by the waves 1-15 when the block's value is out and by wave 0 after its polls
+    auto exchange = [&](double (&acc)[K], auto loads) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) asm volatile("" : "+v"(acc[k]) : : "memory");
+        if constexpr (L::NB == 1) loads();
+        if (!grid_sum<L>(acc, X, slots, phase, bar, &d, loads, loads)) failed = true;
     };
     if (nrm) {
-        load_lane<PER>(V + (long)(j + 1) * n, n, t, A);      // v_{j+1}
-        load_lane<PER>(Vbar + (long)(j + 1) * n, n, t, vb);  // vbar_{j+1}
-        double acc = 0.0;
+        load_lane<L>(V + (long)(j + 1) * n, n, A);      // v_{j+1}
+        load_lane<L>(Vbar + (long)(j + 1) * n, n, vb);  // vbar_{j+1}
+        double acc[K];
 #pragma unroll
-        for (int k = 0; k < PER; ++k) acc = acc + vb[k] * A[k];
-        exchange(acc, [&] { load_lane<PER>(V + (long)j * n, n, t, B); });
+        for (int x = 0; x < E; ++x) acc[x / C] = (x % C ? acc[x / C] : 0.0) + vb[x] * A[x];
+        exchange(acc, [&] { load_lane<L>(V + (long)j * n, n, B); });
         if (failed) goto fail;
         const double rho = s_h[j + 1];
         const double coef = s_hb[j + 1] - d / rho;
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
+        for (int k = 0; k < E; ++k) {
             w[k] = rho * A[k];
             wb[k] = vb[k] / rho + coef * A[k];
         }
     } else {
-        load_lane<PER>(wsrc, n, t, w);
+        load_lane<L>(wsrc, n, w);
         for (int i = 0; i <= j; ++i) {
-            load_lane<PER>(V + (long)i * n, n, t, B);
+            load_lane<L>(V + (long)i * n, n, B);
             const double hij = s_h[i];
 #pragma unroll
-            for (int k = 0; k < PER; ++k) w[k] = w[k] - hij * B[k];
+            for (int k = 0; k < E; ++k) w[k] = w[k] - hij * B[k];
         }
 #pragma unroll
-        for (int k = 0; k < PER; ++k) wb[k] = 0.0;
+        for (int k = 0; k < E; ++k) wb[k] = 0.0;
     }
     {   // <wbar, v_j>; meanwhile v_{j-1} and vbar_j arrive
-        double acc = 0.0;
+        double acc[K];
 #pragma unroll
-        for (int k = 0; k < PER; ++k) acc = acc + wb[k] * B[k];
+        for (int x = 0; x < E; ++x) acc[x / C] = (x % C ? acc[x / C] : 0.0) + wb[x] * B[x];
         exchange(acc, [&] {
-            load_lane<PER>(V + (long)(j > 0 ? j - 1 : 0) * n, n, t, A);
-            load_lane<PER>(Vbar + (long)j * n, n, t, vb);
+            load_lane<L>(V + (long)(j > 0 ? j - 1 : 0) * n, n, A);
+            load_lane<L>(Vbar + (long)j * n, n, vb);
         });
         if (failed) goto fail;
     }
     {
         // reverse pass i with cur = v_i, prev = v_{i-1}, vb = vbar_i, d = <wbar, v_i>
-        auto rpass = [&](int i, double (&cur)[PER], double (&prev)[PER]) {
+        auto rpass = [&](int i, double (&cur)[E], double (&prev)[E]) {
             const double h = s_h[i];
             const double hb = s_hb[i] - d;
-            double acc = 0.0;
+            double acc[K];
 #pragma unroll
-            for (int k = 0; k < PER; ++k) {
+            for (int k = 0; k < E; ++k) {
                 const double v = cur[k];
                 const double wo = w[k] + h * v;
                 w[k] = wo;
@@ -451,13 +587,13 @@ __global__ __launch_bounds__(kPT) void k_mgs_rev_resident(const double* wsrc, co
                 vb[k] = vb[k] + hb * wo - h * b;
                 const double wn = b + hb * v;
                 wb[k] = wn;
-                acc = acc + wn * prev[k];
+                acc[k / C] = (k % C ? acc[k / C] : 0.0) + wn * prev[k];
             }
-            store_lane<PER>(Vbar + (long)i * n, n, t, vb);
+            store_lane<L>(Vbar + (long)i * n, n, vb);
             if (i == 0) return;
             exchange(acc, [&] {
-                load_lane<PER>(V + (long)(i > 1 ? i - 2 : 0) * n, n, t, cur);
-                load_lane<PER>(Vbar + (long)(i - 1) * n, n, t, vb);
+                load_lane<L>(V + (long)(i > 1 ? i - 2 : 0) * n, n, cur);
+                load_lane<L>(Vbar + (long)(i - 1) * n, n, vb);
             });
         };
         int i = j;
@@ -471,71 +607,89 @@ __global__ __launch_bounds__(kPT) void k_mgs_rev_resident(const double* wsrc, co
         }
         if (failed) goto fail;
     }
-    store_lane<PER>(wbar_out, n, t, wb);
+    store_lane<L>(wbar_out, n, wb);
+    // every block has read the word: all have taken part in an exchange since
+    if (L::NB > 1 && blockIdx.x == 0 && threadIdx.x == 0) bar[kBarPhase] = (unsigned)phase;
     return;
 fail:
-    if (blockIdx.x == 0 && threadIdx.x == 0) ints[2] |= ROK_FLAG_BARRIER;
+    exchange_failed(ints, false);
 }
 
-template <int PER>
-static hipError_t launch_res(const Work& W, const double* w, const double* V, long n, int M, int j, double* vnext,
-                             hipStream_t st) {
-    long nn = n;
-    int MM = M, jj = j;
-    double* H = W.H;
-    int* ints = W.ints;
-    double* part = W.gpart;
-    unsigned* bar = W.bar;
-    void* args[] = {(void*)&w, (void*)&V, (void*)&nn, (void*)&MM, (void*)&jj, (void*)&H, (void*)&vnext,
-                    (void*)&ints, (void*)&part, (void*)&bar};
-    return hipLaunchCooperativeKernel((const void*)k_mgs_resident<PER>, dim3(kPB), dim3(kPT), args, 0, st);
+// Cooperative for the big grid (all its blocks must be resident together), plain for the small ones.
+template <class L>
+static hipError_t launch_grid(const void* f, void** args, hipStream_t st) {
+    if (L::NB == kBigGrid) return hipLaunchCooperativeKernel(f, dim3(L::NB), dim3(kPT), args, 0, st);
+    return hipLaunchKernel(f, dim3(L::NB), dim3(kPT), args, 0, st);
 }
 
-// Elements per lane the resident kernel supports (0 if n is too large).
-int mgs_resident_per(long n) {
-    const long T = (long)kPB * kPT;
-    long per = (n + T - 1) / T;
-    if (per <= 1) return 1;
-    if (per <= 2) return 2;
-    if (per <= 4) return 4;
-    if (per <= 8) return 8;
-    if (per <= 16) return 16;
-    return 0;
+// The shape of a vector of n elements (n <= 16 * 262144): fn(Lanes<...>{}).  MAXE: most elements per thread
+// the kernel holds.  The lines: one block streams a basis vector of 8192 elements in about the time of an
+// exchange; eight blocks hold 8 elements per thread at 65536 (a pass there takes about 3 us, against 2.2 us plus
+// the cooperative launch's 15 us a column on 256 blocks); past that, 256.
+template <int MAXE, typename Fn>
+static hipError_t with_shape(long n, Fn fn) {
+    if (n <= 1024) return fn(Lanes<1, 1, 1>{});
+    if (n <= 2048) return fn(Lanes<1, 2, 1>{});
+    if (n <= 4096) return fn(Lanes<1, 4, 1>{});
+    if (n <= 8192) return fn(Lanes<1, 8, 1>{});
+    if (n <= 16384) return fn(Lanes<kMidGrid, 2, 1>{});
+    if (n <= 32768) return fn(Lanes<kMidGrid, 4, 1>{});
+    if (n <= 65536) return fn(Lanes<kMidGrid, 8, 1>{});
+    if (n <= kLanes) return fn(Lanes<kBigGrid, 1, 1>{});
+    if (n <= 2L * kLanes) return fn(Lanes<kBigGrid, 1, 2>{});
+    if (n <= 4L * kLanes) return fn(Lanes<kBigGrid, 1, 4>{});
+    if (n <= 8L * kLanes) return fn(Lanes<kBigGrid, 1, 8>{});
+    if constexpr (MAXE >= 16)
+        if (n <= 16L * kLanes) return fn(Lanes<kBigGrid, 1, 16>{});
+    return hipErrorInvalidValue;
+}
+
+// Whether the resident kernel takes vectors of n elements.
+bool mgs_resident_fits(long n) { return n <= 16L * kLanes; }
+
+// True if the device can host kernel f's cooperative grid.
+static bool coop_available(const void* f) {
+    int dev = 0, coop = 0, cus = 0, nb = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, kPT, 0) != hipSuccess)
+        return false;
+    return coop && (long)nb * cus >= kBigGrid;
 }
 
 static int g_coop_ok = -1;
 
 // True if the device can host the cooperative grid (checked once).
 bool mgs_resident_available() {
-    if (g_coop_ok >= 0) return g_coop_ok == 1;
-    int dev = 0, coop = 0, cus = 0, nb = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void*)k_mgs_resident<16>, kPT, 0) != hipSuccess) {
-        g_coop_ok = 0;
-        return false;
-    }
-    g_coop_ok = (coop && (long)nb * cus >= kPB) ? 1 : 0;
+    if (g_coop_ok < 0) g_coop_ok = coop_available((const void*)k_mgs_resident<Lanes<kBigGrid, 1, 16>>) ? 1 : 0;
     return g_coop_ok == 1;
 }
 
 hipError_t launch_mgs_resident(const Work& W, const double* w, const double* V, long n, int M, int j, double* vnext,
                                hipStream_t st) {
-    switch (mgs_resident_per(n)) {
-        case 1: return launch_res<1>(W, w, V, n, M, j, vnext, st);
-        case 2: return launch_res<2>(W, w, V, n, M, j, vnext, st);
-        case 4: return launch_res<4>(W, w, V, n, M, j, vnext, st);
-        case 8: return launch_res<8>(W, w, V, n, M, j, vnext, st);
-        case 16: return launch_res<16>(W, w, V, n, M, j, vnext, st);
-        default: return hipErrorInvalidValue;
-    }
+    double* H = W.H;
+    int* ints = W.ints;
+    double* slots = W.gpart;
+    unsigned* bar = W.bar;
+    void* args[] = {(void*)&w, (void*)&V, (void*)&n, (void*)&M, (void*)&j, (void*)&H, (void*)&vnext,
+                    (void*)&ints, (void*)&slots, (void*)&bar};
+    return with_shape<16>(n, [&](auto shape) {
+        using L = decltype(shape);
+        return launch_grid<L>((const void*)k_mgs_resident<L>, args, st);
+    });
 }
 
-template <int PER>
-static hipError_t launch_rev(const Work& W, const AdjWork& A, long n, int M, int j, hipStream_t st) {
-    long nn = n;
-    int MM = M, jj = j;
+static int g_rev_ok = -1;
+
+// The resident reverse keeps five lane vectors in registers: up to 8 elements per lane.
+bool mgs_rev_resident_available(long n) {
+    if (n > 8L * kLanes) return false;
+    if (g_rev_ok < 0) g_rev_ok = coop_available((const void*)k_mgs_rev_resident<Lanes<kBigGrid, 1, 8>>) ? 1 : 0;
+    return g_rev_ok == 1;
+}
+
+hipError_t launch_mgs_rev_resident(const Work& W, const AdjWork& A, int M, int j, long n, hipStream_t st) {
     const double* wsrc = W.w;
     const double* V = W.V;
     double* Vbar = A.Vbar;
@@ -543,40 +697,14 @@ static hipError_t launch_rev(const Work& W, const AdjWork& A, long n, int M, int
     const double* Hbar = A.Hbar;
     double* wbar = A.wbar;
     int* ints = W.ints;
-    double* part = W.gpart;
+    double* slots = W.gpart;
     unsigned* bar = W.bar;
-    void* args[] = {(void*)&wsrc, (void*)&V,  (void*)&Vbar, (void*)&H,    (void*)&Hbar, (void*)&nn,
-                    (void*)&MM,   (void*)&jj, (void*)&wbar, (void*)&ints, (void*)&part, (void*)&bar};
-    return hipLaunchCooperativeKernel((const void*)k_mgs_rev_resident<PER>, dim3(kPB), dim3(kPT), args, 0, st);
-}
-
-static int g_rev_ok = -1;
-
-// The resident reverse keeps five lane vectors in registers: up to 8 elements per lane.
-bool mgs_rev_resident_available(long n) {
-    const int per = mgs_resident_per(n);
-    if (per == 0 || per > 8) return false;
-    if (g_rev_ok < 0) {
-        int dev = 0, coop = 0, cus = 0, nb = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void*)k_mgs_rev_resident<8>, kPT, 0) != hipSuccess)
-            g_rev_ok = 0;
-        else
-            g_rev_ok = (coop && (long)nb * cus >= kPB) ? 1 : 0;
-    }
-    return g_rev_ok == 1;
-}
-
-hipError_t launch_mgs_rev_resident(const Work& W, const AdjWork& A, int M, int j, long n, hipStream_t st) {
-    switch (mgs_resident_per(n)) {
-        case 1: return launch_rev<1>(W, A, n, M, j, st);
-        case 2: return launch_rev<2>(W, A, n, M, j, st);
-        case 4: return launch_rev<4>(W, A, n, M, j, st);
-        case 8: return launch_rev<8>(W, A, n, M, j, st);
-        default: return hipErrorInvalidValue;
-    }
+    void* args[] = {(void*)&wsrc, (void*)&V,  (void*)&Vbar, (void*)&H,    (void*)&Hbar,  (void*)&n,
+                    (void*)&M,    (void*)&j,  (void*)&wbar, (void*)&ints, (void*)&slots, (void*)&bar};
+    return with_shape<8>(n, [&](auto shape) {
+        using L = decltype(shape);
+        return launch_grid<L>((const void*)k_mgs_rev_resident<L>, args, st);
+    });
 }
 
 }  // namespace rok
