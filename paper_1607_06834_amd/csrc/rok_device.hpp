@@ -122,6 +122,13 @@ template <typename T> struct Sc<Dual<T>> {
     }
 };
 
+// 1 / r (one division; the dual number's tangent by the chain rule)
+__device__ __forceinline__ double recip(double r) { return 1.0 / r; }
+__device__ __forceinline__ Dual<double> recip(Dual<double> r) {
+    const double iv = 1.0 / r.v;
+    return {iv, -(r.d * iv) * iv};
+}
+
 // The FP64 counterpart of a scalar type (double for float, Dual<double> for
 // Dual<float>) and rounding from it.
 template <typename S> struct Wide { using type = S; };
@@ -273,6 +280,13 @@ __device__ __forceinline__ int wrap(int i, int n) {
     if (i >= 0 && i < n) return i;
     int r = i % n;
     return r < 0 ? r + n : r;
+}
+
+// XCD-aware block order: workgroups are dispatched round-robin over the 8
+// XCDs; give each XCD a contiguous range of tiles so halos hit in its L2.
+__device__ __forceinline__ int xcd_remap(int b, int nb) {
+    int q = nb >> 3, r = nb & 7, x = b & 7, i = b >> 3;
+    return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
 }
 
 }  // namespace rok

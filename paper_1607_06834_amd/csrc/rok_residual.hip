@@ -105,20 +105,6 @@ struct Stage {
 template <int D, int TX, int TY, int TZ, int HW, bool NSV>
 __device__ constexpr typename Stage<D, TX, TY, TZ, HW, NSV>::Cells kStageCells = Stage<D, TX, TY, TZ, HW, NSV>::make();
 
-// 1 / r (one division; the dual number's tangent by the chain rule)
-__device__ __forceinline__ double recip(double r) { return 1.0 / r; }
-__device__ __forceinline__ Dual<double> recip(Dual<double> r) {
-    const double iv = 1.0 / r.v;
-    return {iv, -(r.d * iv) * iv};
-}
-
-// XCD-aware block order: workgroups are dispatched round-robin over the 8
-// XCDs; give each XCD a contiguous range of tiles so halos hit in its L2.
-__device__ __forceinline__ int xcd_remap(int b, int nb) {
-    int q = nb >> 3, r = nb & 7, x = b & 7, i = b >> 3;
-    return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
-}
-
 template <int D, int RECON, bool NSV, int FLUX, int GEO, typename S, int MODE, typename OUT, int TX, int TY, int TZ>
 __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt0, int nt1) {
     using T = Tile<D, TX, TY, TZ, (RECON == 0 ? 1 : 2)>;
