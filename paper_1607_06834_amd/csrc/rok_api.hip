@@ -104,12 +104,9 @@ hipError_t arnoldi_core(const rok_ctx* c, const rok::Work& W, const double* y, c
     if (ortho < 0) return hipErrorNotSupported;
     deferred = deferred && ortho == ORTHO_ONE_REDUCE;
     hipError_t e;
-    if (mode == ROK_JVP_FD && !(eps > 0.0)) {
-        e = rok::launch_norm_eps(W, y, nullptr, N, st);  // unit Arnoldi vectors: ||v_j|| = 1
-        if (e != hipSuccess) return e;
-        epsp = W.scal + 1;
-    }
-    e = rok::launch_start_basis(W, fy, N, V, st);
+    const bool own_eps = mode == ROK_JVP_FD && !(eps > 0.0);   // unit Arnoldi vectors: ||v_j|| = 1
+    if (own_eps) epsp = W.scal + 1;
+    e = rok::launch_start_basis(W, fy, N, V, st, own_eps ? y : nullptr);
     if (e != hipSuccess) return e;
     for (int j = 0; j < M; ++j) {
         double* vj = V + (long)j * N;
@@ -149,9 +146,12 @@ hipError_t step_core(const rok_ctx* c, const rok_tableau* tab, int M, int mode, 
     if (M > 0) {
         e = arnoldi_core(c, W, y_n, W.F, M, mode, 0.0, W.V, st, mgs_only, deferred);
         if (e != hipSuccess) return e;
-        e = rok::launch_lu(W, M, h * tab->gamma, st);
-        if (e != hipSuccess) return e;
+        if (deferred) {   // its first stage has no projection kernel to share
+            e = rok::launch_lu(W, M, h * tab->gamma, st);
+            if (e != hipSuccess) return e;
+        }
     }
+    const double hg = h * tab->gamma;
     // Y_i = y_n + sum_{j<i} alpha_ij k_j is written by the recovery of k_{i-1}
     // (into k_i's slot, free until k_i is formed), in the residual's order
     auto has_terms = [&](int i) {
@@ -170,11 +170,12 @@ hipError_t step_core(const rok_ctx* c, const rok_tableau* tab, int M, int mode, 
         if (M > 0) {
             // with the one-reduce basis (not the library's bitwise path) the first stage's
             // projection is taken from F_1 = beta v_0 instead of a pass over the basis
-            e = (i == 0 && deferred) ? rok::launch_project_first(W, M, st) : rok::launch_project(W, W.V, Fi, N, M, st);
+            e = (i == 0 && deferred) ? rok::launch_project_first(W, M, st)
+                                     : rok::launch_project(W, W.V, Fi, N, M, st, i == 0 ? &hg : nullptr);
             if (e != hipSuccess) return e;
             double grow[ROK_MAX_STAGES];
             for (int j = 0; j < ROK_MAX_STAGES; ++j) grow[j] = (j < i) ? tab->gam[i * ROK_MAX_STAGES + j] : 0.0;
-            e = rok::launch_lambda(W, M, i, grow, h, st, sig);
+            e = rok::launch_lambda(W, M, i, grow, h, N, st, sig);
             if (e != hipSuccess) return e;
         }
         if (i + 1 < s && has_terms(i + 1))
@@ -213,7 +214,7 @@ hipError_t step_adjoint(const rok_ctx* c, const rok_tableau* tab, int M, double 
         double grow[ROK_MAX_STAGES];
         for (int j = 0; j < ROK_MAX_STAGES; ++j) grow[j] = (j < i) ? tab->gam[i * ROK_MAX_STAGES + j] : 0.0;
         if (M > 0) {
-            e = rok::launch_small_rev(W, A, Mm, i, grow, h, st);
+            e = rok::launch_small_rev(W, A, Mm, i, grow, h, N, st);
             if (e != hipSuccess) return e;
         }
         double* Fbar = (i == 0) ? A.Fbar0 : A.FB;

@@ -212,6 +212,27 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v + lane_down<1>(v);
 }
 
+// Final stage of the canonical sum by one wave: the blocks' partials p[0 .. nb)
+// (of 1024; those past nb are zero and not read).  Final lane t of 256 adds
+// partials t, t + 256, t + 512, t + 768 in order; lane l holds t = l + 64 m, so the
+// tree's first two levels are additions within the lane and the rest wave_sum.
+// Every lane gets the sum.
+__device__ __forceinline__ double wave_final(const double* p, int nb) {
+    const int l = threadIdx.x & 63;
+    double v[4][4], a[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[m][r] = (l + 64 * m + 256 * r < nb) ? p[l + 64 * m + 256 * r] : 0.0;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        a[m] = 0.0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[m] = a[m] + v[m][r];
+    }
+    return lane_value(wave_sum((a[0] + a[2]) + (a[1] + a[3])), 0);
+}
+
 // Pairwise halving tree over groups of 256 consecutive threads of a block:
 // with x_i the value of lane i of a group, computes s_i <- s_i + s_{i+h} for
 // h = 128, 64, ..., 1 (i < h) and returns s_0 in lane 0 of each group (other

@@ -64,7 +64,9 @@ hipError_t launch_norm_eps(const Work& W, const double* y, const double* v, long
 // *out = sqrt(sum_i q_i^2 / n), q_i = (a_i - b_i) / (c (atol + rtol max(|y_i|, |a_i|)))
 hipError_t launch_error_norm(const Work& W, const double* y, const double* a, const double* b, long n, double rtol,
                              double atol, double c, double* out, hipStream_t st);
-hipError_t launch_start_basis(const Work& W, const double* f, long n, double* v0, hipStream_t st);
+// beta = ||f|| (scal[2]), v0 = f / beta; with y also scal[0] = ||y||, scal[1] = sqrt((1 + ||y||) u)
+hipError_t launch_start_basis(const Work& W, const double* f, long n, double* v0, hipStream_t st,
+                              const double* y = nullptr);
 hipError_t launch_mgs_column(const Work& W, double* w, const double* V, long n, int M, int j, double* vnext,
                              hipStream_t st);
 // v = w / ||w|| with ||w||^2 finished from `partials`, after the breakdown test of column j (H[j+1][j] = ||w||)
@@ -93,11 +95,14 @@ double ritz_residual(int m, const double* H, int ldh, double hlast, double tre, 
 }  // namespace dense
 hipError_t launch_copy_h(const Work& W, int M, double* Hout, int* meff_out, hipStream_t st);
 hipError_t launch_lu(const Work& W, int M, double hg, hipStream_t st);
-hipError_t launch_project(const Work& W, const double* V, const double* F, long n, int M, hipStream_t st);
+// with lu_hg (host): also the LU factors of I - *lu_hg H, in the same launch
+hipError_t launch_project(const Work& W, const double* V, const double* F, long n, int M, hipStream_t st,
+                          const double* lu_hg = nullptr);
 // phi_1 = beta e_1 (F_1 = f(y_n) = beta v_0) as projection partials, without reading V
 hipError_t launch_project_first(const Work& W, int M, hipStream_t st);
 // sig: the basis scales (W.sig) when V holds unnormalised columns, else null
-hipError_t launch_lambda(const Work& W, int M, int i, const double* gam_row, double h, hipStream_t st,
+// n: the vectors' length (the projection's partials it left)
+hipError_t launch_lambda(const Work& W, int M, int i, const double* gam_row, double h, long n, hipStream_t st,
                          const double* sig = nullptr);
 // k_i = V lambda_i + h (F_i - V phi_i) into k; if y is non-null (last stage)
 // writes y_{n+1} = y + sum_{q<s} b_q k_q into k instead, K holding k_0..k_{s-2}.
@@ -133,7 +138,7 @@ hipError_t launch_stage_state(const double* y, const double* K, const double* al
                               hipStream_t st);
 hipError_t launch_scatter(const AdjWork& A, const double* Ybar, double* ybar, const double* alpha_row, int i, long n,
                           hipStream_t st);
-hipError_t launch_small_rev(const Work& W, const AdjWork& A, int M, int i, const double* gam_row, double h,
+hipError_t launch_small_rev(const Work& W, const AdjWork& A, int M, int i, const double* gam_row, double h, long n,
                             hipStream_t st);
 // first: initialise Vbar (the first stage reversed) instead of accumulating.
 hipError_t launch_vbar_stage(const Work& W, const AdjWork& A, int M, int i, double h, double* Fbar, long n,

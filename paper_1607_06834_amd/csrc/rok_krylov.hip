@@ -92,13 +92,13 @@ __global__ __launch_bounds__(kRedThreads) void k_red(double* w, const double* vp
     if (threadIdx.x == 0) partials[blockIdx.x] = bs;
 }
 
-enum { FIN_SQRT_TO = 0, FIN_STORE = 1, FIN_BETA = 2, FIN_EPS = 3 };
+enum { FIN_SQRT_TO = 0, FIN_STORE = 1, FIN_EPS = 2 };
 
 // One block: finishes a sum and applies the bookkeeping of `op`.
 __global__ __launch_bounds__(kRedThreads) void k_finish(const double* partials, int op, double* out, double* scal,
                                                        int* ints, int has_v) {
     __shared__ double s[kRedThreads];
-    if ((op == FIN_STORE || op == FIN_BETA) && ints[1]) return;
+    if (op == FIN_STORE && ints[1]) return;
     double tot = final_sum(partials, s);
     if (threadIdx.x != 0) return;
     if (op == FIN_SQRT_TO) {
@@ -106,15 +106,6 @@ __global__ __launch_bounds__(kRedThreads) void k_finish(const double* partials, 
     } else if (op == FIN_STORE) {
         *out = tot;
         if (nonfinite(tot)) ints[2] |= ROK_FLAG_NONFINITE;
-    } else if (op == FIN_BETA) {
-        double beta = sqrt(tot);
-        scal[2] = beta;
-        if (beta == 0.0) {
-            ints[0] = 0;
-            ints[1] = 1;
-            ints[2] |= ROK_FLAG_ZERO_RHS;
-        }
-        if (nonfinite(beta)) ints[2] |= ROK_FLAG_NONFINITE;
     } else {  // FIN_EPS: eps = sqrt((1 + ||y||) u) [/ ||v||]
         double ny = sqrt(tot);
         scal[0] = ny;
@@ -125,34 +116,81 @@ __global__ __launch_bounds__(kRedThreads) void k_finish(const double* partials, 
 }
 
 // v_{j+1} = w / h_{j+1,j}, h_{j+1,j} = sqrt(w.w) finished from `partials`,
-// after the breakdown test h_{j+1,j} <= tol ||(h_1j, ..., h_{j+1,j})||;
-// for j < 0: v_0 = w / beta (scal[2]).
+// after the breakdown test h_{j+1,j} <= tol ||(h_1j, ..., h_{j+1,j})||.
 __global__ __launch_bounds__(kRedThreads) void k_normalize(const double* w, const double* partials, double* H, int M,
-                                                          int j, double* v, long n, int* ints, const double* scal) {
+                                                          int j, double* v, long n, int* ints) {
     __shared__ double s[kRedThreads];
     if (ints[1]) return;
-    double hn;
-    if (j < 0) {
-        hn = scal[2];
-    } else {
-        hn = sqrt(final_sum(partials, s));
-        double c = 0.0;
-        for (int i = 0; i <= j; ++i) c = c + H[i * M + j] * H[i * M + j];
-        c = c + hn * hn;
-        bool brk = hn <= kBreakdownTol * sqrt(c);
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            H[(j + 1) * M + j] = hn;
-            if (brk) {
-                ints[0] = j + 1;
-                ints[1] = 1;
-                ints[2] |= ROK_FLAG_BREAKDOWN;
-            }
-            if (nonfinite(hn)) ints[2] |= ROK_FLAG_NONFINITE;
+    const double hn = sqrt(final_sum(partials, s));
+    double c = 0.0;
+    for (int i = 0; i <= j; ++i) c = c + H[i * M + j] * H[i * M + j];
+    c = c + hn * hn;
+    const bool brk = hn <= kBreakdownTol * sqrt(c);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        H[(j + 1) * M + j] = hn;
+        if (brk) {
+            ints[0] = j + 1;
+            ints[1] = 1;
+            ints[2] |= ROK_FLAG_BREAKDOWN;
         }
-        if (brk) return;
+        if (nonfinite(hn)) ints[2] |= ROK_FLAG_NONFINITE;
     }
+    if (brk) return;
     const long stride = (long)gridDim.x * blockDim.x;
     for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) v[e] = ld_stream(w + e) / hn;
+}
+
+// Partials of f.f and, with y, of y.y (the two norms a basis starts from), by the
+// first nb blocks' lanes.
+__global__ __launch_bounds__(kRedThreads) void k_norms(const double* y, const double* f, long n, const int* ints,
+                                                      double* pf, double* py) {
+    __shared__ double s[kRedThreads];
+    if (ints[1]) return;
+    const long stride = (long)kRedBlocks * kRedThreads;
+    double af = 0.0, ay = 0.0;
+    for (long e = (long)blockIdx.x * kRedThreads + threadIdx.x; e < n; e += stride) {
+        const double fe = f[e], ye = y ? y[e] : 0.0;
+        af = af + fe * fe;
+        ay = ay + ye * ye;
+    }
+    const double bf = block_sum(af, s);
+    if (threadIdx.x == 0) pf[blockIdx.x] = bf;
+    if (y) {
+        const double by = block_sum(ay, s);
+        if (threadIdx.x == 0) py[blockIdx.x] = by;
+    }
+}
+
+// v_0 = f / beta, beta = ||f|| finished from pf by every block; the first block also keeps beta and, with py,
+// ||y|| and eps = sqrt((1 + ||y||) u).  A zero f ends the basis (M_eff = 0).
+__global__ __launch_bounds__(kRedThreads) void k_start(const double* f, const double* pf, const double* py, int nb,
+                                                      double* v, long n, int* ints, double* scal) {
+    __shared__ double s_beta;
+    if (ints[1]) return;
+    if (threadIdx.x < 64) {
+        const double b = sqrt(wave_final(pf, nb));
+        if (threadIdx.x == 0) s_beta = b;
+    } else if (py && blockIdx.x == 0 && threadIdx.x < 128) {
+        const double ny = sqrt(wave_final(py, nb));
+        if (threadIdx.x == 64) {
+            scal[0] = ny;
+            scal[1] = sqrt((1.0 + ny) * kEpsMach);
+        }
+    }
+    __syncthreads();
+    const double beta = s_beta;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        scal[2] = beta;
+        if (beta == 0.0) {
+            ints[0] = 0;
+            ints[1] = 1;
+            ints[2] |= ROK_FLAG_ZERO_RHS;
+        }
+        if (nonfinite(beta)) ints[2] |= ROK_FLAG_NONFINITE;
+    }
+    if (beta == 0.0) return;
+    const long stride = (long)gridDim.x * blockDim.x;
+    for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) v[e] = f[e] / beta;
 }
 
 // The normalisation's bookkeeping without the division: h_{j+1,j} = sqrt(w.w)
@@ -203,153 +241,148 @@ __global__ void k_copy_h(const double* H, int M, double* Hout, const int* ints, 
     if (t == 0 && meff_out) *meff_out = m;
 }
 
-// LU with partial pivoting of A = I - hg H (M_eff x M_eff) in LDS, one block.
-// Each entry sees the same sequence of operations as the textbook
-// right-looking elimination; rows (and columns) are updated in parallel.
-__global__ __launch_bounds__(kRedThreads) void k_lu(const double* H, int M, double hg, double* LU, int* perm,
-                                                   const int* ints) {
-    __shared__ double A[kMaxM * kMaxM];
-    __shared__ int P[kMaxM];
-    __shared__ int s_piv;
-    const int m = ints[0];
-    const int tid = threadIdx.x;
-    for (int e = tid; e < m * m; e += blockDim.x) {
-        int i = e / m, j = e % m;
-        A[i * kMaxM + j] = (i == j ? 1.0 : 0.0) - hg * H[i * M + j];
-    }
-    for (int i = tid; i < m; i += blockDim.x) P[i] = i;
-    __syncthreads();
+// LU with partial pivoting of A = I - hg H (M_eff x M_eff) by one wave, lane r
+// holding row r in registers.  Each entry sees the same sequence of
+// operations as the textbook right-looking elimination: the first largest |entry| of the column is the pivot, and
+// rows keep their lanes, a swap exchanging their positions only.  After step k
+// a lane's registers hold columns k + 1, ..., so that every step reads register 0
+// for its column; the multipliers go to L (kMaxM x 64 doubles of LDS).  Bound by its
+// chain of pivot searches and divisions.  (A block of four waves on an LDS matrix, five
+// barriers per step: 15.8 us at M = 16, 7 us at M = 8.)
+template <int MB>
+__device__ __forceinline__ void lu_wave(const double* H, int M, double hg, double* LU, int* perm, int m, double* L) {
+    const int lane = threadIdx.x & 63;
+    double a[MB];
+#pragma unroll
+    for (int c = 0; c < MB; ++c)
+        a[c] = (lane < m && c < m) ? (lane == c ? 1.0 : 0.0) - hg * H[lane * M + c] : 0.0;
+    int pos = lane;           // the row's position: final once it has been the pivot row
+    bool alive = lane < m;
     for (int k = 0; k < m; ++k) {
-        if (tid == 0) {
-            int piv = k;
-            for (int r = k + 1; r < m; ++r)
-                if (fabs(A[r * kMaxM + k]) > fabs(A[piv * kMaxM + k])) piv = r;
-            s_piv = piv;
-            if (piv != k) {
-                int t = P[k];
-                P[k] = P[piv];
-                P[piv] = t;
+        const double v = alive ? fabs(a[0]) : -1.0;
+        double mx = (v == v) ? v : -1.0;   // a NaN is never larger
+        mx = fmax(mx, lane_down<32>(mx));
+        mx = fmax(mx, lane_down<16>(mx));
+        mx = fmax(mx, lane_down<8>(mx));
+        mx = fmax(mx, lane_down<4>(mx));
+        mx = fmax(mx, lane_down<2>(mx));
+        mx = lane_value(fmax(mx, lane_down<1>(mx)), 0);
+        const unsigned long long at_k = __ballot(alive && pos == k);
+        const int row_k = __ffsll((long long)at_k) - 1;
+        unsigned long long cand = __ballot(alive && v == mx);
+        int p = row_k;
+        const double vk = lane_value(v, row_k);
+        if (vk == vk && cand) {   // (a NaN in place is kept: nothing compares larger)
+            p = __ffsll((long long)cand) - 1;
+            int best = __builtin_amdgcn_readlane(pos, p);
+            for (cand &= cand - 1; cand; cand &= cand - 1) {   // equal entries: the first position
+                const int q = __ffsll((long long)cand) - 1;
+                const int pq = __builtin_amdgcn_readlane(pos, q);
+                if (pq < best) {
+                    best = pq;
+                    p = q;
+                }
             }
         }
-        __syncthreads();
-        const int piv = s_piv;
-        if (piv != k) {
-            for (int c = tid; c < m; c += blockDim.x) {
-                double t = A[k * kMaxM + c];
-                A[k * kMaxM + c] = A[piv * kMaxM + c];
-                A[piv * kMaxM + c] = t;
-            }
+        const int pos_p = __builtin_amdgcn_readlane(pos, p);
+        if (lane == row_k) pos = pos_p;
+        if (lane == p) {
+            pos = k;
+            alive = false;
         }
-        __syncthreads();
-        for (int r = k + 1 + tid; r < m; r += blockDim.x) A[r * kMaxM + k] = A[r * kMaxM + k] / A[k * kMaxM + k];
-        __syncthreads();
-        const int w = m - k - 1;
-        for (int e = tid; e < w * w; e += blockDim.x) {
-            int r = k + 1 + e / w, c = k + 1 + e % w;
-            A[r * kMaxM + c] = A[r * kMaxM + c] - A[r * kMaxM + k] * A[k * kMaxM + c];
+        const double l = a[0] / lane_value(a[0], p);
+        if (alive) L[k * 64 + lane] = l;
+#pragma unroll
+        for (int c = 1; c < MB; ++c) {
+            const double u = lane_value(a[c], p);
+            if (alive) a[c - 1] = a[c] - l * u;
         }
-        __syncthreads();
     }
-    for (int e = tid; e < m * m; e += blockDim.x) {
-        int i = e / m, j = e % m;
-        LU[i * M + j] = A[i * kMaxM + j];
+    if (lane < m) {
+        for (int c = 0; c < pos; ++c) LU[pos * M + c] = L[c * 64 + lane];
+#pragma unroll
+        for (int c = 0; c < MB; ++c)
+            if (pos + c < m) LU[pos * M + pos + c] = a[c];
+        perm[pos] = lane;
     }
-    for (int i = tid; i < m; i += blockDim.x) perm[i] = P[i];
+}
+
+template <int MB>
+__global__ __launch_bounds__(64) void k_lu(const double* H, int M, double hg, double* LU, int* perm, const int* ints) {
+    __shared__ double L[MB * 64];
+    lu_wave<MB>(H, M, hg, LU, perm, ints[0], L);
 }
 
 struct GamRow {
     double g[kMaxStages];
 };
 
-// phi_i = V^T F_i finished from the projection partials (all columns at once,
-// canonical order per column), then
-// lambda_i = LU^{-1} (h phi_i + h H sum_{j<i} gamma_ij lambda_j) on the same block.
-__global__ __launch_bounds__(kRedThreads) void k_lambda(const double* H, const double* LU, const int* perm, int M,
-                                                       int i, GamRow gr, double h, const double* partials,
-                                                       double* phi, double* lam, int* ints, const double* sig) {
-    __shared__ double s[16][kRedThreads];
-    __shared__ double sphi[kMaxM];
-    __shared__ double sLU[kMaxM * kMaxM], sH[kMaxM * kMaxM];
-    __shared__ double g[kMaxM];
-    __shared__ int sperm[kMaxM];
-    const int tid = threadIdx.x;
-    // Every load whose address does not depend on M_eff is issued first, for the
-    // compiled size M (entries past M_eff are loaded and never used): the first
-    // 16 columns' partials (lane tid adds partials tid, tid + 256, tid + 512,
-    // tid + 768 of each column in order), then LU, H, the pivots and the earlier
-    // lambdas, staged in LDS; one round trip to memory instead of three.
-    static_assert(kRedBlocks == 4 * kRedThreads, "four partials per lane");
-    const int n16 = M < 16 ? M : 16;
-    double pv[16][4];
-#pragma unroll
-    for (int c = 0; c < 16; ++c)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) pv[c][q] = (c < n16) ? partials[(long)c * kRedBlocks + tid + q * kRedThreads] : 0.0;
-    for (int e = tid; e < M * M; e += kRedThreads) {
-        const int r = e / M, c = e % M;
-        sLU[r * kMaxM + c] = LU[e];
-        sH[r * kMaxM + c] = H[e];
+constexpr int kSmallThreads = 1024;   // the reduced solve's block
+constexpr int kLd = kMaxM + 1;        // leading dimension of its LDS matrices: rows and columns without bank conflicts
+
+// phi_i = V^T F_i finished from the projection partials (one column per wave,
+// canonical order), then
+// lambda_i = LU^{-1} (h phi_i + h H sum_{j<i} gamma_ij lambda_j) on wave 0.
+// Bound by latency: one memory round trip, the sums, then about M^2 / 2
+// dependent subtractions.  Every load is issued before the first wait, for the
+// compiled size M (entries past M_eff are loaded and never used).  In the back
+// substitution all products of a row are formed at once (one per lane) and
+// only their subtraction, in increasing column order, is serial.  At M = 16: 16.1 us
+// with 256 threads summing 16 columns through LDS trees and the products in
+// the chain.
+__global__ __launch_bounds__(kSmallThreads) void k_lambda(const double* H, const double* LU, const int* perm, int M,
+                                                         int i, GamRow gr, double h, const double* partials, int nb,
+                                                         double* phi, double* lam, int* ints, const double* sig) {
+    __shared__ double sphi[kMaxM], g[kMaxM];
+    __shared__ double sLU[kMaxM * kLd], sH[kMaxM * kLd];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int m = ints[0];
+    for (int e = tid; e < M * M; e += kSmallThreads) {
+        const int r = e / M, c = e - r * M;
+        sLU[r * kLd + c] = LU[e];
+        sH[r * kLd + c] = H[e];
     }
     if (tid < M) {
-        sperm[tid] = perm[tid];
         double a = 0.0;
         for (int j = 0; j < i; ++j)
             if (gr.g[j] != 0.0) a = a + gr.g[j] * lam[j * M + tid];
         g[tid] = a;
     }
-    const int m = ints[0];
-    for (int c0 = 0; c0 < m; c0 += 16) {
-        const int nc = (m - c0) < 16 ? (m - c0) : 16;
-        if (c0 > 0) {   // columns past the first 16 (M > 16)
-#pragma unroll
-            for (int c = 0; c < 16; ++c)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    pv[c][q] = (c < nc) ? partials[(long)(c0 + c) * kRedBlocks + tid + q * kRedThreads] : 0.0;
-        }
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            if (c < nc) {
-                double acc = 0.0;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) acc = acc + pv[c][q];
-                s[c][tid] = acc;
-            }
-        }
-        __syncthreads();
-        for (int st = kRedThreads / 2; st > 0; st >>= 1) {
-            if (tid < st)
-                for (int c = 0; c < nc; ++c) s[c][tid] = s[c][tid] + s[c][tid + st];
-            __syncthreads();
-        }
+    const int row = (tid < M) ? perm[tid] : tid;
+    for (int c = tid >> 6; c < M; c += kSmallThreads / 64) {
+        const double t = wave_final(partials + (long)c * kRedBlocks, nb);
         // a column stored unnormalised: <v_c, F> = sig_c <V_c, F>
-        if (tid < nc) sphi[c0 + tid] = sig ? s[tid][0] * sig[c0 + tid] : s[tid][0];
-        __syncthreads();
+        if (lane == 0) sphi[c] = sig ? t * sig[c] : t;
     }
+    __syncthreads();
+    if (tid >= 64) return;   // m <= kMaxM = 64: row r on lane r
     if (tid < m) phi[i * M + tid] = sphi[tid];
-    // The reduced solve: the right-hand side row-parallel, the forward substitution
-    // column-parallel (each entry still sees its updates in increasing column order),
-    // the back substitution one row at a time (each row's sum in increasing column
-    // order) with the finished entries broadcast from their lanes.
-    // From here on wave 0 alone (m <= kMaxM = 64: row r on lane r), with no block barrier:
-    // lane values move by lane shuffles and broadcasts.
-    if (tid >= 64) return;
     double x = 0.0;
     if (tid < m) {   // x_r = h phi_r + h (H g)_r
         double hg = 0.0;
-        for (int c = 0; c < m; ++c) hg = hg + sH[tid * kMaxM + c] * g[c];
+        for (int c = 0; c < m; ++c) hg = hg + sH[tid * kLd + c] * g[c];
         x = h * sphi[tid] + h * hg;
     }
-    double yr = __shfl(x, tid < m ? sperm[tid] : tid, 64);   // placed at its pivoted position
-    for (int c = 0; c + 1 < m; ++c) {   // forward substitution with the unit lower factor
+    double yr = __shfl(x, tid < m ? row : tid, 64);   // placed at its pivoted position
+    // forward substitution with the unit lower factor, column by column (each entry's updates in column order)
+    double col = sLU[tid * kLd];
+    for (int c = 0; c + 1 < m; ++c) {
+        const double next = sLU[tid * kLd + c + 1];
         const double yc = lane_value(yr, c);
-        if (tid > c && tid < m) yr = yr - sLU[tid * kMaxM + c] * yc;
+        if (tid > c && tid < m) yr = yr - col * yc;
+        col = next;
     }
-    for (int r = m - 1; r >= 0; --r) {   // back substitution: row r's sum in increasing column order
+    // back substitution, row by row: a_r = y_r - sum_c U_rc y_c in increasing column order
+    double u = m > 0 ? sLU[(m - 1) * kLd + tid] : 0.0;
+    for (int r = m - 1; r >= 0; --r) {
+        const double next = r > 0 ? sLU[(r - 1) * kLd + tid] : 0.0;
+        const double pr = u * yr;
         double a = lane_value(yr, r);
-        for (int c = r + 1; c < m; ++c) a = a - sLU[r * kMaxM + c] * lane_value(yr, c);
-        a = a / sLU[r * kMaxM + r];
+#pragma unroll 4
+        for (int c = r + 1; c < m; ++c) a = a - lane_value(pr, c);
+        a = a / lane_value(u, r);
         if (tid == r) yr = a;
+        u = next;
     }
     if (tid < m) lam[i * M + tid] = yr;
     const bool bad = __any(tid < m && nonfinite(yr));
@@ -359,16 +392,36 @@ __global__ __launch_bounds__(kRedThreads) void k_lambda(const double* H, const d
 // Projection partials: for c < M_eff, canonical per-block partial sums of
 // V[:, c] . F (finished by k_lambda).  MB >= M; the common case M_eff == MB
 // runs a branch-free loop so all loads of an element are in flight together.
+// With lu.LU the grid has one block more, the first, which factorises the
+// step's reduced matrix meanwhile (nothing before the solve after this kernel needs it).
+struct LuArgs {
+    const double* H;
+    double* LU;
+    int* perm;
+    int M;
+    double hg;
+};
+
 template <int MB>
 __global__ __launch_bounds__(kRedThreads) void k_project(const double* V, const double* F, long n, const int* ints,
-                                                        double* partials) {
+                                                        double* partials, LuArgs lu) {
+    __shared__ double sm[16][kRedThreads];
     const int m = ints[0];
+    int block = blockIdx.x;
+    if (lu.LU) {
+        if (block == 0) {
+            static_assert(sizeof(sm) >= sizeof(double) * 64 * kMaxM, "the multipliers");
+            if (threadIdx.x < 64) lu_wave<MB>(lu.H, lu.M, lu.hg, lu.LU, lu.perm, m, &sm[0][0]);
+            return;
+        }
+        --block;
+    }
     double acc[MB];
 #pragma unroll
     for (int c = 0; c < MB; ++c) acc[c] = 0.0;
     const long stride = (long)kRedBlocks * kRedThreads;
     if (m == MB) {
-        for (long e = (long)blockIdx.x * kRedThreads + threadIdx.x; e < n; e += stride) {
+        for (long e = (long)block * kRedThreads + threadIdx.x; e < n; e += stride) {
             double fe = ld_stream(F + e);
             double vc[MB];
 #pragma unroll
@@ -377,15 +430,14 @@ __global__ __launch_bounds__(kRedThreads) void k_project(const double* V, const 
             for (int c = 0; c < MB; ++c) acc[c] = acc[c] + vc[c] * fe;
         }
     } else {
-        for (long e = (long)blockIdx.x * kRedThreads + threadIdx.x; e < n; e += stride) {
+        for (long e = (long)block * kRedThreads + threadIdx.x; e < n; e += stride) {
             double fe = ld_stream(F + e);
 #pragma unroll
             for (int c = 0; c < MB; ++c)
                 if (c < m) acc[c] = acc[c] + ld_stream(V + (long)c * n + e) * fe;
         }
     }
-    __shared__ double sm[16][kRedThreads];
-    tree256_chunks<0, MB>(acc, m, sm, [&](int c, double b) { partials[(long)c * kRedBlocks + blockIdx.x] = b; });
+    tree256_chunks<0, MB>(acc, m, sm, [&](int c, double b) { partials[(long)c * kRedBlocks + block] = b; });
 }
 
 struct BRow {
@@ -605,12 +657,19 @@ hipError_t launch_error_norm(const Work& W, const double* y, const double* a, co
     return hipGetLastError();
 }
 
-hipError_t launch_start_basis(const Work& W, const double* f, long n, double* v0, hipStream_t st) {
-    ROK_RED(false, true, (double*)f, nullptr, nullptr, nullptr, nullptr, n, W.ints, mgs_part(W, 0));
-    hipLaunchKernelGGL(k_finish, dim3(1), dim3(kRedThreads), 0, st, mgs_part(W, 0), (int)FIN_BETA, nullptr, W.scal,
-                       W.ints, 0);
-    hipLaunchKernelGGL(k_normalize, dim3(grid_for(n, kRedThreads)), dim3(kRedThreads), 0, st, f, nullptr, W.H, 1, -1,
-                       v0, n, W.ints, W.scal);
+// Blocks of a reduction grid that hold elements of an n-vector.
+static inline int red_blocks(long n) {
+    const long g = (n + kRedThreads - 1) / kRedThreads;
+    return (int)(g < 1 ? 1 : (g > kRedBlocks ? kRedBlocks : g));
+}
+
+hipError_t launch_start_basis(const Work& W, const double* f, long n, double* v0, hipStream_t st, const double* y) {
+    double *pf = mgs_part(W, 0), *py = mgs_part(W, 1);
+    const int nb = red_blocks(n);
+    hipLaunchKernelGGL(k_norms, dim3((unsigned)nb), dim3(kRedThreads), 0, st, y, f, n, W.ints, pf, py);
+    unsigned g = grid_for(n, kRedThreads);
+    if (g > 2048) g = 2048;   // every block finishes the sum from 1024 partials
+    hipLaunchKernelGGL(k_start, dim3(g), dim3(kRedThreads), 0, st, f, pf, y ? py : nullptr, nb, v0, n, W.ints, W.scal);
     return hipGetLastError();
 }
 
@@ -631,7 +690,7 @@ hipError_t launch_mgs_column(const Work& W, double* w, const double* V, long n, 
         ROK_RED(true, true, w, V + (long)j * n, mgs_part(W, j), W.H + (long)j * M + j, nullptr, n, W.ints,
                 mgs_part(W, j + 1));
         hipLaunchKernelGGL(k_normalize, dim3(grid_for(n, kRedThreads)), dim3(kRedThreads), 0, st, w,
-                           mgs_part(W, j + 1), W.H, M, j, vnext, n, W.ints, W.scal);
+                           mgs_part(W, j + 1), W.H, M, j, vnext, n, W.ints);
     } else {
         hipLaunchKernelGGL(k_finish, dim3(1), dim3(kRedThreads), 0, st, mgs_part(W, j), (int)FIN_STORE,
                            W.H + (long)j * M + j, W.scal, W.ints, 0);
@@ -642,7 +701,7 @@ hipError_t launch_mgs_column(const Work& W, double* w, const double* V, long n, 
 hipError_t launch_normalize(const Work& W, const double* w, const double* partials, int M, int j, double* v, long n,
                             hipStream_t st) {
     hipLaunchKernelGGL(k_normalize, dim3(grid_for(n, kRedThreads)), dim3(kRedThreads), 0, st, w, partials, W.H, M, j,
-                       v, n, W.ints, W.scal);
+                       v, n, W.ints);
     return hipGetLastError();
 }
 
@@ -653,11 +712,6 @@ hipError_t launch_norm_scale(const Work& W, const double* partials, int M, int j
 
 hipError_t launch_copy_h(const Work& W, int M, double* Hout, int* meff_out, hipStream_t st) {
     hipLaunchKernelGGL(k_copy_h, dim3(grid_for((long)M * M, 256)), dim3(256), 0, st, W.H, M, Hout, W.ints, meff_out);
-    return hipGetLastError();
-}
-
-hipError_t launch_lu(const Work& W, int M, double hg, hipStream_t st) {
-    hipLaunchKernelGGL(k_lu, dim3(1), dim3(kRedThreads), 0, st, W.H, M, hg, W.LU, W.perm, W.ints);
     return hipGetLastError();
 }
 
@@ -684,6 +738,13 @@ static int mbucket(int M) {
         default: CALL(64); break;      \
     }
 
+hipError_t launch_lu(const Work& W, int M, double hg, hipStream_t st) {
+#define ROK_LU(MB) hipLaunchKernelGGL((k_lu<MB>), dim3(1), dim3(64), 0, st, W.H, M, hg, W.LU, W.perm, W.ints)
+    ROK_MB_SWITCH(mbucket(M), ROK_LU)
+#undef ROK_LU
+    return hipGetLastError();
+}
+
 // The first stage's projection without a pass over the basis: F_1 = f(y_n) =
 // beta v_0 (the basis starts from it), so phi_1 = V^T F_1 = beta e_1 in exact
 // arithmetic.  Leaves partials that k_lambda finishes to exactly that:
@@ -700,20 +761,23 @@ hipError_t launch_project_first(const Work& W, int M, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_project(const Work& W, const double* V, const double* F, long n, int M, hipStream_t st) {
+hipError_t launch_project(const Work& W, const double* V, const double* F, long n, int M, hipStream_t st,
+                          const double* lu_hg) {
+    const LuArgs lu = lu_hg ? LuArgs{W.H, W.LU, W.perm, M, *lu_hg} : LuArgs{};
+    const unsigned g = (unsigned)red_blocks(n) + (lu_hg ? 1u : 0u);
 #define ROK_PROJ(MB) \
-    hipLaunchKernelGGL((k_project<MB>), dim3(kRedBlocks), dim3(kRedThreads), 0, st, V, F, n, W.ints, W.partials)
+    hipLaunchKernelGGL((k_project<MB>), dim3(g), dim3(kRedThreads), 0, st, V, F, n, W.ints, W.partials, lu)
     ROK_MB_SWITCH(mbucket(M), ROK_PROJ)
 #undef ROK_PROJ
     return hipGetLastError();
 }
 
-hipError_t launch_lambda(const Work& W, int M, int i, const double* gam_row, double h, hipStream_t st,
+hipError_t launch_lambda(const Work& W, int M, int i, const double* gam_row, double h, long n, hipStream_t st,
                          const double* sig) {
     GamRow gr{};
     for (int j = 0; j < kMaxStages; ++j) gr.g[j] = (j < i) ? gam_row[j] : 0.0;
-    hipLaunchKernelGGL(k_lambda, dim3(1), dim3(kRedThreads), 0, st, W.H, W.LU, W.perm, M, i, gr, h, W.partials,
-                       W.phi, W.lam, W.ints, sig);
+    hipLaunchKernelGGL(k_lambda, dim3(1), dim3(kSmallThreads), 0, st, W.H, W.LU, W.perm, M, i, gr, h, W.partials,
+                       red_blocks(n), W.phi, W.lam, W.ints, sig);
     return hipGetLastError();
 }
 

@@ -101,69 +101,74 @@ struct GRow {
     double g[kMaxStages];
 };
 
+constexpr int kSmall = 1024;          // threads of the reduced reverse
+constexpr int kLd = kMaxM + 1;        // leading dimension of its LDS matrices (no bank conflicts either way)
+
 // Reduced-space reverse of stage i on one block; P = V^T kbar_i from the
-// projection partials (column c at part + c kB).  H, LU and the lambdas are
-// staged in LDS; the triangular solves run column by column across threads,
-// the rank-one updates of Abar and Hbar entry-parallel.
-__global__ __launch_bounds__(kT) void k_small_rev(const double* part, int M, int i, GRow gr, double h,
-                                                 const double* H, const double* LU, const int* perm,
-                                                 const double* lam, double* lambar, double* phibar, double* Abar,
-                                                 double* Hbar, const int* ints) {
-    __shared__ double s[kT];
-    __shared__ double P[kMaxM], r[kMaxM], z[kMaxM], g[kMaxM], Htr[kMaxM], li[kMaxM];
-    __shared__ double sLU[kMaxM * kMaxM], sH[kMaxM * kMaxM];
+// projection partials (column c at part + c kB, one column per wave).  The
+// triangular solves run column by column on wave 0 (lane r holds entry r, the
+// finished entries broadcast), the rank-one updates of Abar and Hbar
+// entry-parallel.  (256 threads finishing one column at a time, a block barrier per solved column:
+// 30 us at M = 16.)
+__global__ __launch_bounds__(kSmall) void k_small_rev(const double* part, int nb, int M, int i, GRow gr, double h,
+                                                     const double* H, const double* LU, const int* perm,
+                                                     const double* lam, double* lambar, double* phibar, double* Abar,
+                                                     double* Hbar, const int* ints) {
+    __shared__ double P[kMaxM], r[kMaxM], g[kMaxM], li[kMaxM];
+    __shared__ double sLU[kMaxM * kLd], sH[kMaxM * kLd];
     const int m = ints[0];
     const int tid = threadIdx.x;
-    for (int c = 0; c < m; ++c) {
-        double t = finish(part + (long)c * kB, s);
-        if (tid == 0) P[c] = t;
+    for (int e = tid; e < M * M; e += kSmall) {
+        const int a = e / M, b = e - a * M;
+        sLU[a * kLd + b] = LU[e];
+        sH[a * kLd + b] = H[e];
     }
-    for (int e = tid; e < m * m; e += kT) {
-        const int a = e / m, b = e % m;
-        sLU[a * kMaxM + b] = LU[a * M + b];
-        sH[a * kMaxM + b] = H[a * M + b];
-    }
-    __syncthreads();
-    double* lb = lambar + (long)i * M;
     if (tid < m) {
-        const double v = lb[tid] + P[tid];
-        lb[tid] = v;
-        z[tid] = v;
         li[tid] = lam[(long)i * M + tid];
         double a = 0.0;
         for (int j = 0; j < i; ++j)
             if (gr.g[j] != 0.0) a = a + gr.g[j] * lam[j * M + tid];
         g[tid] = a;
     }
+    const int row = (tid < m) ? perm[tid] : 0;
+    for (int c = tid >> 6; c < m; c += kSmall / 64) {
+        const double t = wave_final(part + (long)c * kB, nb);
+        if ((tid & 63) == 0) P[c] = t;
+    }
     __syncthreads();
-    // A = P^T L U (row permutation perm):  A^T r = lb  <=>  U^T z = lb, L^T u = z, r[perm[q]] = u[q]
-    for (int q = 0; q < m; ++q) {          // U^T (lower triangular) forward, column-oriented
-        if (tid == 0) z[q] = z[q] / sLU[q * kMaxM + q];
-        __syncthreads();
-        if (tid > q && tid < m) z[tid] = z[tid] - sLU[q * kMaxM + tid] * z[q];
-        __syncthreads();
+    if (tid < 64) {
+        double* lb = lambar + (long)i * M;
+        double z = 0.0;
+        if (tid < m) {
+            z = lb[tid] + P[tid];
+            lb[tid] = z;
+        }
+        // A = P^T L U (row permutation perm):  A^T r = lb  <=>  U^T z = lb, L^T u = z, r[perm[q]] = u[q]
+        for (int q = 0; q < m; ++q) {          // U^T (lower triangular) forward, column-oriented
+            const double u = sLU[q * kLd + tid];
+            const double zq = lane_value(z, q) / lane_value(u, q);
+            if (tid == q) z = zq;
+            if (tid > q && tid < m) z = z - u * zq;
+        }
+        for (int q = m - 1; q > 0; --q) {      // L^T (unit upper triangular) backward, column-oriented
+            const double zq = lane_value(z, q);
+            if (tid < q) z = z - sLU[q * kLd + tid] * zq;
+        }
+        if (tid < m) r[row] = z;
     }
-    for (int q = m - 1; q > 0; --q) {      // L^T (unit upper triangular) backward, column-oriented
-        if (tid < q) z[tid] = z[tid] - sLU[q * kMaxM + tid] * z[q];
-        __syncthreads();
-    }
-    if (tid < m) r[perm[tid]] = z[tid];
     __syncthreads();
-    if (tid < m) {
-        phibar[(long)i * M + tid] = -h * P[tid] + h * r[tid];
-        double a = 0.0;                     // (H^T r)_c
-        for (int q = 0; q < m; ++q) a = a + sH[q * kMaxM + tid] * r[q];
-        Htr[tid] = a;
-    }
-    for (int e = tid; e < m * m; e += kT) {
-        const int a = e / m, b = e % m;
+    for (int e = tid; e < m * m; e += kSmall) {
+        const int a = e / m, b = e - a * m;
         Abar[a * M + b] = Abar[a * M + b] - r[a] * li[b];
         Hbar[a * M + b] = Hbar[a * M + b] + h * r[a] * g[b];
     }
-    __syncthreads();
-    if (tid < m)
+    if (tid < m) {
+        phibar[(long)i * M + tid] = -h * P[tid] + h * r[tid];
+        double a = 0.0;                     // (H^T r)_c
+        for (int q = 0; q < m; ++q) a = a + sH[q * kLd + tid] * r[q];
         for (int j = 0; j < i; ++j)
-            if (gr.g[j] != 0.0) lambar[j * M + tid] = lambar[j * M + tid] + gr.g[j] * h * Htr[tid];
+            if (gr.g[j] != 0.0) lambar[j * M + tid] = lambar[j * M + tid] + gr.g[j] * h * a;
+    }
 }
 
 // Vbar[:, c] += (lam_c - h phi_c) kbar + phibar_c F;  Fbar = h kbar + V phibar.
@@ -379,11 +384,12 @@ hipError_t launch_scatter(const AdjWork& A, const double* Ybar, double* ybar, co
     return hipGetLastError();
 }
 
-hipError_t launch_small_rev(const Work& W, const AdjWork& A, int M, int i, const double* gam_row, double h,
+hipError_t launch_small_rev(const Work& W, const AdjWork& A, int M, int i, const double* gam_row, double h, long n,
                             hipStream_t st) {
     GRow gr{};
     for (int j = 0; j < kMaxStages; ++j) gr.g[j] = (j < i) ? gam_row[j] : 0.0;
-    hipLaunchKernelGGL(k_small_rev, dim3(1), dim3(kT), 0, st, A.part, M, i, gr, h, W.H, W.LU, W.perm, W.lam,
+    const long nb = (n + kT - 1) / kT;   // the projection's blocks
+    hipLaunchKernelGGL(k_small_rev, dim3(1), dim3(kSmall), 0, st, A.part, (int)(nb < kB ? nb : kB), M, i, gr, h, W.H, W.LU, W.perm, W.lam,
                        A.lambar, A.phibar, A.Abar, A.Hbar, W.ints);
     return hipGetLastError();
 }
