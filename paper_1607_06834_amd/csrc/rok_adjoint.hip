@@ -571,22 +571,14 @@ struct Side {
     T q[4], c, cr, cp;
 };
 
-// c, dc/dr and dc/dp of a state: two reciprocals and a root (dual numbers by the chain rule, no division of their own)
-__device__ __forceinline__ void sound_speed(const Geom& G, double r, double p, double& c, double& cr, double& cp) {
-    const double ir = 1.0 / r;
-    c = sqrt(G.g * p * ir);
-    cr = -0.5 * c * ir;
-    cp = 0.5 * G.g * ir / c;
-}
-__device__ __forceinline__ void sound_speed(const Geom& G, Dual<double> r, Dual<double> p, Dual<double>& c,
-                                            Dual<double>& cr, Dual<double>& cp) {
-    const Dual<double> ir = recip(r);
-    const Dual<double> x = G.g * (p * ir);
-    c.v = sqrt(x.v);
-    const double ic = 1.0 / c.v;
-    c.d = 0.5 * x.d * ic;
+// c, dc/dr and dc/dp of a state: one reciprocal and a root with its own (dual numbers by the chain rule)
+template <typename T>
+__device__ __forceinline__ void sound_speed(const Geom& G, T r, T p, T& c, T& cr, T& cp) {
+    const T ir = recip(r);
+    T h;   // 1 / (2 c)
+    c = Sc<T>::sqrt_(G.g * (p * ir), h);
     cr = -0.5 * (c * ir);
-    cp = (0.5 * G.g) * (ir * Dual<double>{ic, -(c.d * ic) * ic});
+    cp = (G.g * ir) * h;
 }
 
 // Adjoint of one side of Rusanov's flux along d: the physical flux with weight

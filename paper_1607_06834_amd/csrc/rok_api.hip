@@ -301,6 +301,9 @@ rok_status rok_create(const rok_problem* p, rok_ctx** out) {
     G.suth_one_s = 1.0 + p->sutherland;
     G.t_ref = p->sutherland > 0.0 ? p->t_ref : 1.0;
     G.kden = (p->gamma - 1.0) * p->prandtl;
+    G.gm1_inv = 1.0 / G.gm1;
+    G.t_ref_inv = 1.0 / G.t_ref;
+    G.kden_inv = 1.0 / G.kden;
     *out = c;
     return ROK_OK;
 }

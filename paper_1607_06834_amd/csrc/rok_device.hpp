@@ -28,6 +28,8 @@ struct Geom {
     double invdx[3];  // 1 / dx, rounded once
     double hinv[3];   // 0.5 / dx (central differences)
     double g, gm1;    // gamma, gamma - 1
+    double gm1_inv;   // 1 / (gamma - 1), 1 / T_ref and 1 / ((gamma - 1) Pr), rounded once (see over)
+    double t_ref_inv, kden_inv;
     double mu, c23mu, kappa;  // mu, (2/3) mu, mu gamma / ((gamma-1) Pr)
     int flux;                 // inviscid flux: 0 Rusanov, 1 Roe
     int suth;                 // Sutherland's law (else constant mu)
@@ -38,17 +40,14 @@ struct Geom {
     double t_wall;            //   and (Navier-Stokes) t_wall the isothermal wall's temperature
 };
 
-// Residual-kernel inputs: the stage state Y = y + sum_t cs[t] xs[t]
-// (PLAIN), or y + eps v (FD), or the pair (y, v) (TANGENT).
+// Residual-kernel inputs: the state y (PLAIN), or y + eps v (FD), or the pair
+// (y, v) (TANGENT).
 struct ResArgs {
     const double* y;
     const double* v;
     const double* f0;          // FD: f(y)
     const double* eps_dev;     // FD: if non-null, eps is read from here
     double eps;
-    int nterm;
-    const double* xs[kMaxStages];
-    double cs[kMaxStages];
     void* out;
     // optional: skip the launch unless gate_col + 1 >= *gate (gate: a
     // device-side basis size, e.g. M_eff of the Arnoldi process)
@@ -69,7 +68,84 @@ struct ResArgs {
 };
 
 // ---------------------------------------------------------------------------
-// Dual numbers (value, tangent): exact forward-mode derivative of f.
+// Quotients and roots.  The residual is bound by FP64 issue, and a correctly
+// rounded division is about eleven instructions (two of them scalings, one a
+// quarter-rate reciprocal).  over(b) takes the reciprocal y of b once, by two Newton
+// steps on the hardware's estimate, and a / over(b) is then q = a y corrected by the exact remainder,
+// q + (a - b q) y (Markstein 1990), with the hardware's fixup for zeros,
+// infinities and NaN: four instructions for every further quotient.
+// The same correctly rounded bits as a / b for operands and quotients between
+// 2^-900 and 2^900 (FP32: 2^-100 and 2^100): only the scalings for exponents outside are left
+// out.  over(b, y): y = RN(1 / b) from the host.
+// ---------------------------------------------------------------------------
+template <typename S> struct Quot;
+template <> struct Quot<double> { double b, y; };
+template <> struct Quot<float> { float b, y; };
+
+__device__ __forceinline__ Quot<double> over(double b) {
+    double y = __builtin_amdgcn_rcp(b);
+    y = __builtin_fma(__builtin_fma(-b, y, 1.0), y, y);
+    y = __builtin_fma(__builtin_fma(-b, y, 1.0), y, y);
+    return {b, y};
+}
+__device__ __forceinline__ Quot<double> over(double b, double y) { return {b, y}; }
+__device__ __forceinline__ double operator/(double a, Quot<double> r) {
+    double q = a * r.y;
+    q = __builtin_fma(__builtin_fma(-r.b, q, a), r.y, q);
+    return __builtin_amdgcn_div_fixup(q, r.b, a);
+}
+__device__ __forceinline__ Quot<float> over(float b) {
+    float y = __builtin_amdgcn_rcpf(b);
+    y = __builtin_fmaf(__builtin_fmaf(-b, y, 1.0f), y, y);
+    return {b, y};
+}
+__device__ __forceinline__ Quot<float> over(float b, double) { return over(b); }
+__device__ __forceinline__ float operator/(float a, Quot<float> r) {
+    float q = a * r.y;
+    q = __builtin_fmaf(__builtin_fmaf(-r.b, q, a), r.y, q);
+    return __builtin_amdgcn_div_fixupf(q, r.b, a);
+}
+
+// Square root s with h = 1 / (2 s): Goldschmidt's coupled iteration from the hardware's reciprocal root, the last
+// two steps correcting by the exact remainder (the correctly rounded root of x above 2^-767: the scaling of smaller
+// arguments is left out), then a Newton step of h on s.
+__device__ __forceinline__ double root(double x, double& h) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y;
+    h = 0.5 * y;
+    const double r = __builtin_fma(-h, g, 0.5);
+    g = __builtin_fma(g, r, g);
+    h = __builtin_fma(h, r, h);
+    g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+    g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+    h = __builtin_fma(h, __builtin_fma(-(g + g), h, 1.0), h);
+    return (x == 0.0 || x == __builtin_inf()) ? x : g;
+}
+__device__ __forceinline__ float root(float x, float& h) {
+    const float y = __builtin_amdgcn_rsqf(x);
+    float g = x * y;
+    h = 0.5f * y;
+    const float r = __builtin_fmaf(-h, g, 0.5f);
+    g = __builtin_fmaf(g, r, g);
+    h = __builtin_fmaf(h, r, h);
+    g = __builtin_fmaf(__builtin_fmaf(-g, g, x), h, g);
+    h = __builtin_fmaf(h, __builtin_fmaf(-(g + g), h, 1.0f), h);
+    return (x == 0.0f || x == __builtin_inff()) ? x : g;
+}
+
+// x y + z with one rounding, y + x / 2 and y - x / 2 (halving is exact, so
+// these round once like the separate operations)
+__device__ __forceinline__ double mad(double x, double y, double z) { return __builtin_fma(x, y, z); }
+__device__ __forceinline__ float mad(float x, float y, float z) { return __builtin_fmaf(x, y, z); }
+__device__ __forceinline__ double plus_half(double y, double x) { return __builtin_fma(0.5, x, y); }
+__device__ __forceinline__ float plus_half(float y, float x) { return __builtin_fmaf(0.5f, x, y); }
+__device__ __forceinline__ double minus_half(double y, double x) { return __builtin_fma(-0.5, x, y); }
+__device__ __forceinline__ float minus_half(float y, float x) { return __builtin_fmaf(-0.5f, x, y); }
+
+// ---------------------------------------------------------------------------
+// Dual numbers (value, tangent): exact forward-mode derivative of f.  Every
+// operation rounds as written, like the plain arithmetic; a quotient's value
+// and tangent share the divisor's reciprocal.
 // ---------------------------------------------------------------------------
 template <typename T>
 struct Dual {
@@ -80,10 +156,32 @@ template <typename T> __device__ __forceinline__ Dual<T> operator+(Dual<T> a, Du
 template <typename T> __device__ __forceinline__ Dual<T> operator-(Dual<T> a, Dual<T> b) { return {a.v - b.v, a.d - b.d}; }
 template <typename T> __device__ __forceinline__ Dual<T> operator-(Dual<T> a) { return {-a.v, -a.d}; }
 template <typename T> __device__ __forceinline__ Dual<T> operator*(Dual<T> a, Dual<T> b) { return {a.v * b.v, a.d * b.v + a.v * b.d}; }
-template <typename T> __device__ __forceinline__ Dual<T> operator/(Dual<T> a, Dual<T> b) {
-    T q = a.v / b.v;
-    return {q, (a.d - q * b.d) / b.v};
+template <typename T> __device__ __forceinline__ Dual<T> plus_half(Dual<T> y, Dual<T> x) { return {plus_half(y.v, x.v), plus_half(y.d, x.d)}; }
+template <typename T> __device__ __forceinline__ Dual<T> minus_half(Dual<T> y, Dual<T> x) { return {minus_half(y.v, x.v), minus_half(y.d, x.d)}; }
+
+// divisor of dual numbers: the value's reciprocal serves value and tangent
+template <typename T> struct Quot<Dual<T>> {
+    Dual<T> b;
+    Quot<T> r;
+};
+template <typename T> __device__ __forceinline__ Quot<Dual<T>> over(Dual<T> b) { return {b, over(b.v)}; }
+// x / b to about an ulp
+__device__ __forceinline__ double times(double x, Quot<double> r) { return x * r.y; }
+__device__ __forceinline__ float times(float x, Quot<float> r) { return x * r.y; }
+template <typename T> __device__ __forceinline__ Dual<T> operator/(Dual<T> a, Quot<Dual<T>> q) {
+    const T v = a.v / q.r;
+    return {v, (a.d - v * q.b.d) / q.r};
 }
+template <typename T> __device__ __forceinline__ Dual<T> times(Dual<T> x, Quot<Dual<T>> q) {
+    const T v = times(x.v, q.r);
+    return {v, times(x.d - v * q.b.d, q.r)};
+}
+template <typename T> __device__ __forceinline__ Dual<T> operator/(Dual<T> a, Dual<T> b) { return a / over(b); }
+// a constant divisor (any nesting depth)
+template <typename T, typename R, typename = typename std::enable_if<std::is_floating_point<R>::value>::type>
+__device__ __forceinline__ Dual<T> times(Dual<T> x, Quot<R> r) { return {times(x.v, r), times(x.d, r)}; }
+template <typename T, typename R, typename = typename std::enable_if<std::is_floating_point<R>::value>::type>
+__device__ __forceinline__ Dual<T> operator/(Dual<T> a, Quot<R> r) { return {a.v / r, a.d / r}; }
 // products and quotients with a plain floating-point constant (any nesting depth)
 template <typename T, typename R, typename = typename std::enable_if<std::is_floating_point<R>::value>::type>
 __device__ __forceinline__ Dual<T> operator*(R a, Dual<T> b) { return {a * b.v, a * b.d}; }
@@ -104,29 +202,48 @@ template <> struct Sc<double> {
     using R = double;
     static __device__ __forceinline__ double val(double x) { return x; }
     static __device__ __forceinline__ double make(double x) { return x; }
-    static __device__ __forceinline__ double sqrt_(double x) { return sqrt(x); }
+    static __device__ __forceinline__ double sqrt_(double x, double& h) { return root(x, h); }
+    static __device__ __forceinline__ double sqrt_(double x) { double h; return root(x, h); }
 };
 template <> struct Sc<float> {
     using R = float;
     static __device__ __forceinline__ float val(float x) { return x; }
     static __device__ __forceinline__ float make(double x) { return (float)x; }
-    static __device__ __forceinline__ float sqrt_(float x) { return sqrtf(x); }
+    static __device__ __forceinline__ float sqrt_(float x, float& h) { return root(x, h); }
+    static __device__ __forceinline__ float sqrt_(float x) { float h; return root(x, h); }
 };
 template <typename T> struct Sc<Dual<T>> {
     using R = typename Sc<T>::R;
     static __device__ __forceinline__ R val(Dual<T> x) { return Sc<T>::val(x.v); }
     static __device__ __forceinline__ Dual<T> make(double x) { return {Sc<T>::make(x), Sc<T>::make(0.0)}; }
-    static __device__ __forceinline__ Dual<T> sqrt_(Dual<T> x) {
-        T s = Sc<T>::sqrt_(x.v);
-        return {s, x.d / (s + s)};
+    // sqrt(x) and h = 1 / (2 sqrt(x)), whose tangent is -(s' / s) h
+    static __device__ __forceinline__ Dual<T> sqrt_(Dual<T> x, Dual<T>& h) {
+        T hv;
+        const T s = Sc<T>::sqrt_(x.v, hv);
+        const T sd = root_tangent(x.d, s, hv);
+        h = {hv, -(sd * hv) * (hv + hv)};
+        return {s, sd};
     }
+    static __device__ __forceinline__ Dual<T> sqrt_(Dual<T> x) {
+        T hv;
+        const T s = Sc<T>::sqrt_(x.v, hv);
+        return {s, root_tangent(x.d, s, hv)};
+    }
+    // d / (2 s), h being 1 / (2 s)
+    static __device__ __forceinline__ double root_tangent(double d, double s, double h) {
+        return d / over(s + s, h);
+    }
+    static __device__ __forceinline__ float root_tangent(float d, float s, float h) {
+        return d / Quot<float>{s + s, h};
+    }
+    template <typename U> static __device__ __forceinline__ Dual<U> root_tangent(Dual<U> d, Dual<U> s, Dual<U>) { return d / over(s + s); }
 };
 
-// 1 / r (one division; the dual number's tangent by the chain rule)
-__device__ __forceinline__ double recip(double r) { return 1.0 / r; }
-__device__ __forceinline__ Dual<double> recip(Dual<double> r) {
-    const double iv = 1.0 / r.v;
-    return {iv, -(r.d * iv) * iv};
+// 1 / b to about an ulp (one reciprocal; the dual number's tangent by the chain rule)
+__device__ __forceinline__ double recip(double b) { return over(b).y; }
+__device__ __forceinline__ Dual<double> recip(Dual<double> b) {
+    const double y = over(b.v).y;
+    return {y, -(b.d * y) * y};
 }
 
 // The FP64 counterpart of a scalar type (double for float, Dual<double> for
@@ -171,6 +288,14 @@ template <int H>
 __device__ __forceinline__ double lane_down(double v) {
     const long long b = __double_as_longlong(v);
     const int lo = lane_down_word<H>((int)(b & 0xffffffffLL)), hi = lane_down_word<H>((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+// The value of the lane before, within rows of 16 lanes (the first lane of a row gets zero).
+__device__ __forceinline__ double lane_up1(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffLL), 0x111, 0xf, 0xf, true);   // row_shr:1
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x111, 0xf, 0xf, true);
     return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 

@@ -10,12 +10,32 @@
 
 namespace rok {
 
-template <typename S> __device__ __forceinline__ S sabs(S x) { return Sc<S>::val(x) >= 0 ? x : -x; }
+// |x|; of a dual number the branch x >= 0 (a plain number's fabs is an operand modifier, no instruction)
+__device__ __forceinline__ double sabs(double x) { return __builtin_fabs(x); }
+__device__ __forceinline__ float sabs(float x) { return __builtin_fabsf(x); }
+template <typename T> __device__ __forceinline__ Dual<T> sabs(Dual<T> x) { return Sc<Dual<T>>::val(x) >= 0 ? x : -x; }
 
 template <typename S> __device__ __forceinline__ S minmod(S a, S b) {
     using R = typename Sc<S>::R;
-    if (Sc<S>::val(a) * Sc<S>::val(b) <= (R)0) return Sc<S>::make(0.0);
-    return (Sc<S>::val(sabs(a)) <= Sc<S>::val(sabs(b))) ? a : b;
+    const R x = Sc<S>::val(a), y = Sc<S>::val(b);
+    if (x * y <= (R)0) return Sc<S>::make(0.0);
+    return (sabs(x) <= sabs(y)) ? a : b;
+}
+
+// The MUSCL states on the two sides of a cell, base + mm(a, b) / 2 and
+// base - mm(a, b) / 2: the branch that limits the slope to zero takes the factor 0 instead of
+// 1/2, one select on a constant's upper word instead of two on the slope (the same
+// values for finite slopes; a cell between two infinite ones, whose faces are not finite
+// anyway, gets NaN).
+template <typename T> __device__ __forceinline__ T axpy(T f, T x, T y) { return mad(f, x, y); }
+template <typename R, typename T> __device__ __forceinline__ Dual<T> axpy(R f, Dual<T> x, Dual<T> y) {
+    return {axpy(f, x.v, y.v), axpy(f, x.d, y.d)};
+}
+template <typename S> __device__ __forceinline__ S muscl(S base, S a, S b, typename Sc<S>::R half) {
+    using R = typename Sc<S>::R;
+    const R x = Sc<S>::val(a), y = Sc<S>::val(b);
+    const R f = (x * y <= (R)0) ? (R)0 : half;
+    return axpy(f, (sabs(x) <= sabs(y)) ? a : b, base);
 }
 
 template <int D, typename S>
@@ -32,18 +52,17 @@ __device__ __forceinline__ void rusanov(const Geom& G, int d, const S* UL, S rL,
                                         const S* UR, S rR, const S* vR, S pR, S* Fh) {
     using R = typename Sc<S>::R;
     const R g = (R)G.g;
-    const R half = (R)0.5;
-    S cL = Sc<S>::sqrt_(g * pL / rL);
-    S cR = Sc<S>::sqrt_(g * pR / rR);
+    S cL = Sc<S>::sqrt_(g * pL / over(rL));
+    S cR = Sc<S>::sqrt_(g * pR / over(rR));
     S sL = sabs(vL[d]) + cL;
     S sR = sabs(vR[d]) + cR;
     S a = (Sc<S>::val(sL) >= Sc<S>::val(sR)) ? sL : sR;
     S FL[D + 2], FR[D + 2];
     euler_flux<D>(UL, vL, pL, d, FL);
     euler_flux<D>(UR, vR, pR, d, FR);
-    S ha = half * a;
+    S ha = (R)0.5 * a;
 #pragma unroll
-    for (int m = 0; m < D + 2; ++m) Fh[m] = half * (FL[m] + FR[m]) - ha * (UR[m] - UL[m]);
+    for (int m = 0; m < D + 2; ++m) Fh[m] = plus_half(-(ha * (UR[m] - UL[m])), FL[m] + FR[m]);
 }
 
 // Roe's approximate Riemann flux along d (Roe 1981): the central flux minus
@@ -59,7 +78,7 @@ constexpr double kRoeFix = 0.125;
 template <typename S>
 __device__ __forceinline__ S roe_fixed(S lam, S delta) {
     S l = sabs(lam);
-    if (Sc<S>::val(l) < Sc<S>::val(delta)) l = (l * l + delta * delta) / (delta + delta);
+    if (Sc<S>::val(l) < Sc<S>::val(delta)) l = (l * l + delta * delta) / over(delta + delta);
     return l;
 }
 
@@ -76,9 +95,10 @@ __device__ __forceinline__ void roe_dissipation(const Geom& G, int d, const S* u
     const S un = u[d];
     const S rc = rho * c;
     const S cc = c2 + c2;
-    const S a1 = (dp - rc * du[d]) / cc;
-    const S a3 = (dp + rc * du[d]) / cc;
-    const S a2 = dr - dp / c2;
+    const auto qcc = over(cc);
+    const S a1 = (dp - rc * du[d]) / qcc;
+    const S a3 = (dp + rc * du[d]) / qcc;
+    const S a2 = dr - dp / over(c2);
     const S delta = (R)kRoeFix * c;
     const S l1 = roe_fixed(un - c, delta);
     const S l2 = sabs(un);
@@ -111,15 +131,16 @@ __device__ __forceinline__ void roe(const Geom& G, int d, const S* UL, S rL, con
     euler_flux<D>(UR, vR, pR, d, FR);
     const S sL = Sc<S>::sqrt_(rL), sR = Sc<S>::sqrt_(rR);
     const S den = sL + sR;
-    const S wL = sL / den, wR = sR / den;
+    const auto qden = over(den);
+    const S wL = sL / qden, wR = sR / qden;
     S u[D], du[D];
 #pragma unroll
     for (int e = 0; e < D; ++e) {
         u[e] = wL * vL[e] + wR * vR[e];
         du[e] = vR[e] - vL[e];
     }
-    const S HL = (UL[D + 1] + pL) / rL;
-    const S HR = (UR[D + 1] + pR) / rR;
+    const S HL = (UL[D + 1] + pL) / over(rL);
+    const S HR = (UR[D + 1] + pR) / over(rR);
     const S H = wL * HL + wR * HR;
     const S rho = sL * sR;
     S ke = u[0] * u[0];
@@ -128,7 +149,7 @@ __device__ __forceinline__ void roe(const Geom& G, int d, const S* UL, S rL, con
     S Dv[D + 2];
     roe_dissipation<D>(G, d, u, H, rho, ke, rR - rL, du, pR - pL, Dv);
 #pragma unroll
-    for (int m = 0; m < D + 2; ++m) Fh[m] = half * (FL[m] + FR[m]) - half * Dv[m];
+    for (int m = 0; m < D + 2; ++m) Fh[m] = half * ((FL[m] + FR[m]) - Dv[m]);
 }
 
 // The inviscid numerical flux selected at compile time (ROK_RUSANOV = 0, ROK_ROE = 1).
@@ -142,15 +163,13 @@ __device__ __forceinline__ void num_flux(const Geom& G, int d, const S* UL, S rL
 template <int D, typename S>
 __device__ __forceinline__ void to_conserved(const Geom& G, S r, const S* vel, S p, S* U) {
     using R = typename Sc<S>::R;
-    const R gm1 = (R)G.gm1;
-    const R half = (R)0.5;
     S ke = vel[0] * vel[0];
 #pragma unroll
     for (int d = 1; d < D; ++d) ke = ke + vel[d] * vel[d];
     U[0] = r;
 #pragma unroll
     for (int d = 0; d < D; ++d) U[1 + d] = r * vel[d];
-    U[D + 1] = p / gm1 + (half * r) * ke;
+    U[D + 1] = plus_half(p / over((R)G.gm1, G.gm1_inv), r * ke);
 }
 
 
@@ -158,14 +177,14 @@ template <int D, typename S>
 __device__ __forceinline__ void primitives(const Geom& G, const S* U, S& r, S* vel, S& p) {
     using R = typename Sc<S>::R;
     const R gm1 = (R)G.gm1;
-    const R half = (R)0.5;
     r = U[0];
+    const auto qr = over(r);
 #pragma unroll
-    for (int d = 0; d < D; ++d) vel[d] = U[1 + d] / r;
+    for (int d = 0; d < D; ++d) vel[d] = U[1 + d] / qr;
     S ke = vel[0] * vel[0];
 #pragma unroll
     for (int d = 1; d < D; ++d) ke = ke + vel[d] * vel[d];
-    p = gm1 * (U[D + 1] - (half * r) * ke);
+    p = gm1 * minus_half(U[D + 1], r * ke);
 }
 
 // Inviscid flux of the face between stencil cells a and b = a + 1 along d,
@@ -200,8 +219,8 @@ __device__ __forceinline__ void face_flux_cells(const Geom& G, const S (*U)[D + 
 #pragma unroll
         for (int m = 0; m < NV; ++m) {
             S am1 = q[0][m], a0 = q[1][m], ap1 = q[2][m], ap2 = q[3][m];
-            qL[m] = a0 + half * minmod(a0 - am1, ap1 - a0);
-            qR[m] = ap1 - half * minmod(ap1 - a0, ap2 - ap1);
+            qL[m] = muscl(a0, a0 - am1, ap1 - a0, (R)0.5);
+            qR[m] = muscl(ap1, ap1 - a0, ap2 - ap1, (R)-0.5);
         }
         rL = qL[0];
         rR = qR[0];
@@ -232,10 +251,11 @@ __device__ __forceinline__ void prim_rev(const Geom& G, const T* U, T rb, const 
     using R = typename Sc<T>::R;
     const R gm1 = (R)G.gm1, half = (R)0.5;
     const T r = U[0];
+    const auto qr = over(r);
     T vel[D], vb[D];
 #pragma unroll
     for (int e = 0; e < D; ++e) {
-        vel[e] = U[1 + e] / r;
+        vel[e] = U[1 + e] / qr;
         vb[e] = vb_in[e];
     }
     T ke = vel[0] * vel[0];
@@ -251,8 +271,9 @@ __device__ __forceinline__ void prim_rev(const Geom& G, const T* U, T rb, const 
     // vel_e = U[1+e] / r
 #pragma unroll
     for (int e = 0; e < D; ++e) {
-        Ub[1 + e] = Ub[1 + e] + vb[e] / r;
-        rb = rb - vb[e] * vel[e] / r;
+        const T m = times(vb[e], qr);
+        Ub[1 + e] = Ub[1 + e] + m;
+        rb = rb - m * vel[e];
     }
     Ub[0] = Ub[0] + rb;
 }
@@ -261,7 +282,7 @@ __device__ __forceinline__ void prim_rev(const Geom& G, const T* U, T rb, const 
 template <int D, typename T>
 __device__ __forceinline__ void cons_rev(const Geom& G, T r, const T* vel, const T* Ub, T& rb, T* vb, T& pb) {
     using R = typename Sc<T>::R;
-    const R gm1 = (R)G.gm1, half = (R)0.5;
+    const R half = (R)0.5;
     T ke = vel[0] * vel[0];
 #pragma unroll
     for (int e = 1; e < D; ++e) ke = ke + vel[e] * vel[e];
@@ -272,7 +293,7 @@ __device__ __forceinline__ void cons_rev(const Geom& G, T r, const T* vel, const
         rb = rb + Ub[1 + e] * vel[e];
         vb[e] = vb[e] + Ub[1 + e] * r + (vel[e] + vel[e]) * keb;
     }
-    pb = pb + Ub[D + 1] / gm1;
+    pb = pb + times(Ub[D + 1], over((R)G.gm1, G.gm1_inv));
 }
 
 // One side of the reverse of rusanov(): the Euler flux of that side carries
@@ -299,9 +320,9 @@ __device__ __forceinline__ void rusanov_side_rev(const Geom& G, int d, const T* 
     unb = unb + fe * (U[D + 1] + p);
     if (taken) {
         unb = (Sc<T>::val(un) >= 0) ? unb + ab : unb - ab;
-        const T xb = ab / (c + c);
-        pb = pb + g * xb / r;
-        rb = rb - xb * x / r;
+        const T xb = times(ab / over(c + c), over(r));
+        pb = pb + g * xb;
+        rb = rb - xb * x;
     }
     vb[d] = vb[d] + unb;
 }
@@ -314,7 +335,7 @@ __device__ __forceinline__ void rusanov_rev(const Geom& G, int d, const T* UL, T
     using R = typename Sc<T>::R;
     const R g = (R)G.g, half = (R)0.5;
     constexpr int NV = D + 2;
-    const T xL = g * pL / rL, xR = g * pR / rR;
+    const T xL = g * pL / over(rL), xR = g * pR / over(rR);
     const T cL = Sc<T>::sqrt_(xL), cR = Sc<T>::sqrt_(xR);
     const T sL = sabs(vL[d]) + cL, sR = sabs(vR[d]) + cR;
     const bool takeL = Sc<T>::val(sL) >= Sc<T>::val(sR);
@@ -380,8 +401,8 @@ __device__ __forceinline__ void face_flux_vjp(const Geom& G, const T (*U)[D + 2]
                      : ((Sc<T>::val(sabs(x1)) <= Sc<T>::val(sabs(y1))) ? 1 : 2);
             brR[m] = (Sc<T>::val(x2) * Sc<T>::val(y2) <= (R)0) ? 0
                      : ((Sc<T>::val(sabs(x2)) <= Sc<T>::val(sabs(y2))) ? 1 : 2);
-            qL[m] = a0 + half * minmod(x1, y1);
-            qR[m] = ap1 - half * minmod(x2, y2);
+            qL[m] = muscl(a0, x1, y1, (R)0.5);
+            qR[m] = muscl(ap1, x2, y2, (R)-0.5);
         }
         T UL[NV], UR[NV], vL[D], vR[D];
 #pragma unroll
@@ -484,7 +505,7 @@ __device__ __forceinline__ void rusanov_ref(const Geom& G, const RefState<D, typ
             uu = uu + u[e] * u[e];
             ku = ku + q[1 + e] * (u[e] + Q.u0[e]);       // |u|^2 - |u0|^2
         }
-        const S Ep = pp / gm1 + half * (rp * uu + Q.r0 * ku);   // E - E0
+        const S Ep = plus_half(pp / over(gm1), rp * uu + Q.r0 * ku);   // E - E0
         const S Hp = Ep + pp;                                    // (E + p) - (E0 + p0)
         Up[side][0] = rp;
 #pragma unroll
@@ -495,12 +516,12 @@ __device__ __forceinline__ void rusanov_ref(const Geom& G, const RefState<D, typ
         for (int e = 0; e < D; ++e)
             F[side][1 + e] = (e == d) ? mp[d] * u[e] + Q.m0[d] * q[1 + e] + pp : mp[d] * u[e] + Q.m0[d] * q[1 + e];
         F[side][D + 1] = Hp * u[d] + Q.H0 * q[1 + d];
-        sp[side] = sabs(u[d]) + Sc<S>::sqrt_(g * p / r);
+        sp[side] = sabs(u[d]) + Sc<S>::sqrt_(g * p / over(r));
     }
     const S a = (Sc<S>::val(sp[0]) >= Sc<S>::val(sp[1])) ? sp[0] : sp[1];
     const S ha = half * a;
 #pragma unroll
-    for (int m = 0; m < NV; ++m) Fh[m] = half * (F[0][m] + F[1][m]) - ha * (Up[1][m] - Up[0][m]);
+    for (int m = 0; m < NV; ++m) Fh[m] = plus_half(-(ha * (Up[1][m] - Up[0][m])), F[0][m] + F[1][m]);
 }
 
 // Roe flux minus F(q0) at a face in the reference-state form: the central part
@@ -531,7 +552,7 @@ __device__ __forceinline__ void roe_ref(const Geom& G, const RefState<D, typenam
             uu = uu + u[e] * u[e];
             ku = ku + q[1 + e] * (u[e] + Q.u0[e]);
         }
-        const S Ep = pp / gm1 + half * (rp * uu + Q.r0 * ku);
+        const S Ep = plus_half(pp / over(gm1), rp * uu + Q.r0 * ku);
         const S Hp = Ep + pp;
         F[side][0] = mp[d];
 #pragma unroll
@@ -540,12 +561,13 @@ __device__ __forceinline__ void roe_ref(const Geom& G, const RefState<D, typenam
         F[side][D + 1] = Hp * u[d] + Q.H0 * q[1 + d];
         rs[side] = r;
         sq[side] = Sc<S>::sqrt_(r);
-        Hs[side] = (Q.H0 + Hp) / r;          // (E + p) / rho
+        Hs[side] = (Q.H0 + Hp) / over(r);    // (E + p) / rho
 #pragma unroll
         for (int e = 0; e < D; ++e) us[side][e] = u[e];
     }
     const S den = sq[0] + sq[1];
-    const S wL = sq[0] / den, wR = sq[1] / den;
+    const auto qden = over(den);
+    const S wL = sq[0] / qden, wR = sq[1] / qden;
     S u[D], du[D];
 #pragma unroll
     for (int e = 0; e < D; ++e) {
@@ -561,7 +583,7 @@ __device__ __forceinline__ void roe_ref(const Geom& G, const RefState<D, typenam
     roe_dissipation<D>(G, d, u, H, rho, ke, qR[0] - qL[0], du, qR[D + 1] - qL[D + 1], Dv);
     (void)rs;
 #pragma unroll
-    for (int m = 0; m < NV; ++m) Fh[m] = half * (F[0][m] + F[1][m]) - half * Dv[m];
+    for (int m = 0; m < NV; ++m) Fh[m] = half * ((F[0][m] + F[1][m]) - Dv[m]);
 }
 
 template <int D, int FLUX, typename S>

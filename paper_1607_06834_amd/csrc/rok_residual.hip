@@ -39,9 +39,7 @@ __device__ __forceinline__ void load_state(const ResArgs& A, long ncell, long gi
     for (int m = 0; m < NV; ++m) {
         long k = (long)m * ncell + gi;
         if constexpr (MODE == MODE_PLAIN) {
-            double acc = A.y[k];
-            for (int t = 0; t < A.nterm; ++t) acc = acc + A.cs[t] * A.xs[t][k];
-            U[m] = Sc<S>::make(acc);
+            U[m] = Sc<S>::make(A.y[k]);
         } else if constexpr (MODE == MODE_FD) {
             U[m] = Sc<S>::make(A.y[k] + eps * A.v[k]);
         } else {
@@ -153,9 +151,9 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
             return sq[OFF_T][q];
         } else if constexpr (PERT) {
             const S rp = sq[0][q], pp = sq[OFF_P][q];
-            return (s_ref.r0 * pp - s_ref.p0 * rp) / (s_ref.r0 * (s_ref.r0 + rp));
+            return (s_ref.r0 * pp - s_ref.p0 * rp) / over(s_ref.r0 * (s_ref.r0 + rp));
         } else {
-            return sq[OFF_P][q] / sq[0][q];
+            return sq[OFF_P][q] / over(sq[0][q]);
         }
     };
 
@@ -262,15 +260,15 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
                 if constexpr (PACKED) s_slot[c] = (unsigned short)i;
                 S* U = Ub[it];
                 const R gm1 = (R)G.gm1;
-                const R half = (R)0.5;
                 S r = U[0];
                 S vel[D];
+                const auto qr = over(r);
 #pragma unroll
-                for (int d = 0; d < D; ++d) vel[d] = U[1 + d] / r;
+                for (int d = 0; d < D; ++d) vel[d] = U[1 + d] / qr;
                 S ke = vel[0] * vel[0];
 #pragma unroll
                 for (int d = 1; d < D; ++d) ke = ke + vel[d] * vel[d];
-                S p = gm1 * (U[D + 1] - (half * r) * ke);
+                S p = gm1 * minus_half(U[D + 1], r * ke);
                 np |= (Sc<S>::val(r) <= (R)0 || Sc<S>::val(p) <= (R)0) ? 1 : 0;
                 if constexpr (CONS) {
 #pragma unroll
@@ -281,7 +279,7 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
 #pragma unroll
                 for (int d = 0; d < D; ++d) sq[OFF_VEL + d][q] = vel[d];
                 sq[OFF_P][q] = p;
-                if constexpr (TSTAGED) sq[OFF_T][q] = p / r;
+                if constexpr (TSTAGED) sq[OFF_T][q] = p / qr;
             }
         }
         __syncthreads();
@@ -311,7 +309,7 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
             SD ke = vel[0] * vel[0];
 #pragma unroll
             for (int d = 1; d < D; ++d) ke = ke + vel[d] * vel[d];
-            SD p = G.gm1 * (U[D + 1] - (0.5 * r) * ke);
+            SD p = G.gm1 * minus_half(U[D + 1], r * ke);
             np |= (Sc<SD>::val(r) <= 0.0 || Sc<SD>::val(p) <= 0.0) ? 1 : 0;
             sq[0][q] = narrow<S>(r - s_refd[0]);
 #pragma unroll
@@ -364,13 +362,12 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
 #pragma unroll
                     for (int k = 0; k < NV; ++k) { qL[k] = sq[k][ia]; qR[k] = sq[k][ib]; }
                 } else {
-                    const R half = (R)0.5;
                     const int im = slot(ca - sd), ip = slot(cb + sd);
 #pragma unroll
                     for (int k = 0; k < NV; ++k) {
                         S am1 = sq[k][im], a0 = sq[k][ia], ap1 = sq[k][ib], ap2 = sq[k][ip];
-                        qL[k] = a0 + half * minmod(a0 - am1, ap1 - a0);
-                        qR[k] = ap1 - half * minmod(ap1 - a0, ap2 - ap1);
+                        qL[k] = muscl(a0, a0 - am1, ap1 - a0, (R)0.5);
+                        qR[k] = muscl(ap1, ap1 - a0, ap2 - ap1, (R)-0.5);
                     }
                 }
                 num_flux_ref<D, FLUX>(G, s_ref, d, qL, qR, Fh);
@@ -384,7 +381,6 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
                 pL = sq[OFF_P][ia];
                 pR = sq[OFF_P][ib];
             } else {
-                const R half = (R)0.5;
                 S qL[NV], qR[NV];
                 // O-grid: no slope across the wall (row 0) or the far field (row n1 - 1)
                 bool flatL = false, flatR = false;
@@ -398,10 +394,12 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
 #pragma unroll
                 for (int k = 0; k < NV; ++k) {
                     S am1 = sq[k][im], a0 = sq[k][ia], ap1 = sq[k][ib], ap2 = sq[k][ip];
-                    const S sl = flatL ? Sc<S>::make(0.0) : minmod(a0 - am1, ap1 - a0);
-                    const S sr = flatR ? Sc<S>::make(0.0) : minmod(ap1 - a0, ap2 - ap1);
-                    qL[k] = a0 + half * sl;
-                    qR[k] = ap1 - half * sr;
+                    qL[k] = muscl(a0, a0 - am1, ap1 - a0, (R)0.5);
+                    qR[k] = muscl(ap1, ap1 - a0, ap2 - ap1, (R)-0.5);
+                    if constexpr (GEO == 2) {
+                        if (flatL) qL[k] = a0;
+                        if (flatR) qR[k] = ap1;
+                    }
                 }
                 rL = qL[0];
                 rR = qR[0];
@@ -437,8 +435,9 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
                 const int ga = wrap(y0 + fy - (d == 1), n1) * n0 + wrap(x0 + fx - (d == 0), n0);
                 const double sx = G.metric[(long)(2 * d) * G.ncell + ga];
                 const double sy = G.metric[(long)(2 * d + 1) * G.ncell + ga];
-                const double ln = sqrt(sx * sx + sy * sy);
-                const double nx = sx / ln, ny = sy / ln;
+                const double ln = Sc<double>::sqrt_(sx * sx + sy * sy);
+                const auto qln = over(ln);
+                const double nx = sx / qln, ny = sy / qln;
                 S vLr[D], vRr[D], ULr[NV], URr[NV], Fr[NV];
                 vLr[0] = vL[0] * nx + vL[1] * ny;
                 vLr[1] = vL[1] * nx - vL[0] * ny;
@@ -528,7 +527,7 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
                         Tf = half * (sq[OFF_T][ca] + sq[OFF_T][cb]);
                     }
                     // chain rule through the face's two grid directions
-                    const double J = dcx * sx + dcy * sy;
+                    const auto J = over(dcx * sx + dcy * sy);
                     S ux, uy, vx, vy, Tx, Ty;
                     if (d == 0) {
                         ux = (nu * sx - tu * dcy) / J;
@@ -558,9 +557,9 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
                         Fh[3] = Fh[3] - en;
                     };
                     if (G.suth) {
-                        const S th = Tf / (R)G.t_ref;
-                        const S muf = (R)G.mu * th * Sc<S>::sqrt_(th) * (R)G.suth_one_s / (th + (R)G.suth_s);
-                        vflux(muf, (R)(2.0 / 3.0) * muf, muf * (R)G.g / (R)G.kden);
+                        const S th = Tf / over((R)G.t_ref, G.t_ref_inv);
+                        const S muf = (R)G.mu * th * Sc<S>::sqrt_(th) * (R)G.suth_one_s / over(th + (R)G.suth_s);
+                        vflux(muf, (R)(2.0 / 3.0) * muf, muf * (R)G.g / over((R)G.kden, G.kden_inv));
                     } else {
                         vflux((R)G.mu, (R)G.c23mu, (R)G.kappa);
                     }
@@ -585,6 +584,7 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
                         tbm[bb] = slot(cb - st);
                     }
                 }
+                // across the face the gradient; along it twice the gradient, halved where it is added
                 S Gr[D][D];
 #pragma unroll
                 for (int a = 0; a < D; ++a) {
@@ -592,38 +592,39 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
                     for (int bb = 0; bb < D; ++bb) {
                         if (bb == d) {
                             Gr[a][bb] = (sq[OFF_VEL + a][ib] - sq[OFF_VEL + a][ia]) * (R)G.invdx[d];
-                        } else {
+                        } else if (a == d || a == bb) {
                             const R h = (R)G.hinv[bb];
                             S gca = (sq[OFF_VEL + a][tap[bb]] - sq[OFF_VEL + a][tam[bb]]) * h;
                             S gcb = (sq[OFF_VEL + a][tbp[bb]] - sq[OFF_VEL + a][tbm[bb]]) * h;
-                            Gr[a][bb] = half * (gca + gcb);
+                            Gr[a][bb] = gca + gcb;
                         }
                     }
                 }
-                S div = Gr[0][0];
+                S div = (d == 0) ? Gr[0][0] : half * Gr[0][0];
 #pragma unroll
-                for (int a = 1; a < D; ++a) div = div + Gr[a][a];
+                for (int a = 1; a < D; ++a) div = (a == d) ? div + Gr[a][a] : plus_half(div, Gr[a][a]);
                 // stress, work and conduction for viscosity mu_, (2/3) mu_ and conductivity kappa_
                 auto viscous = [&](auto mu_, auto c23mu_, auto kappa_) {
                     S work;
 #pragma unroll
                     for (int a = 0; a < D; ++a) {
-                        S tau = (a == d) ? mu_ * (Gr[a][d] + Gr[d][a]) - c23mu_ * div : mu_ * (Gr[a][d] + Gr[d][a]);
-                        S uf = half * (sq[OFF_VEL + a][ia] + sq[OFF_VEL + a][ib]);
-                        if constexpr (PERT) uf = s_ref.u0[a] + uf;   // perturbations staged: add the reference
+                        S tau = (a == d) ? mu_ * (Gr[a][d] + Gr[d][a]) - c23mu_ * div
+                                         : mu_ * plus_half(Gr[a][d], Gr[d][a]);
+                        S uf = sq[OFF_VEL + a][ia] + sq[OFF_VEL + a][ib];   // twice the face velocity
+                        if constexpr (PERT) uf = (R)2 * s_ref.u0[a] + uf;      // perturbations staged: add the reference
                         work = (a == 0) ? uf * tau : work + uf * tau;
                         Fh[1 + a] = Fh[1 + a] - tau;
                     }
                     S dTdn = (temp(ib) - temp(ia)) * (R)G.invdx[d];
-                    Fh[D + 1] = Fh[D + 1] - (work + kappa_ * dTdn);
+                    Fh[D + 1] = Fh[D + 1] - plus_half(kappa_ * dTdn, work);
                 };
                 if (G.suth) {
                     // Sutherland's law at the face temperature (T_a + T_b) / 2
                     S Tf = half * (temp(ia) + temp(ib));
                     if constexpr (PERT) Tf = (R)s_refd[D + 2] + Tf;
-                    const S th = Tf / (R)G.t_ref;
-                    const S muf = mu * th * Sc<S>::sqrt_(th) * (R)G.suth_one_s / (th + (R)G.suth_s);
-                    viscous(muf, (R)(2.0 / 3.0) * muf, muf * (R)G.g / (R)G.kden);
+                    const S th = Tf / over((R)G.t_ref, G.t_ref_inv);
+                    const S muf = mu * th * Sc<S>::sqrt_(th) * (R)G.suth_one_s / over(th + (R)G.suth_s);
+                    viscous(muf, (R)(2.0 / 3.0) * muf, muf * (R)G.g / over((R)G.kden, G.kden_inv));
                 } else {
                     viscous(mu, c23mu, kappa);
                 }
@@ -655,6 +656,7 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
 
     // 4. write out (and note a NaN or Inf in the output)
     bool nonfin = false;
+    const auto qeps = over(eps);   // FD
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
         int cell = tid + k * kThreads;
@@ -671,7 +673,7 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
             if constexpr (MODE == MODE_PLAIN) {
                 x = (OUT)res[k][m];
             } else if constexpr (MODE == MODE_FD) {
-                x = (OUT)((res[k][m] - f0pre[k][m]) / eps);
+                x = (OUT)((res[k][m] - f0pre[k][m]) / qeps);
             } else {
                 x = (OUT)res[k][m].d;
             }
@@ -697,35 +699,43 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
 // one plane early) and are staged from there one plane later, with the 144
 // halo cells, so every cell is loaded once per range.  Each thread computes
 // the x face and the y face on the low side of its cell and the z face above
-// it, and exchanges fluxes with its neighbours by lane shuffles; the faces on
-// the column's +x and +y edges are computed by two waves and passed through a
-// small LDS buffer.  LDS per block stays under a third of the CU's, so three
-// blocks (12 waves) share a CU.  Every face flux and every cell sum is the
+// it, and exchanges fluxes and temperatures with its neighbours by lane moves; the 32 faces on
+// the column's +x and +y edges are computed together by half a wave, a different wave
+// each plane, and passed through a small LDS buffer.  LDS per block stays under a third of the
+// CU's, so three blocks (12 waves) share a CU.  Every face flux and every cell sum is the
 // same sequence of operations on the same values as in k_residual (the same
 // bits).
+// It is bound by instruction issue: at 256^3 (Navier-Stokes, Rusanov) the residual moves 1.34 GB,
+// 0.27 ms at a copy's rate, and takes 722 us, the FD product 893.  They took 881 and 1056 (3324 vector
+// instructions a plane and wave, now 2270) when every quotient was a full division, the gradients along
+// a face were halved one by one, each access formed a 64-bit address, and the edge faces were two
+// half-empty passes.  Registers are the other bound (168 for three blocks): each face's viscous
+// part comes first, since between the reconstruction and the flux it would hold both sides' states, and 40
+// bytes of scratch a thread alone took the FD product from 1101 to 1251 us.
 // ---------------------------------------------------------------------------
 constexpr int kZW = 20;              // staged plane width (16 + 2 + 2)
 constexpr int kZR = kZW * kZW;       // cells of a staged plane
 constexpr int kZHalo = kZR - 256;    // its halo cells
+constexpr int kZT = 4 * 16 + 16;     // temperatures of a plane that waves exchange
 constexpr int kZBlocks = 1536;       // two rounds of three resident blocks on each of 256 CUs
+
+constexpr int kBufRaw = 0x00020000;  // word 3 of a raw buffer descriptor (data format 32)
 
 struct ZRef {
     int s, c;   // LDS slot, index in the staged plane
 };
 
-// primitive variables (rho, u, v, w, p) of a conserved state, in the staging
-// order of k_residual; returns whether rho <= 0 or p <= 0
+// primitive variables (rho, u, v, w, p) of a conserved state, in the staging order of k_residual; returns whether rho <= 0 or p <= 0
 __device__ __forceinline__ bool zprim(const Geom& G, const double* U, double* q) {
-    const double gm1 = G.gm1;
-    const double half = 0.5;
     const double r = U[0];
+    const auto qr = over(r);
     double vel[3];
 #pragma unroll
-    for (int e = 0; e < 3; ++e) vel[e] = U[1 + e] / r;
+    for (int e = 0; e < 3; ++e) vel[e] = U[1 + e] / qr;
     double ke = vel[0] * vel[0];
 #pragma unroll
     for (int e = 1; e < 3; ++e) ke = ke + vel[e] * vel[e];
-    const double p = gm1 * (U[4] - (half * r) * ke);
+    const double p = G.gm1 * minus_half(U[4], r * ke);
     q[0] = r;
 #pragma unroll
     for (int e = 0; e < 3; ++e) q[1 + e] = vel[e];
@@ -734,25 +744,74 @@ __device__ __forceinline__ bool zprim(const Geom& G, const double* U, double* q)
 }
 
 // The flux through one face along d between cells a and b = a + e_d:
-// MUSCL-minmod reconstruction from the primitive states (qm, qa, qb, qp) of
-// the cells a - e_d, a, b, b + e_d, the inviscid flux and, with NSV, the
+// MUSCL-minmod reconstruction from the primitive variables q(i, k) of the cells
+// a - e_d, a, b, b + e_d (i = 0..3), the inviscid flux and, with NSV, the
 // central viscous flux with the tangential derivatives from the neighbours
-// ta / tb (+/- along each direction bb != d, read from the staged planes).
-template <int d, bool NSV, int FLUX>
+// ta / tb (+/- along each direction bb != d, read from the staged planes: velocity component a
+// at r.c + vo[a]) and the cells' temperatures Ta, Tb.  invdx, hinv: 1 / dx and 0.5 / dx per direction.
+template <int d, bool NSV, int FLUX, typename Q>
 __device__ __forceinline__ void zface(const Geom& G, int viscous_only, const double (*ring)[5][kZR],
-                                      const double (&qm)[5], const double (&qa)[5], const double (&qb)[5],
-                                      const double (&qp)[5], const ZRef (&tap)[3], const ZRef (&tam)[3],
-                                      const ZRef (&tbp)[3], const ZRef (&tbm)[3], double* Fh) {
-    auto V = [&](ZRef r, int k) -> double { return ring[r.s][k][r.c]; };
-    const double half = 0.5;
+                                      const double* invdx, const double* hinv, const int (&vo)[3], Q q, double Ta,
+                                      double Tb, const ZRef (&tap)[3], const ZRef (&tam)[3], const ZRef (&tbp)[3],
+                                      const ZRef (&tbm)[3], double* Fh) {
+    auto V = [&](ZRef r, int a) -> double { return (&ring[r.s][0][0])[vo[a] + r.c]; };
+    // the viscous part first: it leaves four numbers, where the inviscid part would hold its cells' states across it
+    double tv[4];   // stress row and energy term
+    if constexpr (NSV) {
+        double va[3], vb[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            va[a] = q(1, 1 + a);
+            vb[a] = q(2, 1 + a);
+        }
+        // across the face the gradient; along it twice the gradient, halved where it is added
+        double Gr[3][3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+#pragma unroll
+            for (int bb = 0; bb < 3; ++bb) {
+                if (bb == d) {
+                    Gr[a][bb] = (vb[a] - va[a]) * invdx[d];
+                } else if (a == d || a == bb) {
+                    const double h = hinv[bb];
+                    double gca = (V(tap[bb], a) - V(tam[bb], a)) * h;
+                    double gcb = (V(tbp[bb], a) - V(tbm[bb], a)) * h;
+                    Gr[a][bb] = gca + gcb;
+                }
+            }
+        }
+        double div = (d == 0) ? Gr[0][0] : 0.5 * Gr[0][0];
+#pragma unroll
+        for (int a = 1; a < 3; ++a) div = (a == d) ? div + Gr[a][a] : plus_half(div, Gr[a][a]);
+        auto viscous = [&](double mu_, double c23mu_, double kappa_) {
+            double work;   // twice the stress' work
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const double tau = (a == d) ? mu_ * (Gr[a][d] + Gr[d][a]) - c23mu_ * div
+                                            : mu_ * plus_half(Gr[a][d], Gr[d][a]);
+                const double uf = va[a] + vb[a];
+                work = (a == 0) ? uf * tau : work + uf * tau;
+                tv[a] = tau;
+            }
+            const double dTdn = (Tb - Ta) * invdx[d];
+            tv[3] = plus_half(kappa_ * dTdn, work);
+        };
+        if (G.suth) {
+            const double Tf = 0.5 * (Ta + Tb);
+            const double th = Tf / over(G.t_ref, G.t_ref_inv);
+            const double muf = G.mu * th * Sc<double>::sqrt_(th) * G.suth_one_s / over(th + G.suth_s);
+            viscous(muf, (2.0 / 3.0) * muf, muf * G.g / over(G.kden, G.kden_inv));
+        } else {
+            viscous(G.mu, G.c23mu, G.kappa);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
     double qL[5], qR[5];
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-        const double am1 = qm[k], a0 = qa[k], ap1 = qb[k], ap2 = qp[k];
-        const double sl = minmod(a0 - am1, ap1 - a0);
-        const double sr = minmod(ap1 - a0, ap2 - ap1);
-        qL[k] = a0 + half * sl;
-        qR[k] = ap1 - half * sr;
+        const double am1 = q(0, k), a0 = q(1, k), ap1 = q(2, k), ap2 = q(3, k);
+        qL[k] = muscl(a0, a0 - am1, ap1 - a0, 0.5);
+        qR[k] = muscl(ap1, ap1 - a0, ap2 - ap1, -0.5);
     }
     double UL[5], UR[5], vL[3], vR[3];
     const double rL = qL[0], rR = qR[0];
@@ -770,46 +829,8 @@ __device__ __forceinline__ void zface(const Geom& G, int viscous_only, const dou
 #pragma unroll
             for (int m = 0; m < 5; ++m) Fh[m] = 0.0;
         }
-        const double mu = G.mu, c23mu = G.c23mu, kappa = G.kappa;
-        double Gr[3][3];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-#pragma unroll
-            for (int bb = 0; bb < 3; ++bb) {
-                if (bb == d) {
-                    Gr[a][bb] = (qb[1 + a] - qa[1 + a]) * G.invdx[d];
-                } else {
-                    const double h = G.hinv[bb];
-                    double gca = (V(tap[bb], 1 + a) - V(tam[bb], 1 + a)) * h;
-                    double gcb = (V(tbp[bb], 1 + a) - V(tbm[bb], 1 + a)) * h;
-                    Gr[a][bb] = half * (gca + gcb);
-                }
-            }
-        }
-        double div = Gr[0][0];
-#pragma unroll
-        for (int a = 1; a < 3; ++a) div = div + Gr[a][a];
-        const double Ta = qa[4] / qa[0], Tb = qb[4] / qb[0];
-        auto viscous = [&](double mu_, double c23mu_, double kappa_) {
-            double work;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                double tau = (a == d) ? mu_ * (Gr[a][d] + Gr[d][a]) - c23mu_ * div : mu_ * (Gr[a][d] + Gr[d][a]);
-                double uf = half * (qa[1 + a] + qb[1 + a]);
-                work = (a == 0) ? uf * tau : work + uf * tau;
-                Fh[1 + a] = Fh[1 + a] - tau;
-            }
-            double dTdn = (Tb - Ta) * G.invdx[d];
-            Fh[4] = Fh[4] - (work + kappa_ * dTdn);
-        };
-        if (G.suth) {
-            double Tf = half * (Ta + Tb);
-            const double th = Tf / G.t_ref;
-            const double muf = mu * th * sqrt(th) * G.suth_one_s / (th + G.suth_s);
-            viscous(muf, (2.0 / 3.0) * muf, muf * G.g / G.kden);
-        } else {
-            viscous(mu, c23mu, kappa);
-        }
+        for (int m = 0; m < 4; ++m) Fh[1 + m] = Fh[1 + m] - tv[m];
     }
 }
 
@@ -822,11 +843,13 @@ __device__ __forceinline__ int zhalo(int h) {
     return (2 + (k >> 2)) * kZW + (c < 2 ? c : c + 16);
 }
 
-template <bool NSV, int FLUX, int MODE>
+template <bool NSV, int FLUX, int MODE, bool BIG>
 __global__ __launch_bounds__(kThreads, (NSV && FLUX == 1) ? 2 : 3) void k_res3z(Geom G, ResArgs A, int nbx, int nby, int nch) {
     __shared__ double ring[3][5][kZR];
     __shared__ double fedge_x[5][16];      // x faces on the column's +x edge, by row
-    __shared__ double frow_y[5][5][16];    // y faces below rows 0, 4, 8, 12 and above row 15
+    __shared__ double frow_y[4][5][16];    // y faces below rows 4, 8, 12 and above row 15
+    // temperatures of the current plane that lanes cannot pass on: the rows below the waves (y = -1, 3, 7, 11) and x = -1
+    __shared__ double sT[NSV ? kZT : 1];
     if (A.gate && A.gate_col + 1 < *A.gate) return;
     if (A.stop && *A.stop) return;
     const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4, wv = tid >> 6, lane = tid & 63;
@@ -845,21 +868,67 @@ __global__ __launch_bounds__(kThreads, (NSV && FLUX == 1) ? 2 : 3) void k_res3z(
     int np = 0;
     const int c0 = (ty + 2) * kZW + (tx + 2);          // this thread's cell in a staged plane
     const int hc = tid < kZHalo ? zhalo(tid) : c0;      // the halo cell it stages
-    auto gidx = [&](int z, int c) -> long {
-        const int gx = wrap(x0 - 2 + c % kZW, n0), gy = wrap(y0 - 2 + c / kZW, n1);
-        return ((long)wrap(z, n2) * n1 + gy) * n0 + gx;
+    // byte offsets of the two cells in a plane (below 2^32): a plane's loads and stores are buffer accesses with a
+    // scalar base and one of these offsets, which takes no vector arithmetic and no address registers
+    const unsigned own_off = 8u * ((unsigned)(y0 + ty) * n0 + (unsigned)(x0 + tx));
+    const unsigned halo_off = 8u * ((unsigned)wrap(y0 - 2 + hc / kZW, n1) * n0 + (unsigned)wrap(x0 - 2 + hc % kZW, n0));
+    const long plane = (long)n0 * n1;
+    // variable m of the vector at p (moved to a plane): the variable is the access' scalar offset, or, in vectors
+    // whose variables reach past 2^32 bytes (BIG), part of the base.  range: bytes from a plane's base to the end
+    // of the last variable's plane (the check covers both offsets)
+    const unsigned range = 8u * (unsigned)((BIG ? 0L : 4L * G.ncell) + plane);
+    auto rsrc = [&](const double* p, int m) {
+        if constexpr (BIG) p += (long)m * G.ncell;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(p), (short)0, (int)range, kBufRaw);
     };
-    auto load_prim = [&](int z, int c, double* q) {
+    const unsigned var = BIG ? 0u : 8u * (unsigned)G.ncell;
+    auto at = [&](const double* p, int m, unsigned off) -> double {
+        return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rsrc(p, m), off, m * var, 0));
+    };
+    // the inputs of the cell at byte offset off of plane z, and its primitives from them
+    struct Raw {
+        double y[5], v[MODE == MODE_FD ? 5 : 1];
+    };
+    auto load_raw = [&](int z, unsigned off, Raw& r) {
+        const long zo = wrap(z, n2) * plane;
+#pragma unroll
+        for (int m = 0; m < 5; ++m) {
+            r.y[m] = at(A.y + zo, m, off);
+            if constexpr (MODE == MODE_FD) r.v[m] = at(A.v + zo, m, off);
+        }
+    };
+    auto to_prim = [&](const Raw& r, double* q) {
         double U[5];
-        load_state<MODE, 5, double>(A, G.ncell, gidx(z, c), eps_st, U, vs);
+#pragma unroll
+        for (int m = 0; m < 5; ++m) {
+            if constexpr (MODE == MODE_FD) U[m] = r.y[m] + eps_st * r.v[m];
+            else U[m] = r.y[m];
+        }
         np |= zprim(G, U, q) ? 1 : 0;
     };
-    auto stage_halo = [&](int z, int s) {
-        if (tid < kZHalo) {
-            double q[5];
-            load_prim(z, hc, q);
+    auto load_prim = [&](int z, unsigned off, double* q) {
+        Raw r;
+        load_raw(z, off, r);
+        to_prim(r, q);
+    };
+    auto stage_halo = [&](const Raw& r, int s) {
+        double q[5];
+        to_prim(r, q);
 #pragma unroll
-            for (int k = 0; k < 5; ++k) ring[s][k][hc] = q[k];
+        for (int k = 0; k < 5; ++k) ring[s][k][hc] = q[k];
+    };
+    // the plane in slot s becomes current: own is the thread's cell's temperature there, the column's outer ones are
+    // formed by wave w
+    double Tz = 0.0;
+    auto stage_temp = [&](int s, double own, int w) {
+        Tz = own;
+        if constexpr (NSV) {
+            if ((ty & 3) == 3 && ty < 15) sT[16 * ((ty + 1) >> 2) + tx] = own;
+            if (wv == w && lane < 32) {
+                const int i = lane & 15;
+                const int c = lane < 16 ? kZW + i + 2 : (i + 2) * kZW + 1;
+                sT[lane < 16 ? i : 64 + i] = ring[s][4][c] / over(ring[s][0][c]);
+            }
         }
     };
     int sA = 0, sB = 1, sC = 2;   // slots of planes z - 1, z, z + 1
@@ -867,79 +936,79 @@ __global__ __launch_bounds__(kThreads, (NSV && FLUX == 1) ? 2 : 3) void k_res3z(
         double q[5];
 #pragma unroll 1
         for (int i = 0; i < 3; ++i) {
-            load_prim(zs - 1 + i, c0, q);
+            load_prim(zs - 1 + i, own_off, q);
 #pragma unroll
             for (int k = 0; k < 5; ++k) ring[i][k][c0] = q[k];
-            stage_halo(zs - 1 + i, i);
+            if (tid < kZHalo) {
+                Raw r;
+                load_raw(zs - 1 + i, halo_off, r);
+                stage_halo(r, i);
+            }
         }
     }
+    const int vxyz[3] = {kZR, 2 * kZR, 3 * kZR};   // velocity components in a staged plane
     double Fdown[5];   // flux through the z face below this thread's cell
     {
-        double qm[5], qa[5], qb[5], qp[5];
-        load_prim(zs - 2, c0, qm);
+        double qm[5];
+        load_prim(zs - 2, own_off, qm);
         __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-            qa[k] = ring[0][k][c0];
-            qb[k] = ring[1][k][c0];
-            qp[k] = ring[2][k][c0];
-        }
+        auto q = [&](int i, int k) { return i == 0 ? qm[k] : ring[i - 1][k][c0]; };
         ZRef tap[3], tam[3], tbp[3], tbm[3];
         tap[0] = {0, c0 + 1};   tam[0] = {0, c0 - 1};   tbp[0] = {1, c0 + 1};   tbm[0] = {1, c0 - 1};
         tap[1] = {0, c0 + kZW}; tam[1] = {0, c0 - kZW}; tbp[1] = {1, c0 + kZW}; tbm[1] = {1, c0 - kZW};
         tap[2] = tam[2] = tbp[2] = tbm[2] = {0, c0};
-        zface<2, NSV, FLUX>(G, A.viscous_only, ring, qm, qa, qb, qp, tap, tam, tbp, tbm, Fdown);
+        const double Ta = NSV ? q(1, 4) / over(q(1, 0)) : 0.0, Tb = NSV ? q(2, 4) / over(q(2, 0)) : 0.0;
+        zface<2, NSV, FLUX>(G, A.viscous_only, ring, G.invdx, G.hinv, vxyz, q, Ta, Tb, tap, tam, tbp, tbm, Fdown);
+        stage_temp(1, Tb, 0);
     }
-    const long gxy = (long)(y0 + ty) * n0 + (x0 + tx);
+    __syncthreads();
     bool nonfin = false;
     double* out = (double*)A.out;
 #pragma unroll 1
     for (int z = zs; z < ze; ++z) {
-        const long go = (long)z * n0 * n1 + gxy;
+        const long zo = (long)z * plane;
         double rx[5], ry[5];
         // x face on the -x side of the cell; the +x side's from the next lane of the row
         {
             const int ca = c0 - 1, cb = c0;
-            double qm[5], qa[5], qb[5], qp[5];
-#pragma unroll
-            for (int k = 0; k < 5; ++k) {
-                qm[k] = ring[sB][k][ca - 1];
-                qa[k] = ring[sB][k][ca];
-                qb[k] = ring[sB][k][cb];
-                qp[k] = ring[sB][k][cb + 1];
-            }
+            auto q = [&](int i, int k) { return ring[sB][k][c0 - 2 + i]; };
             ZRef tap[3], tam[3], tbp[3], tbm[3];
             tap[0] = tam[0] = tbp[0] = tbm[0] = {sB, ca};
             tap[1] = {sB, ca + kZW}; tam[1] = {sB, ca - kZW}; tbp[1] = {sB, cb + kZW}; tbm[1] = {sB, cb - kZW};
             tap[2] = {sC, ca};       tam[2] = {sA, ca};       tbp[2] = {sC, cb};       tbm[2] = {sA, cb};
             double F[5];
-            zface<0, NSV, FLUX>(G, A.viscous_only, ring, qm, qa, qb, qp, tap, tam, tbp, tbm, F);
+            double Ta = 0.0;
+            if constexpr (NSV) {
+                Ta = lane_up1(Tz);
+                if (tx == 0) Ta = sT[64 + ty];
+            }
+            zface<0, NSV, FLUX>(G, A.viscous_only, ring, G.invdx, G.hinv, vxyz, q, Ta, Tz, tap, tam, tbp,
+                                tbm, F);
 #pragma unroll
             for (int m = 0; m < 5; ++m) {
-                const double nb = __shfl_down(F[m], 1, 16);
+                const double nb = lane_down<1>(F[m]);
                 rx[m] = (tx < 15) ? (F[m] - nb) * G.invdx[0] : F[m];
             }
         }
         // y face on the -y side; the +y side's from the lane 16 up, or (last row of a wave) through LDS
         {
             const int ca = c0 - kZW, cb = c0;
-            double qm[5], qa[5], qb[5], qp[5];
-#pragma unroll
-            for (int k = 0; k < 5; ++k) {
-                qm[k] = ring[sB][k][ca - kZW];
-                qa[k] = ring[sB][k][ca];
-                qb[k] = ring[sB][k][cb];
-                qp[k] = ring[sB][k][cb + kZW];
-            }
+            auto q = [&](int i, int k) { return ring[sB][k][c0 + (i - 2) * kZW]; };
             ZRef tap[3], tam[3], tbp[3], tbm[3];
             tap[0] = {sB, ca + 1}; tam[0] = {sB, ca - 1}; tbp[0] = {sB, cb + 1}; tbm[0] = {sB, cb - 1};
             tap[1] = tam[1] = tbp[1] = tbm[1] = {sB, ca};
             tap[2] = {sC, ca};     tam[2] = {sA, ca};     tbp[2] = {sC, cb};     tbm[2] = {sA, cb};
             double F[5];
-            zface<1, NSV, FLUX>(G, A.viscous_only, ring, qm, qa, qb, qp, tap, tam, tbp, tbm, F);
-            if ((ty & 3) == 0) {
+            double Ta = 0.0;
+            if constexpr (NSV) {
+                Ta = __shfl_up(Tz, 16, 64);
+                if ((ty & 3) == 0) Ta = sT[16 * (ty >> 2) + tx];
+            }
+            zface<1, NSV, FLUX>(G, A.viscous_only, ring, G.invdx, G.hinv, vxyz, q, Ta, Tz, tap, tam, tbp,
+                                tbm, F);
+            if ((ty & 3) == 0 && ty > 0) {
 #pragma unroll
-                for (int m = 0; m < 5; ++m) frow_y[ty >> 2][m][tx] = F[m];
+                for (int m = 0; m < 5; ++m) frow_y[(ty >> 2) - 1][m][tx] = F[m];
             }
 #pragma unroll
             for (int m = 0; m < 5; ++m) {
@@ -947,86 +1016,90 @@ __global__ __launch_bounds__(kThreads, (NSV && FLUX == 1) ? 2 : 3) void k_res3z(
                 ry[m] = ((ty & 3) != 3) ? (F[m] - nb) * G.invdx[1] : F[m];
             }
         }
-        // the column's edge faces: two waves (alternating by plane), 16 lanes each
-        const int we = (z & 1) * 2;
-        if (wv == we && lane < 16) {
-            const int cb = (lane + 2) * kZW + 18, ca = cb - 1;
-            double qm[5], qa[5], qb[5], qp[5];
-#pragma unroll
-            for (int k = 0; k < 5; ++k) {
-                qm[k] = ring[sB][k][ca - 1];
-                qa[k] = ring[sB][k][ca];
-                qb[k] = ring[sB][k][cb];
-                qp[k] = ring[sB][k][cb + 1];
-            }
+        // the column's edge faces by one wave, alternating by plane: lanes 0-15 the +x edge, lanes 16-31 the +y
+        // edge.  A face along y is one along x with the two directions and velocity components exchanged (the
+        // sums over components start with those two, whose order does not round differently).
+        if (wv == (z & 3) && lane < 32) {
+            const bool isy = lane >= 16;
+            const int i = lane & 15;
+            const int sn = isy ? kZW : 1, st = isy ? 1 : kZW;   // steps across and along the face
+            const int cb = isy ? 18 * kZW + i + 2 : (i + 2) * kZW + 18, ca = cb - sn;
+            const int vo[3] = {isy ? 2 * kZR : kZR, isy ? kZR : 2 * kZR, 3 * kZR};
+            const double invdx[3] = {isy ? G.invdx[1] : G.invdx[0], 0.0, 0.0};
+            const double hinv[3] = {0.0, isy ? G.hinv[0] : G.hinv[1], G.hinv[2]};
+            const double* P = &ring[sB][0][0];
+            auto q = [&](int i, int k) { return P[((k >= 1 && k <= 3) ? vo[k - 1] : k * kZR) + ca + (i - 1) * sn]; };
             ZRef tap[3], tam[3], tbp[3], tbm[3];
             tap[0] = tam[0] = tbp[0] = tbm[0] = {sB, ca};
-            tap[1] = {sB, ca + kZW}; tam[1] = {sB, ca - kZW}; tbp[1] = {sB, cb + kZW}; tbm[1] = {sB, cb - kZW};
-            tap[2] = {sC, ca};       tam[2] = {sA, ca};       tbp[2] = {sC, cb};       tbm[2] = {sA, cb};
+            tap[1] = {sB, ca + st}; tam[1] = {sB, ca - st}; tbp[1] = {sB, cb + st}; tbm[1] = {sB, cb - st};
+            tap[2] = {sC, ca};      tam[2] = {sA, ca};      tbp[2] = {sC, cb};      tbm[2] = {sA, cb};
             double F[5];
-            zface<0, NSV, FLUX>(G, A.viscous_only, ring, qm, qa, qb, qp, tap, tam, tbp, tbm, F);
-#pragma unroll
-            for (int m = 0; m < 5; ++m) fedge_x[m][lane] = F[m];
-        } else if (wv == we + 1 && lane < 16) {
-            const int cb = 18 * kZW + lane + 2, ca = cb - kZW;
-            double qm[5], qa[5], qb[5], qp[5];
-#pragma unroll
-            for (int k = 0; k < 5; ++k) {
-                qm[k] = ring[sB][k][ca - kZW];
-                qa[k] = ring[sB][k][ca];
-                qb[k] = ring[sB][k][cb];
-                qp[k] = ring[sB][k][cb + kZW];
-            }
-            ZRef tap[3], tam[3], tbp[3], tbm[3];
-            tap[0] = {sB, ca + 1}; tam[0] = {sB, ca - 1}; tbp[0] = {sB, cb + 1}; tbm[0] = {sB, cb - 1};
-            tap[1] = tam[1] = tbp[1] = tbm[1] = {sB, ca};
-            tap[2] = {sC, ca};     tam[2] = {sA, ca};     tbp[2] = {sC, cb};     tbm[2] = {sA, cb};
-            double F[5];
-            zface<1, NSV, FLUX>(G, A.viscous_only, ring, qm, qa, qb, qp, tap, tam, tbp, tbm, F);
-#pragma unroll
-            for (int m = 0; m < 5; ++m) frow_y[4][m][lane] = F[m];
+            const double Ta = NSV ? q(1, 4) / over(q(1, 0)) : 0.0, Tb = NSV ? q(2, 4) / over(q(2, 0)) : 0.0;
+            zface<0, NSV, FLUX>(G, A.viscous_only, ring, invdx, hinv, vo, q, Ta, Tb, tap, tam, tbp, tbm, F);
+            double* out_f = isy ? &frow_y[3][0][0] : &fedge_x[0][0];
+            out_f[i] = F[0];
+            out_f[16 + i] = isy ? F[2] : F[1];
+            out_f[32 + i] = isy ? F[1] : F[2];
+            out_f[48 + i] = F[3];
+            out_f[64 + i] = F[4];
         }
         // z face above the cell (planes z - 1 .. z + 2 of this column)
-        double q2[5], Fup[5];
+        double q2[5], Tn = 0.0, Fup[5];
         {
-            load_prim(z + 2, c0, q2);
-            double qm[5], qa[5], qb[5];
-#pragma unroll
-            for (int k = 0; k < 5; ++k) {
-                qm[k] = ring[sA][k][c0];
-                qa[k] = ring[sB][k][c0];
-                qb[k] = ring[sC][k][c0];
-            }
+            __builtin_amdgcn_sched_barrier(0);   // not before the faces above: its registers would be held across them
+            load_prim(z + 2, own_off, q2);
+            auto q = [&](int i, int k) {
+                return i == 0 ? ring[sA][k][c0] : (i == 1 ? ring[sB][k][c0] : (i == 2 ? ring[sC][k][c0] : q2[k]));
+            };
             ZRef tap[3], tam[3], tbp[3], tbm[3];
+            if constexpr (NSV) Tn = q(2, 4) / over(q(2, 0));
             tap[0] = {sB, c0 + 1};   tam[0] = {sB, c0 - 1};   tbp[0] = {sC, c0 + 1};   tbm[0] = {sC, c0 - 1};
             tap[1] = {sB, c0 + kZW}; tam[1] = {sB, c0 - kZW}; tbp[1] = {sC, c0 + kZW}; tbm[1] = {sC, c0 - kZW};
             tap[2] = tam[2] = tbp[2] = tbm[2] = {sB, c0};
-            zface<2, NSV, FLUX>(G, A.viscous_only, ring, qm, qa, qb, q2, tap, tam, tbp, tbm, Fup);
+            zface<2, NSV, FLUX>(G, A.viscous_only, ring, G.invdx, G.hinv, vxyz, q, Tz, Tn, tap, tam, tbp, tbm, Fup);
         }
-        __syncthreads();   // edge faces written; plane z - 1 no longer read
+        // loads that travel across the barrier: f(y), or, without it, the halo of plane z + 2 (with both the FD
+        // form spills and takes 1032 us at 256^3, with f(y) alone 893, with neither 910; the residual takes 722 with
+        // the halo, 737 without)
+        __builtin_amdgcn_sched_barrier(0);
+        Raw halo;
         double f0v[5];
         if constexpr (MODE == MODE_FD) {
 #pragma unroll
-            for (int m = 0; m < 5; ++m) f0v[m] = A.f0[(long)m * G.ncell + go];
+            for (int m = 0; m < 5; ++m) f0v[m] = at(A.f0 + zo, m, own_off);
+        } else {
+            if (tid < kZHalo) load_raw(z + 2, halo_off, halo);
         }
+        __syncthreads();   // edge faces written; plane z - 1 no longer read
+        double eps_z = eps;
+        asm volatile("" : "+s"(eps_z));   // its reciprocal is formed per plane: no registers held for it across the faces
+        const auto qeps = over(eps_z);
 #pragma unroll
         for (int m = 0; m < 5; ++m) {
             if (tx == 15) rx[m] = (rx[m] - fedge_x[m][ty]) * G.invdx[0];
-            if ((ty & 3) == 3) ry[m] = (ry[m] - frow_y[(ty + 1) >> 2][m][tx]) * G.invdx[1];
+            if ((ty & 3) == 3) ry[m] = (ry[m] - frow_y[ty >> 2][m][tx]) * G.invdx[1];
             double res = rx[m];
             res = res + ry[m];
             res = res + (Fdown[m] - Fup[m]) * G.invdx[2];
             Fdown[m] = Fup[m];
             double x;
-            if constexpr (MODE == MODE_FD) x = (res - f0v[m]) / eps;
+            if constexpr (MODE == MODE_FD) x = (res - f0v[m]) / qeps;
             else x = res;
-            out[(long)m * G.ncell + go] = x;
+            using B64 = decltype(__builtin_amdgcn_raw_buffer_load_b64(rsrc(out, 0), 0, 0, 0));
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(B64, x), rsrc(out + zo, m), own_off, m * var, 0);
             nonfin = nonfin || !(fabs(x) < __builtin_inf());
         }
         // plane z + 2 replaces plane z - 1
 #pragma unroll
         for (int k = 0; k < 5; ++k) ring[sA][k][c0] = q2[k];
-        stage_halo(z + 2, sA);
+        if (tid < kZHalo) {
+            if constexpr (MODE == MODE_FD) {
+                __builtin_amdgcn_sched_barrier(0);
+                load_raw(z + 2, halo_off, halo);
+            }
+            stage_halo(halo, sA);
+        }
+        stage_temp(sC, Tn, (z + 2) & 3);
         __syncthreads();   // plane z + 2 staged; the edge faces read
         const int t = sA;
         sA = sB;
@@ -1061,7 +1134,7 @@ static hipError_t launch_v(const Geom& G, const ResArgs& A, hipStream_t st) {
     } else {
         if constexpr (RECON == 1 && GEO == 0 && std::is_same<S, double>::value && std::is_same<OUT, double>::value &&
                       MODE != MODE_TAN) {
-            if (G.n[0] % 16 == 0 && G.n[1] % 16 == 0) {
+            if (G.n[0] % 16 == 0 && G.n[1] % 16 == 0 && (long)G.n[0] * G.n[1] < (1L << 29)) {
                 // columns of 16 x 16 cells, each cut into nch ranges of planes: enough
                 // blocks to fill the chip once, ranges of at least 8 planes
                 const int nbx = G.n[0] / 16, nby = G.n[1] / 16;
@@ -1070,8 +1143,12 @@ static hipError_t launch_v(const Geom& G, const ResArgs& A, hipStream_t st) {
                 nch = std::min<long>(nch, std::max(1, G.n[2] / 8));
                 const long nb = ncol * nch;
                 if (nb <= 0 || nb > 0x7fffffffL) return hipErrorInvalidValue;
-                hipLaunchKernelGGL((k_res3z<NSV, FLUX, MODE>), dim3((unsigned)nb), dim3(kThreads), 0, st, G, A, nbx,
-                                   nby, (int)nch);
+                if (4L * G.ncell + (long)G.n[0] * G.n[1] < (1L << 29))   // a vector's variables below 2^32 bytes
+                    hipLaunchKernelGGL((k_res3z<NSV, FLUX, MODE, false>), dim3((unsigned)nb), dim3(kThreads), 0, st, G, A,
+                                       nbx, nby, (int)nch);
+                else
+                    hipLaunchKernelGGL((k_res3z<NSV, FLUX, MODE, true>), dim3((unsigned)nb), dim3(kThreads), 0, st, G, A,
+                                       nbx, nby, (int)nch);
                 return hipGetLastError();
             }
         }
