@@ -103,8 +103,17 @@ struct Stage {
 template <int D, int TX, int TY, int TZ, int HW, bool NSV>
 __device__ constexpr typename Stage<D, TX, TY, TZ, HW, NSV>::Cells kStageCells = Stage<D, TX, TY, TZ, HW, NSV>::make();
 
+// Threads of a tile kernel's block.  A 3-D FP64 tangent tile fills a CU's LDS by itself, so its waves come from
+// one block: 12 of them (168 registers each) take the tile's 912 faces in 15 pieces without regard to the direction.
+// Four waves that passed three times over one direction's 272 to 320 faces, with a
+// barrier after each, took 64 us at 64^3 and 121 at 90 x 75 x 61; eight 41 and 77, twelve 39 and 72, sixteen (128
+// registers) 41 and 76.  The FP32 tangent, with three blocks of four waves on a CU, is better off unmerged: 57 us at 90 x 75 x 61,
+// 71 with eight merged.
+template <int D, typename S, int MODE>
+constexpr int kTileThreads = (D == 3 && MODE == MODE_TAN && sizeof(S) == 16) ? 768 : kThreads;
+
 template <int D, int RECON, bool NSV, int FLUX, int GEO, typename S, int MODE, typename OUT, int TX, int TY, int TZ>
-__global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt0, int nt1) {
+__global__ __launch_bounds__((kTileThreads<D, S, MODE>)) void k_residual(Geom G, ResArgs A, int nt0, int nt1) {
     using T = Tile<D, TX, TY, TZ, (RECON == 0 ? 1 : 2)>;
     using R = typename Sc<S>::R;
     constexpr int NV = D + 2;
@@ -114,8 +123,10 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
     constexpr int OFF_VEL = CONS ? NV : 1;
     constexpr int OFF_P = OFF_VEL + D;
     constexpr int OFF_T = OFF_P + 1;
-    constexpr int CPT = T::CELLS / kThreads;
-    static_assert(T::CELLS % kThreads == 0, "tile must be a multiple of the block size");
+    constexpr int NT = kTileThreads<D, S, MODE>;
+    constexpr bool MERGED = NT > T::CELLS;
+    constexpr int CPT = MERGED ? 1 : T::CELLS / NT;
+    static_assert(MERGED || T::CELLS % NT == 0, "tile must be a multiple of the block size");
     using ST = Stage<D, TX, TY, TZ, T::H, NSV>;
     const auto& cells = kStageCells<D, TX, TY, TZ, T::H, NSV>;
     // 3-D: only the box cells the stencil reads are staged, packed in the order
@@ -135,7 +146,13 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
     constexpr int kFaceUnroll = (D == 2 && sizeof(S) == 8 && !PERT && FLUX == 0) ? 2 : 1;
 
     __shared__ S sq[NP][NSLOT];
-    __shared__ S fb[NV][T::NFMAX];
+    // face fluxes: of one direction at a time, or (merged) of all; of a tangent only the derivative leaves
+    using FB = typename std::conditional<MODE == MODE_TAN, R, S>::type;
+    auto flux_out = [](const S& x) -> FB {
+        if constexpr (MODE == MODE_TAN) return x.d;
+        else return x;
+    };
+    __shared__ FB fb[NV][MERGED ? T::NF0 + T::NF1 + T::NF2 : T::NFMAX];
     __shared__ unsigned short s_slot[PACKED ? T::BOX : 1];
     // FP32 form: the tile's reference state (float, and as doubles)
     __shared__ RefState<D, R> s_ref;
@@ -234,11 +251,11 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
     // rho <= 0 or p <= 0 (no positivity fix: the arithmetic goes on).
     int np = 0;
     if constexpr (!PERT) {
-        constexpr int NIT = (ST::N + kThreads - 1) / kThreads;
+        constexpr int NIT = (ST::N + NT - 1) / NT;
         S Ub[NIT][NV];
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
-            const int i = tid + it * kThreads;
+            const int i = tid + it * NT;
             if (it + 1 < NIT || i < ST::N) {
                 const int c = ST::LIST ? (int)cells.c[i] : i;
                 int bx = c % T::BX;
@@ -253,7 +270,7 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
         }
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
-            const int i = tid + it * kThreads;
+            const int i = tid + it * NT;
             if (it + 1 < NIT || i < ST::N) {
                 const int c = ST::LIST ? (int)cells.c[i] : i;
                 const int q = PACKED ? i : c;
@@ -287,7 +304,7 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
         // FP32 reference-state form: the state is converted in FP64 (one
         // reciprocal of the density) and the perturbation about the tile's
         // reference state is rounded to float
-        for (int i = tid; i < ST::N; i += kThreads) {
+        for (int i = tid; i < ST::N; i += NT) {
             const int c = ST::LIST ? (int)cells.c[i] : i;
             const int q = PACKED ? i : c;
             if constexpr (PACKED) s_slot[c] = (unsigned short)i;
@@ -326,7 +343,7 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
     if constexpr (MODE == MODE_FD) {
 #pragma unroll
         for (int k = 0; k < CPT; ++k) {
-            const int cell = tid + k * kThreads;
+            const int cell = tid + k * NT;
             const int gx = x0 + cell % TX, gy = y0 + (cell / TX) % TY, gz = z0 + cell / (TX * TY);
             const bool in = gx < n0 && gy < n1 && (D != 3 || gz < n2);
             const long gi = in ? ((long)gz * n1 + gy) * n0 + gx : 0;
@@ -335,18 +352,11 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
         }
     }
 
-    S res[CPT][NV];
-
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        const int FX = TX + (d == 0), FY = TY + (d == 1);
-        const int NF = (d == 0) ? T::NF0 : (d == 1 ? T::NF1 : T::NF2);
-        const int sd = T::stride(d);
-        // 2. every face flux of the tile along d, once (plain FP64: two faces
-        // interleaved per thread, which hides the latency of their long chains
-        // of divisions and square roots)
-#pragma unroll(kFaceUnroll)
-        for (int f = tid; f < NF; f += kThreads) {
+    // 2. the flux of face f of the tile along d (a compile-time direction), into fb from column fo on
+    auto face = [&](auto dir, int f, int fo) __attribute__((always_inline)) {
+            constexpr int d = decltype(dir)::value;
+            constexpr int FX = TX + (d == 0), FY = TY + (d == 1);
+            constexpr int sd = T::stride(d);
             int fx = f % FX;
             int fy = (f / FX) % FY;
             int fz = f / (FX * FY);
@@ -630,28 +640,72 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
                 }
             }
 #pragma unroll
-            for (int m = 0; m < NV; ++m) fb[m][f] = Fh[m];
-        }
-        __syncthreads();
-        // 3. flux differences of this thread's cells
-        const int fs = (d == 0) ? 1 : (d == 1 ? FX : FX * FY);
+            for (int m = 0; m < NV; ++m) fb[m][fo + f] = flux_out(Fh[m]);
+    };
+    // 3. flux differences of this thread's cells
+    FB res[CPT][NV];
+    auto difference = [&](auto dir, int fo) __attribute__((always_inline)) {
+        constexpr int d = decltype(dir)::value;
+        constexpr int FX = TX + (d == 0), FY = TY + (d == 1);
+        constexpr int fs = (d == 0) ? 1 : (d == 1 ? FX : FX * FY);
         const R inv = (R)G.invdx[d];
 #pragma unroll
         for (int k = 0; k < CPT; ++k) {
-            int cell = tid + k * kThreads;
+            int cell = tid + k * NT;
             int cx = cell % TX;
             int cy = (cell / TX) % TY;
             int cz = cell / (TX * TY);
-            int fl = (cz * FY + cy) * FX + cx;
+            int fl = fo + (cz * FY + cy) * FX + cx;
             R icell = inv;
             if constexpr (GEO >= 1) icell = G.metric[4L * G.ncell + wrap(y0 + cy, n1) * n0 + wrap(x0 + cx, n0)];
 #pragma unroll
             for (int m = 0; m < NV; ++m) {
-                S term = (fb[m][fl] - fb[m][fl + fs]) * icell;
+                FB term = (fb[m][fl] - fb[m][fl + fs]) * icell;
                 res[k][m] = (d == 0) ? term : res[k][m] + term;
             }
         }
+    };
+    using X = std::integral_constant<int, 0>;
+    using Y = std::integral_constant<int, 1>;
+    using Z = std::integral_constant<int, 2>;
+    if constexpr (MERGED) {
+        // waves take 64 faces at a time, of whichever direction
+        constexpr int W0 = (T::NF0 + 63) / 64, W1 = W0 + (T::NF1 + 63) / 64, W2 = W1 + (T::NF2 + 63) / 64;
+        const int lane = tid & 63;
+#pragma unroll 1
+        for (int t = __builtin_amdgcn_readfirstlane(tid >> 6); t < W2; t += NT / 64) {
+            if (t < W0) {
+                const int f = 64 * t + lane;
+                if (f < T::NF0) face(X(), f, 0);
+            } else if (t < W1) {
+                const int f = 64 * (t - W0) + lane;
+                if (f < T::NF1) face(Y(), f, T::NF0);
+            } else {
+                const int f = 64 * (t - W1) + lane;
+                if (f < T::NF2) face(Z(), f, T::NF0 + T::NF1);
+            }
+        }
         __syncthreads();
+        if (tid < T::CELLS) {
+            difference(X(), 0);
+            difference(Y(), T::NF0);
+            difference(Z(), T::NF0 + T::NF1);
+        }
+    } else {
+        // one direction after the other through the same columns (plain FP64: two faces
+        // interleaved per thread, which hides the latency of their long chains
+        // of divisions and square roots)
+#define ROK_DIRECTION(DIR, NF)                                 \
+    _Pragma("unroll(kFaceUnroll)") for (int f = tid; f < NF; f += NT) face(DIR(), f, 0); \
+    __syncthreads();                                           \
+    difference(DIR(), 0);                                      \
+    __syncthreads()
+        ROK_DIRECTION(X, T::NF0);
+        ROK_DIRECTION(Y, T::NF1);
+        if constexpr (D == 3) {
+            ROK_DIRECTION(Z, T::NF2);
+        }
+#undef ROK_DIRECTION
     }
 
     // 4. write out (and note a NaN or Inf in the output)
@@ -659,7 +713,8 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
     const auto qeps = over(eps);   // FD
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
-        int cell = tid + k * kThreads;
+        int cell = tid + k * NT;
+        if (MERGED && cell >= T::CELLS) break;
         int gx = x0 + cell % TX;
         int gy = y0 + (cell / TX) % TY;
         int gz = z0 + cell / (TX * TY);
@@ -675,7 +730,7 @@ __global__ __launch_bounds__(kThreads) void k_residual(Geom G, ResArgs A, int nt
             } else if constexpr (MODE == MODE_FD) {
                 x = (OUT)((res[k][m] - f0pre[k][m]) / qeps);
             } else {
-                x = (OUT)res[k][m].d;
+                x = (OUT)res[k][m];
             }
             out[o] = x;
             nonfin = nonfin || !(fabs((double)x) < __builtin_inf());
@@ -717,7 +772,7 @@ constexpr int kZW = 20;              // staged plane width (16 + 2 + 2)
 constexpr int kZR = kZW * kZW;       // cells of a staged plane
 constexpr int kZHalo = kZR - 256;    // its halo cells
 constexpr int kZT = 4 * 16 + 16;     // temperatures of a plane that waves exchange
-constexpr int kZBlocks = 1536;       // two rounds of three resident blocks on each of 256 CUs
+constexpr long kZBlocks = 768;       // resident blocks: three on each of 256 CUs
 
 constexpr int kBufRaw = 0x00020000;  // word 3 of a raw buffer descriptor (data format 32)
 
@@ -1117,7 +1172,7 @@ static hipError_t launch_t(const Geom& G, const ResArgs& A, hipStream_t st) {
     int nt2 = (D == 3) ? (G.n[2] + TZ - 1) / TZ : 1;
     long nb = (long)nt0 * nt1 * nt2;
     if (nb <= 0 || nb > 0x7fffffffL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_residual<D, RECON, NSV, FLUX, GEO, S, MODE, OUT, TX, TY, TZ>), dim3((unsigned)nb), dim3(kThreads), 0, st,
+    hipLaunchKernelGGL((k_residual<D, RECON, NSV, FLUX, GEO, S, MODE, OUT, TX, TY, TZ>), dim3((unsigned)nb), dim3(kTileThreads<D, S, MODE>), 0, st,
                        G, A, nt0, nt1);
     return hipGetLastError();
 }
@@ -1135,12 +1190,23 @@ static hipError_t launch_v(const Geom& G, const ResArgs& A, hipStream_t st) {
         if constexpr (RECON == 1 && GEO == 0 && std::is_same<S, double>::value && std::is_same<OUT, double>::value &&
                       MODE != MODE_TAN) {
             if (G.n[0] % 16 == 0 && G.n[1] % 16 == 0 && (long)G.n[0] * G.n[1] < (1L << 29)) {
-                // columns of 16 x 16 cells, each cut into nch ranges of planes: enough
-                // blocks to fill the chip once, ranges of at least 8 planes
+                // columns of 16 x 16 cells, each cut into nch ranges of planes: of the counts that
+                // fill one to four rounds of resident blocks the one whose rounds take the fewest planes, with
+                // one more for a range's start.  (Ranges of at least 8 planes, at least two rounds: residual
+                // and FD product 45 and 51 us at 64^3, 44 and 49 at 32^3; now 24 and 27, 11 and 12.  At 224^3,
+                // where one round leaves a quarter of the blocks out, 618 and 773 against 490 and 650 for three.)
                 const int nbx = G.n[0] / 16, nby = G.n[1] / 16;
-                const long ncol = (long)nbx * nby;
-                long nch = (kZBlocks + ncol - 1) / ncol;
-                nch = std::min<long>(nch, std::max(1, G.n[2] / 8));
+                const long ncol = (long)nbx * nby, n2 = G.n[2];
+                long nch = 1, least = 0;
+                for (int r = 1; r <= 4; ++r) {
+                    const long most = std::min(std::max(1L, r * kZBlocks / ncol), n2);
+                    const long planes = (n2 + most - 1) / most, c = (n2 + planes - 1) / planes;
+                    const long cost = ((ncol * c + kZBlocks - 1) / kZBlocks) * (planes + 1);
+                    if (r == 1 || cost < least) {
+                        nch = c;
+                        least = cost;
+                    }
+                }
                 const long nb = ncol * nch;
                 if (nb <= 0 || nb > 0x7fffffffL) return hipErrorInvalidValue;
                 if (4L * G.ncell + (long)G.n[0] * G.n[1] < (1L << 29))   // a vector's variables below 2^32 bytes
