@@ -136,7 +136,7 @@ void rok_destroy(rok_ctx* ctx);
 
 /* Selects how the modified Gram-Schmidt passes of rok_arnoldi / rok_step
  * run: ROK_MGS_PER_PASS launches one kernel per pass (the work vector is
- * streamed through memory); ROK_MGS_RESIDENT runs one cooperative kernel per
+ * streamed through memory); ROK_MGS_RESIDENT runs one kernel per
  * Arnoldi column with the work vector held in registers (N up to 16 * 2^18 = 4194304);
  * ROK_MGS_AUTO (default) takes the resident kernel when the device and N
  * allow it.  Both produce bit-identical results.  The setting also selects
@@ -161,6 +161,11 @@ void rok_destroy(rok_ctx* ctx);
  * Changes the context: not to be called while other calls on the same
  * context are being made.  ROK_EINVAL for an unknown path. */
 rok_status rok_set_mgs_path(rok_ctx* ctx, int path);
+
+/* For tests: the resident kernels of 256 blocks behave as if only the first
+ * `blocks` of them had found room on the device in time (0, the default: off).
+ * The results do not change.  ROK_EINVAL outside 0 .. 256. */
+rok_status rok_set_gang_hold(rok_ctx* ctx, int blocks);
 
 /* The orthogonalisation rok_arnoldi, rok_step and rok_mgs_column take on this
  * context for Krylov dimension M (1..ROK_MAX_M): ROK_MGS_PER_PASS,

@@ -18,6 +18,7 @@ struct rok_ctx {
     rok_problem pb;
     rok::Geom G;
     int mgs_path;
+    int gang_hold;   // see rok_set_gang_hold
 };
 
 namespace {
@@ -116,7 +117,7 @@ hipError_t arnoldi_core(const rok_ctx* c, const rok::Work& W, const double* y, c
         if (e != hipSuccess) return e;
         double* vnext = (j + 1 < M) ? V + (long)(j + 1) * N : nullptr;
         if (ortho == ORTHO_RESIDENT)
-            e = rok::launch_mgs_resident(W, W.w, V, N, M, j, vnext, st);
+            e = rok::launch_mgs_resident(W, W.w, V, N, M, j, vnext, st, c->gang_hold);
         else if (ortho == ORTHO_ONE_REDUCE)
             e = rok::launch_ls_column(W, W.w, V, N, M, j, vnext, st, deferred);
         else
@@ -240,7 +241,7 @@ hipError_t step_adjoint(const rok_ctx* c, const rok_tableau* tab, int M, double 
             // as h_{j+1,j} v_{j+1}: the basis' last column
             e = jvp_into(c, y_n, nullptr, vj, W.w, ROK_JVP_TANGENT, nullptr, 0.0, st, W.ints, j);
             if (e != hipSuccess) return e;
-            e = rok::launch_arnoldi_rev_col(W, A, M, j, N, resident, st);
+            e = rok::launch_arnoldi_rev_col(W, A, M, j, N, resident, st, c->gang_hold);
             if (e != hipSuccess) return e;
             // w = J(y) v_j:  vbar_j += J^T wbar,  ybar += d/dt [J(y + t v_j)^T wbar]
             e = rok::launch_vjp(c->G, recon, y_n, vj, A.wbar, A.Vbar + (long)j * N, ybar_n, 1, st, W.ints, j);
@@ -278,6 +279,7 @@ rok_status rok_create(const rok_problem* p, rok_ctx** out) {
     if (!c) return ROK_EINVAL;
     c->pb = *p;
     c->mgs_path = ROK_MGS_AUTO;
+    c->gang_hold = 0;
     rok::Geom& G = c->G;
     memset(&G, 0, sizeof(G));
     G.D = p->ndim;
@@ -361,6 +363,12 @@ rok_status rok_set_mgs_path(rok_ctx* c, int path) {
                path != ROK_MGS_ONE_REDUCE))
         return ROK_EINVAL;
     c->mgs_path = path;
+    return ROK_OK;
+}
+
+rok_status rok_set_gang_hold(rok_ctx* c, int blocks) {
+    if (!c || blocks < 0 || blocks > 256) return ROK_EINVAL;
+    c->gang_hold = blocks;
     return ROK_OK;
 }
 
@@ -704,7 +712,7 @@ rok_status rok_eigs(rok_ctx* c, const double* y, const double* v0, int k, int m,
                           rok::mgs_resident_available();
     if (c->mgs_path == ROK_MGS_RESIDENT && !resident) return ROK_EUNSUPPORTED;
     auto mgs = [&](const rok::Work& Wx, int j, double* vnext) -> hipError_t {
-        return resident ? rok::launch_mgs_resident(Wx, Wx.w, V, N, Mp, j, vnext, st)
+        return resident ? rok::launch_mgs_resident(Wx, Wx.w, V, N, Mp, j, vnext, st, c->gang_hold)
                         : rok::launch_mgs_column(Wx, Wx.w, V, N, Mp, j, vnext, st);
     };
     // orthonormalise W.w against V[:, 0..j] into V[:, j+1] by modified Gram-Schmidt,
@@ -942,7 +950,7 @@ rok_status rok_mgs_column(rok_ctx* c, const double* V, int M, int j, double* w, 
     if (ortho < 0) return ROK_EUNSUPPORTED;
     double* vn = (j + 1 < M) ? vnext : nullptr;
     if (ortho == ORTHO_RESIDENT)
-        ROK_TRY(rok::launch_mgs_resident(W, w, V, N, M, j, vn, st));
+        ROK_TRY(rok::launch_mgs_resident(W, w, V, N, M, j, vn, st, c->gang_hold));
     else if (ortho == ORTHO_ONE_REDUCE)
         ROK_TRY(rok::launch_ls_column(W, w, V, N, M, j, vn, st));
     else

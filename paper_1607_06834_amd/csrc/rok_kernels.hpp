@@ -50,7 +50,7 @@ constexpr int kRedBlocks = 1024;   // reduction grid (fixed: it fixes the summat
 constexpr int kRedThreads = 256;
 constexpr int kBarWords = 1024;   // exchange state (4 KiB)
 constexpr int kExchangeCopies = 8;   // copies of the exchange slots of the resident MGS kernels
-constexpr int kExchangeSlots = 3 * kExchangeCopies * kRedThreads;   // three buffers
+constexpr int kExchangeSlots = 3 * (kExchangeCopies + 1) * kRedThreads;   // three buffers, and three without copies
 constexpr unsigned long long kExchangeEmpty = 0x7ff4000000000ea5ull;   // an empty exchange slot: a signalling NaN
 
 size_t work_small_bytes(int M, int s);
@@ -84,8 +84,8 @@ hipError_t launch_norm_scale(const Work& W, const double* partials, int M, int j
 // Resident-w MGS for one column (rok_mgs.hip).
 bool mgs_resident_fits(long n);
 bool mgs_resident_available();
-hipError_t launch_mgs_resident(const Work& W, const double* w, const double* V, long n, int M, int j, double* vnext,
-                               hipStream_t st);
+hipError_t launch_mgs_resident(const Work& W, double* w, const double* V, long n, int M, int j, double* vnext,
+                               hipStream_t st, int hold);
 // Eigenvalue estimate pieces (rok_eigs.hip)
 hipError_t launch_combine(const double* V, long n, int m1, const double* C, int nc, double* Vout, hipStream_t st);
 namespace dense {
@@ -144,11 +144,11 @@ hipError_t launch_small_rev(const Work& W, const AdjWork& A, int M, int i, const
 hipError_t launch_vbar_stage(const Work& W, const AdjWork& A, int M, int i, double h, double* Fbar, long n,
                              bool first, hipStream_t st);
 hipError_t launch_abar_to_hbar(const Work& W, const AdjWork& A, int M, double hg, hipStream_t st);
-// resident: one cooperative kernel for the column (mgs_rev_resident_available(n)), else per-pass kernels
+// resident: one kernel for the column (mgs_rev_resident_available(n)), else per-pass kernels
 hipError_t launch_arnoldi_rev_col(const Work& W, const AdjWork& A, int M, int j, long n, bool resident,
-                                  hipStream_t st);
+                                  hipStream_t st, int hold);
 bool mgs_rev_resident_available(long n);
-hipError_t launch_mgs_rev_resident(const Work& W, const AdjWork& A, int M, int j, long n, hipStream_t st);
+hipError_t launch_mgs_rev_resident(const Work& W, const AdjWork& A, int M, int j, long n, hipStream_t st, int hold);
 hipError_t launch_beta_rev(const Work& W, const AdjWork& A, long n, hipStream_t st);
 
 }  // namespace rok

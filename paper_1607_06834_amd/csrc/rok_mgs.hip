@@ -45,14 +45,16 @@
 //
 // Grids by size (n elements; a block has 1024 threads):
 //   n <= 8192            one block, no exchange: up to 8 elements per thread
-//   n <= 65536           eight blocks, up to 8 elements per thread
-//   n <= 4194304         256 blocks, up to 16 elements per thread, cooperative
-// An exchange needs all blocks of its grid resident.  256 blocks fill the
-// chip, so only a cooperative launch guarantees that (it costs about 15 us
-// more than a plain one); eight blocks do not need it: a device
+//   n <= 32768           eight blocks, up to 4 elements per thread
+//   n <= 4194304         256 blocks, up to 16 elements per thread
+// An exchange needs all blocks of its grid running.  Eight blocks always get there: a device
 // runs at most one kernel per hardware queue at a time (streams on one queue
 // are serialised; 4 queues by default, 32 at most), so at most 32 x 8 = 256
-// blocks wait in exchanges, one per CU, and every other kernel drains.
+// blocks wait in exchanges, one per CU, and every other kernel drains.  256
+// blocks fill the chip, and settle first who takes part (Gang below).  Launched
+// cooperatively instead, which drains the stream around the kernel, a column cost 12 to 15 us more:
+// 611 x 389 step 909 us, now 710; 1024^2 step 2867, 2632; gradient at 512^2 9892, 8166;
+// adaptive 512^2 5649, 4552; 24 columns at 64^3 2386, 2072.
 //
 // The same machinery runs the reverse of a column for the discrete adjoint
 // of the step (k_mgs_rev_resident below): the normalisation and the passes
@@ -76,9 +78,12 @@ constexpr int kWaitVmcnt0 = 0x0F70;
 
 #define AGENT __HIP_MEMORY_SCOPE_AGENT
 
-// exchange words in Work::bar (unsigned): the number of the next exchange modulo 3, and the error word
+// exchange words in Work::bar (unsigned): the number of the next exchange modulo 3 (and that of the next exchange
+// of a closed gang), the error word, and the 64-bit gate
 constexpr int kBarPhase = 0;
+constexpr int kBarGangPhase = 1;
 constexpr int kBarErr = 32;
+constexpr int kBarGate = 64;
 
 // The lanes of a block: thread tid of block b holds, for k < K and c < C, the
 // element of lane (g * 256 + (tid & 255)), chunk c, of group
@@ -88,9 +93,10 @@ struct Lanes {
     static constexpr int NB = NB_, K = K_, C = C_, E = K_ * C_;
     static_assert(NB * 4 * K <= kRedBlocks, "groups past the canonical 1024");
     static_assert(C == 1 || 4 * K * NB == kRedBlocks, "chunks only where every lane of the grid is held");
-    static __device__ __forceinline__ int base() {
-        return (blockIdx.x + NB * (threadIdx.x >> 8)) * kRedThreads + (threadIdx.x & (kRedThreads - 1));
+    static __device__ __forceinline__ int base(int b) {
+        return (b + NB * (threadIdx.x >> 8)) * kRedThreads + (threadIdx.x & (kRedThreads - 1));
     }
+    static __device__ __forceinline__ int base() { return base(blockIdx.x); }
     static constexpr __device__ int step(int x) { return (x / C) * (NB * kPT) + (x % C) * kLanes; }
 };
 
@@ -123,6 +129,68 @@ __device__ __forceinline__ double wave_tree(double (&v)[K]) {
     return r;
 }
 
+// The gang of a launch of 256 blocks.  Its blocks wait for each other, and a plain launch does not promise
+// that all of them get onto the chip together: another stream's blocks may hold CUs, in the worst case while they
+// wait themselves.  So who takes part is settled by one word, the gate: every block adds 1 to its
+// lower half when it starts (a launch adds 256 in all, so the count says which launch it is in and
+// how many of its blocks have started), and a block that has waited long with no one coming (kGateIdle) may close the gate by
+// a compare-and-swap that writes the launch's mark and the count into the upper half, unless the
+// count is complete.  A block that finds the gate closed when it starts leaves.  With all 256 in, nobody
+// can close any more, and every block is running, so the waits end.  Closed, the blocks that are in do
+// the whole column by themselves (gang_column, gang_reverse), dealing the 256 blocks' work out among them: the same bits,
+// slower.  Nothing of this costs a launch but the one atomic, under the first loads.
+struct Gang {
+    unsigned base;   // the count before this launch
+    unsigned mark;   // this launch's mark: upper half of a closed gate without the count
+    int rank;        // this block's order of arrival, or -1: came to a closed gate
+    int size;        // blocks that take part (once closed)
+};
+constexpr int kGateSpins = 64;    // polls between two looks at the gate (about 50 us)
+constexpr int kGateIdle = 20;     // looks without an arrival before a block closes (about 1 ms)
+constexpr int kGateHold = 1 << 16;
+
+__device__ __forceinline__ unsigned long long* gate_word(unsigned* bar) { return (unsigned long long*)(bar + kBarGate); }
+
+// The launch's state in the gate's value g: 0 open, 256 complete, else the size of the closed gang.
+__device__ __forceinline__ int gate_state(const Gang& q, unsigned long long g) {
+    const unsigned hi = (unsigned)(g >> 32);
+    if ((hi & ~0xffu) == q.mark) return (int)(hi & 0xff);
+    return (unsigned)g - q.base == (unsigned)kBigGrid ? kBigGrid : 0;
+}
+
+// Closes the gate unless the count is complete; returns the state (each failed exchange is an arrival or a closure).
+__device__ __forceinline__ int gate_close(const Gang& q, unsigned* bar) {
+    unsigned long long g = __hip_atomic_load(gate_word(bar), __ATOMIC_RELAXED, AGENT);
+    for (;;) {
+        const int s = gate_state(q, g);
+        if (s) return s;
+        const unsigned n = (unsigned)g - q.base;
+        const unsigned long long want = (g & 0xffffffffull) | ((unsigned long long)(q.mark | n) << 32);
+        if (__hip_atomic_compare_exchange_strong(gate_word(bar), &g, want, __ATOMIC_RELAXED, __ATOMIC_RELAXED, AGENT))
+            return (int)n;
+    }
+}
+
+// This block enters (one thread).  hold > 0 (tests): the gang closes with that many blocks, the others coming late.
+__device__ __forceinline__ Gang gate_enter(unsigned* bar, int hold) {
+    auto mark_of = [](unsigned count) { return ((count / kBigGrid + 1) & 0xffffffu) << 8; };
+    if (hold > 0 && (int)blockIdx.x >= hold) {
+        for (int i = 0; i < kGateHold; ++i) {
+            const unsigned long long g = __hip_atomic_load(gate_word(bar), __ATOMIC_RELAXED, AGENT);
+            if (((unsigned)(g >> 32) & ~0xffu) == mark_of((unsigned)g)) break;
+        }
+    }
+    const unsigned long long g = __hip_atomic_fetch_add(gate_word(bar), 1ull, __ATOMIC_RELAXED, AGENT);
+    const unsigned count = (unsigned)g;
+    Gang q;
+    q.base = count - count % kBigGrid;
+    q.mark = mark_of(count);
+    q.rank = ((unsigned)(g >> 32) & ~0xffu) == q.mark ? -1 : (int)(count - q.base);
+    q.size = 0;
+    if (hold > 0 && q.rank == hold - 1) gate_close(q, bar);
+    return q;
+}
+
 // LDS of one exchange: the block trees' cross-wave levels (SK values per thread), the group sums, the result
 template <int K>
 struct ExLds {
@@ -132,6 +200,7 @@ struct ExLds {
     double gs[4 * K];
     double out;
     int err;
+    Gang gang;
 };
 
 // The block's value of one canonical sum: acc[k] is this thread's lane sum of
@@ -193,15 +262,32 @@ __device__ __forceinline__ double block_value(double (&acc)[L::K], ExLds<L::K>& 
 // only be passed through from the caller's data, is published as another NaN).
 constexpr unsigned long long kEmptySlot = kExchangeEmpty;
 
+constexpr int kBufSlots = kCopies * kRedThreads;       // slots of one buffer
+constexpr int kGangSlots = 3 * kBufSlots;              // first slot of a closed gang's three buffers (one copy each)
+
+__device__ __forceinline__ unsigned long long slot_bits(double v) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    return u == kEmptySlot ? 0x7ff8000000000000ull : u;
+}
+
+// wave 0: final lanes t and t + 128, then t and t + 64, then the wave's tree
+__device__ __forceinline__ double final_value(const unsigned long long (&u)[4]) {
+    double t[1] = {(__longlong_as_double((long long)u[0]) + __longlong_as_double((long long)u[2])) +
+                   (__longlong_as_double((long long)u[1]) + __longlong_as_double((long long)u[3]))};
+    return lane_value(wave_tree<1>(t), 0);
+}
+
+constexpr int kExFailed = 1, kExClosed = 2;   // ways an exchange does not give a sum
+
 // Canonical sum over the grid of the lane sums acc[k]; every thread gets it in
 // *out.  phase: the exchange's number modulo 3, advanced.  mid() runs in the
 // waves 1-15 once the block's value is out, after() in wave 0 once the other
 // blocks' values have arrived (its loads would otherwise delay the polls:
-// loads return in order).  One block alone calls neither.  False (in every thread of the
-// block) if the exchange failed.
+// loads return in order).  One block alone calls neither.  Nonzero (in every thread of the
+// block) if the exchange failed, or if it is the launch's first and the gang has been closed.
 template <class L, typename Mid, typename After>
-__device__ __forceinline__ bool grid_sum(double (&acc)[L::K], ExLds<L::K>& X, double* slots, int& phase, unsigned* bar,
-                                         double* out, Mid mid, After after) {
+__device__ __forceinline__ int grid_sum(double (&acc)[L::K], ExLds<L::K>& X, double* slots, int& phase, unsigned* bar,
+                                        bool first, double* out, Mid mid, After after) {
     constexpr int NB = L::NB;
     const int tid = threadIdx.x;
     double v = block_value<L>(acc, X);
@@ -209,19 +295,15 @@ __device__ __forceinline__ bool grid_sum(double (&acc)[L::K], ExLds<L::K>& X, do
         if (tid == 0) X.out = v;
         __syncthreads();
         *out = X.out;
-        return true;
+        return 0;
     } else {
-        constexpr int kBuf = kCopies * kRedThreads;   // slots of one buffer
-        unsigned long long* buf = (unsigned long long*)slots + phase * kBuf;
+        unsigned long long* buf = (unsigned long long*)slots + phase * kBufSlots;
         if (tid < 64) {
             // the slots emptied after the last exchange are seen empty before this value is seen
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-            if (tid < kCopies) {
-                unsigned long long u = (unsigned long long)__double_as_longlong(v);
-                if (u == kEmptySlot) u = 0x7ff8000000000000ull;
-                __hip_atomic_store(buf + tid * kRedThreads + blockIdx.x, u, __ATOMIC_RELAXED, AGENT);
-            }
+            if (tid < kCopies)
+                __hip_atomic_store(buf + tid * kRedThreads + blockIdx.x, slot_bits(v), __ATOMIC_RELAXED, AGENT);
         }
         __syncthreads();
         if (tid >= 64) {
@@ -231,7 +313,8 @@ __device__ __forceinline__ bool grid_sum(double (&acc)[L::K], ExLds<L::K>& X, do
             constexpr int Q = (NB + 63) / 64;
             unsigned long long u[Q];
             long spins = 0;
-            int err = 0;
+            int err = 0, idle = 0;
+            unsigned seen = 0;
             for (;;) {
                 bool miss = false;
 #pragma unroll
@@ -245,23 +328,37 @@ __device__ __forceinline__ bool grid_sum(double (&acc)[L::K], ExLds<L::K>& X, do
                 if (++spins > kSpinLimit ||
                     ((spins & 1023) == 0 && __hip_atomic_load(bar + kBarErr, __ATOMIC_RELAXED, AGENT))) {
                     if (tid == 0) __hip_atomic_store(bar + kBarErr, 1u, __ATOMIC_RELAXED, AGENT);
-                    err = 1;
+                    err = kExFailed;
                     break;
+                }
+                if (NB == kBigGrid && first && spins % kGateSpins == 0) {
+                    // (a complete gate stays complete: then only the slots are waited for)
+                    const unsigned long long g = __hip_atomic_load(gate_word(bar), __ATOMIC_RELAXED, AGENT);
+                    int s = gate_state(X.gang, g);
+                    if (s == 0) {
+                        idle = (unsigned)g == seen ? idle + 1 : 0;
+                        seen = (unsigned)g;
+                        if (idle >= kGateIdle) s = gate_close(X.gang, bar);   // (every lane: the first one closes)
+                    }
+                    s = __builtin_amdgcn_readfirstlane(s);
+                    if (s > 0 && s < kBigGrid) {
+                        if (tid == 0) X.gang.size = s;
+                        err = kExClosed;
+                        break;
+                    }
                 }
             }
             after();
-            double x;
-            if constexpr (Q == 4)   // final lanes t and t + 128, then t and t + 64
-                x = (__longlong_as_double((long long)u[0]) + __longlong_as_double((long long)u[2])) +
-                    (__longlong_as_double((long long)u[1]) + __longlong_as_double((long long)u[3]));
-            else
-                x = __longlong_as_double((long long)u[0]);   // lanes past NB hold 0
+            if constexpr (Q == 4) {
+                v = final_value(u);
+            } else {
+                double t[1] = {__longlong_as_double((long long)u[0])};   // lanes past NB hold 0
+                v = lane_value(wave_tree<1>(t), 0);
+            }
             static_assert(Q == 4 || Q == 1, "256 blocks, or at most 64");
-            double t[1] = {x};
-            v = lane_value(wave_tree<1>(t), 0);
-            if (tid < kCopies)
-                __hip_atomic_store((unsigned long long*)slots + (phase == 0 ? 2 : phase - 1) * kBuf + tid * kRedThreads +
-                                       blockIdx.x,
+            if (tid < kCopies && err == 0)
+                __hip_atomic_store((unsigned long long*)slots + (phase == 0 ? 2 : phase - 1) * kBufSlots +
+                                       tid * kRedThreads + blockIdx.x,
                                    kEmptySlot, __ATOMIC_RELAXED, AGENT);
             if (tid == 0) {
                 X.out = v;
@@ -269,10 +366,76 @@ __device__ __forceinline__ bool grid_sum(double (&acc)[L::K], ExLds<L::K>& X, do
             }
         }
         __syncthreads();
-        phase = phase == 2 ? 0 : phase + 1;
         *out = X.out;
-        return X.err == 0;
+        const int err = X.err;
+        if (err == 0) phase = phase == 2 ? 0 : phase + 1;
+        return err;
     }
+}
+
+// A block of a closed gang, after its first exchange (number `phase`): the slots that a complete launch's next
+// exchange would have emptied, and its own of this exchange, which nobody reads.
+__device__ __forceinline__ void gang_start(const Gang& q, double* slots, int phase) {
+    const int tid = threadIdx.x;
+    if (tid >= kCopies) return;
+    unsigned long long* prev = (unsigned long long*)slots + (phase == 0 ? 2 : phase - 1) * kBufSlots + tid * kRedThreads;
+    for (int b = q.rank; b < kBigGrid; b += q.size) __hip_atomic_store(prev + b, kEmptySlot, __ATOMIC_RELAXED, AGENT);
+    __hip_atomic_store((unsigned long long*)slots + phase * kBufSlots + tid * kRedThreads + blockIdx.x, kEmptySlot,
+                       __ATOMIC_RELAXED, AGENT);
+}
+
+// Canonical sum in a closed gang: its blocks publish the values of all 256 (lanes(b) is this thread's lane sum in
+// the place of block b) in slots of their own.  False if the exchange failed.
+template <class L, typename Fn>
+__device__ __forceinline__ bool gang_sum(const Gang& q, ExLds<L::K>& X, double* slots, int& phase, unsigned* bar,
+                                         double* out, Fn lanes) {
+    static_assert(L::NB == kBigGrid && L::K == 1, "the grid that needs it");
+    const int tid = threadIdx.x;
+    unsigned long long* gs = (unsigned long long*)slots + kGangSlots;
+    for (int b = q.rank; b < kBigGrid; b += q.size) {
+        double acc[1] = {lanes(b)};
+        const double v = block_value<L>(acc, X);
+        if (tid < 64) {
+            // the slots emptied after the last exchange are seen empty before this value is seen
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+            if (tid == 0)
+                __hip_atomic_store(gs + phase * kRedThreads + b, slot_bits(v), __ATOMIC_RELAXED, AGENT);
+        }
+        __syncthreads();   // the block's LDS is free again
+    }
+    if (tid < 64) {
+        unsigned long long u[4];
+        long spins = 0;
+        int err = 0;
+        for (;;) {
+            bool miss = false;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                u[k] = __hip_atomic_load(gs + phase * kRedThreads + tid + 64 * k, __ATOMIC_RELAXED, AGENT);
+                miss = miss || u[k] == kEmptySlot;
+            }
+            if (!__any(miss)) break;
+            if (++spins > kSpinLimit || ((spins & 1023) == 0 && __hip_atomic_load(bar + kBarErr, __ATOMIC_RELAXED, AGENT))) {
+                if (tid == 0) __hip_atomic_store(bar + kBarErr, 1u, __ATOMIC_RELAXED, AGENT);
+                err = kExFailed;
+                break;
+            }
+        }
+        const double v = final_value(u);
+        for (int b = q.rank + q.size * tid; b < kBigGrid; b += q.size * 64)
+            __hip_atomic_store(gs + (phase == 0 ? 2 : phase - 1) * kRedThreads + b, kEmptySlot, __ATOMIC_RELAXED, AGENT);
+        if (tid == 0) {
+            X.out = v;
+            X.err = err;
+        }
+    }
+    __syncthreads();
+    phase = phase == 2 ? 0 : phase + 1;
+    *out = X.out;
+    const bool ok = X.err == 0;
+    __syncthreads();   // X.out is read before the next exchange writes it
+    return ok;
 }
 
 // A failed exchange: the results are invalid; later columns do nothing.
@@ -351,21 +514,102 @@ struct LaneVec {
     }
 };
 
+// The end of a column with sum of squares nn: writes h_{j+1,j} (block `lead`), returns it, *brk: breakdown.
+__device__ __forceinline__ double column_norm(double nn, const double* hcol, int M, int j, double* H, int* ints, bool lead,
+                                              bool* brk) {
+    const double hn = sqrt(nn);
+    double c = 0.0;
+    for (int q = 0; q <= j; ++q) c = c + hcol[q] * hcol[q];
+    c = c + hn * hn;
+    *brk = hn <= kBreakdownTolR * sqrt(c);
+    if (lead && threadIdx.x == 0) {
+        H[(j + 1) * M + j] = hn;
+        if (*brk) {
+            ints[0] = j + 1;
+            ints[1] = 1;
+            ints[2] |= ROK_FLAG_BREAKDOWN;
+        }
+        if (!(hn == hn) || hn == __builtin_inf()) ints[2] |= ROK_FLAG_NONFINITE;
+    }
+    return hn;
+}
+
+// The column by a closed gang: w in memory (its buffer is free to change), the passes of k_mgs_resident.  False if an exchange failed.
 template <class L>
-__global__ __launch_bounds__(kPT) void k_mgs_resident(const double* wsrc, const double* V, long n, int M, int j,
+__device__ __forceinline__ bool gang_column(double* w, const double* V, long n, int M, int j, double* H, double* vnext,
+                                            int* ints, double* slots, unsigned* bar, ExLds<L::K>& X, double* hcol) {
+    const Gang q = X.gang;
+    const bool lead = q.rank == 0;
+    int phase = (int)bar[kBarGangPhase];
+    double h = 0.0;
+    for (int i = 0; i <= j; ++i) {
+        const double *prev = V + (long)(i - 1) * n, *cur = V + (long)i * n;
+        if (!gang_sum<L>(q, X, slots, phase, bar, &h, [&](int b) {
+                double acc = 0.0;
+                for (int c = 0; c < L::C; ++c) {
+                    const long e = L::base(b) + (long)c * kLanes;
+                    if (e >= n) continue;
+                    double wk = w[e];
+                    if (i > 0) {
+                        wk = wk - h * prev[e];
+                        w[e] = wk;
+                    }
+                    acc = acc + cur[e] * wk;
+                }
+                return acc;
+            }))
+            return false;
+        if (threadIdx.x == 0) {
+            hcol[i] = h;
+            if (lead) H[i * M + j] = h;
+        }
+    }
+    double nn = 0.0;
+    if (j + 1 < M) {
+        const double* last = V + (long)j * n;
+        if (!gang_sum<L>(q, X, slots, phase, bar, &nn, [&](int b) {
+                double acc = 0.0;
+                for (int c = 0; c < L::C; ++c) {
+                    const long e = L::base(b) + (long)c * kLanes;
+                    if (e >= n) continue;
+                    const double wk = w[e] - h * last[e];
+                    w[e] = wk;
+                    acc = acc + wk * wk;
+                }
+                return acc;
+            }))
+            return false;
+    }
+    // every block has read the word: all have taken part in an exchange since
+    if (lead && threadIdx.x == 0) bar[kBarGangPhase] = (unsigned)phase;
+    if (j + 1 >= M) return true;
+    bool brk;
+    const double hn = column_norm(nn, hcol, M, j, H, ints, lead, &brk);
+    if (brk) return true;
+    for (int b = q.rank; b < kBigGrid; b += q.size)
+        for (int c = 0; c < L::C; ++c) {
+            const long e = L::base(b) + (long)c * kLanes;
+            if (e < n) vnext[e] = w[e] / hn;
+        }
+    return true;
+}
+
+template <class L>
+__global__ __launch_bounds__(kPT) void k_mgs_resident(double* wsrc, const double* V, long n, int M, int j,
                                                      double* H, double* vnext, int* ints, double* slots,
-                                                     unsigned* bar) {
+                                                     unsigned* bar, int hold) {
     constexpr int E = L::E, K = L::K, C = L::C;
     constexpr bool LDSW = E >= 16;
     __shared__ ExLds<K> X;
     __shared__ double s_w[LDSW ? E * kPT : 1];
     __shared__ int s_stop, s_phase;
     if (threadIdx.x == 0) {
+        if constexpr (L::NB == kBigGrid) X.gang = gate_enter(bar, hold);
         s_stop = ints[1];
         s_phase = L::NB > 1 ? (int)bar[kBarPhase] : 0;
     }
     __syncthreads();
-    if (s_stop) return;
+    if (s_stop || (L::NB == kBigGrid && X.gang.rank < 0)) return;
     int phase = s_phase;
     // Two basis-vector arrays alternate: at pass i one holds v_{i-1} (for the
     // update w -= h v_{i-1}) and v_{i+1} is loaded into it after use: by the
@@ -386,7 +630,7 @@ __global__ __launch_bounds__(kPT) void k_mgs_resident(const double* wsrc, const 
     load_lane<L, Fetch<L>::kHint>(V, n, A);
     __shared__ double s_hcol[kMaxM + 1];
     double h = 0.0;
-    bool failed = false;
+    int failed = 0;
     auto none = [] {};
     // Pass i with cur = v_i and prev = v_{i-1}: w -= h_{i-1} prev (i > 0),
     // h_i = <v_i, w>, then prev <- v_{i+1}.
@@ -420,10 +664,8 @@ __global__ __launch_bounds__(kPT) void k_mgs_resident(const double* wsrc, const 
         };
         // unconditional (v_j again after the last pass, 64 lanes' worth): no branch around the loads
         auto after = [&] { load_lane<L, kHint>(next, n, prev); };
-        if (!grid_sum<L>(acc, X, slots, phase, bar, &h, mid, after)) {
-            failed = true;
-            return;
-        }
+        failed = grid_sum<L>(acc, X, slots, phase, bar, i == 0, &h, mid, after);
+        if (failed) return;
         if (threadIdx.x == 0) s_hcol[i] = h;
         if (blockIdx.x == 0 && threadIdx.x == 0) H[i * M + j] = h;
     };
@@ -437,6 +679,12 @@ __global__ __launch_bounds__(kPT) void k_mgs_resident(const double* wsrc, const 
         ++i;
     }
     if (failed) {
+        if constexpr (L::NB == kBigGrid) {
+            if (failed == kExClosed) {
+                gang_start(X.gang, slots, phase);
+                if (gang_column<L>(wsrc, V, n, M, j, H, vnext, ints, slots, bar, X, s_hcol)) return;
+            }
+        }
         exchange_failed(ints, true);
         return;
     }
@@ -462,25 +710,13 @@ __global__ __launch_bounds__(kPT) void k_mgs_resident(const double* wsrc, const 
         }
     }
     double nn;
-    if (!grid_sum<L>(acc, X, slots, phase, bar, &nn, none, none)) {
+    if (grid_sum<L>(acc, X, slots, phase, bar, false, &nn, none, none)) {
         exchange_failed(ints, true);
         return;
     }
     keep_phase();
-    const double hn = sqrt(nn);
-    double c = 0.0;
-    for (int q = 0; q <= j; ++q) c = c + s_hcol[q] * s_hcol[q];
-    c = c + hn * hn;
-    const bool brk = hn <= kBreakdownTolR * sqrt(c);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        H[(j + 1) * M + j] = hn;
-        if (brk) {
-            ints[0] = j + 1;
-            ints[1] = 1;
-            ints[2] |= ROK_FLAG_BREAKDOWN;
-        }
-        if (!(hn == hn) || hn == __builtin_inf()) ints[2] |= ROK_FLAG_NONFINITE;
-    }
+    bool brk;
+    const double hn = column_norm(nn, s_hcol, M, j, H, ints, blockIdx.x == 0, &brk);
     if (brk) return;
     double v[E];
 #pragma unroll
@@ -503,15 +739,82 @@ __global__ __launch_bounds__(kPT) void k_mgs_resident(const double* wsrc, const 
 // the per-pass reverse kernels, whose results this reproduces bit for bit).
 // Nothing runs for j >= M_eff or after a failed in-kernel barrier.
 template <class L>
-__global__ __launch_bounds__(kPT) void k_mgs_rev_resident(const double* wsrc, const double* V, double* Vbar,
+__device__ __forceinline__ bool gang_reverse(double* w, const double* V, double* Vbar, const double* sh, const double* shb, long n,
+                                             int j, bool nrm, double* wbar, double* slots, unsigned* bar, ExLds<L::K>& X) {
+    // by a closed gang, w and wbar in memory
+    const Gang q = X.gang;
+    int phase = (int)bar[kBarGangPhase];
+    double d = 0.0, rho = 0.0, coef = 0.0;
+    const double *vn = V + (long)(j + 1) * n, *vbn = Vbar + (long)(j + 1) * n, *vj = V + (long)j * n;
+    auto sum = [&](auto term) {
+        return gang_sum<L>(q, X, slots, phase, bar, &d, [&](int b) {
+            double acc = 0.0;
+            for (int c = 0; c < L::C; ++c) {
+                const long e = L::base(b) + (long)c * kLanes;
+                if (e < n) acc = acc + term(e);
+            }
+            return acc;
+        });
+    };
+    if (nrm) {
+        if (!sum([&](long e) { return vbn[e] * vn[e]; })) return false;
+        rho = sh[j + 1];
+        coef = shb[j + 1] - d / rho;
+    }
+    if (!sum([&](long e) {
+            double wk, b;
+            if (nrm) {
+                wk = rho * vn[e];
+                b = vbn[e] / rho + coef * vn[e];
+            } else {
+                wk = w[e];
+                for (int i = 0; i <= j; ++i) wk = wk - sh[i] * V[(long)i * n + e];
+                b = 0.0;
+            }
+            w[e] = wk;
+            wbar[e] = b;
+            return b * vj[e];
+        }))
+        return false;
+    for (int i = j; i >= 0; --i) {
+        const double h = sh[i], hb = shb[i] - d;
+        const double *cur = V + (long)i * n, *prev = V + (long)(i - 1) * n;
+        double* vb = Vbar + (long)i * n;
+        auto pass = [&](long e) {
+            const double v = cur[e];
+            const double wo = w[e] + h * v;
+            w[e] = wo;
+            const double b = wbar[e];
+            vb[e] = vb[e] + hb * wo - h * b;
+            const double wn = b + hb * v;
+            wbar[e] = wn;
+            return wn;
+        };
+        if (i > 0) {
+            if (!sum([&](long e) { return pass(e) * prev[e]; })) return false;
+        } else {
+            for (int b = q.rank; b < kBigGrid; b += q.size)
+                for (int c = 0; c < L::C; ++c) {
+                    const long e = L::base(b) + (long)c * kLanes;
+                    if (e < n) pass(e);
+                }
+        }
+    }
+    if (q.rank == 0 && threadIdx.x == 0) bar[kBarGangPhase] = (unsigned)phase;
+    return true;
+}
+
+template <class L>
+__global__ __launch_bounds__(kPT) void k_mgs_rev_resident(double* wsrc, const double* V, double* Vbar,
                                                          const double* H, const double* Hbar, long n, int M, int j,
                                                          double* wbar_out, int* ints, double* slots,
-                                                         unsigned* bar) {
+                                                         unsigned* bar, int hold) {
     constexpr int E = L::E, K = L::K, C = L::C;
     __shared__ ExLds<K> X;
     __shared__ int s_m, s_bad, s_phase;
     __shared__ double s_h[kMaxM + 1], s_hb[kMaxM + 1];   // column j of H and Hbar
     if (threadIdx.x == 0) {
+        if constexpr (L::NB == kBigGrid) X.gang = gate_enter(bar, hold);
         s_m = ints[0];
         s_bad = (ints[2] & ROK_FLAG_BARRIER) != 0;
         s_phase = L::NB > 1 ? (int)bar[kBarPhase] : 0;
@@ -522,19 +825,19 @@ __global__ __launch_bounds__(kPT) void k_mgs_rev_resident(const double* wsrc, co
     }
     __syncthreads();
     const int m = s_m;
-    if (j >= m || s_bad) return;
+    if (j >= m || s_bad || (L::NB == kBigGrid && X.gang.rank < 0)) return;
     const bool nrm = j + 1 < m;
     double w[E], wb[E], A[E], B[E], vb[E];
     int phase = s_phase;
     double d = 0.0;
-    bool failed = false;
+    int failed = 0;
     // canonical sum of the lane sums acc; loads(): the caller's prefetch, issued
     // by the waves 1-15 when the block's value is out and by wave 0 after its polls
-    auto exchange = [&](double (&acc)[K], auto loads) {
+    auto exchange = [&](double (&acc)[K], bool first, auto loads) {
 #pragma unroll
         for (int k = 0; k < K; ++k) asm volatile("" : "+v"(acc[k]) : : "memory");
         if constexpr (L::NB == 1) loads();
-        if (!grid_sum<L>(acc, X, slots, phase, bar, &d, loads, loads)) failed = true;
+        failed = grid_sum<L>(acc, X, slots, phase, bar, first, &d, loads, loads);
     };
     if (nrm) {
         load_lane<L>(V + (long)(j + 1) * n, n, A);      // v_{j+1}
@@ -542,7 +845,7 @@ __global__ __launch_bounds__(kPT) void k_mgs_rev_resident(const double* wsrc, co
         double acc[K];
 #pragma unroll
         for (int x = 0; x < E; ++x) acc[x / C] = (x % C ? acc[x / C] : 0.0) + vb[x] * A[x];
-        exchange(acc, [&] { load_lane<L>(V + (long)j * n, n, B); });
+        exchange(acc, true, [&] { load_lane<L>(V + (long)j * n, n, B); });
         if (failed) goto fail;
         const double rho = s_h[j + 1];
         const double coef = s_hb[j + 1] - d / rho;
@@ -566,7 +869,7 @@ __global__ __launch_bounds__(kPT) void k_mgs_rev_resident(const double* wsrc, co
         double acc[K];
 #pragma unroll
         for (int x = 0; x < E; ++x) acc[x / C] = (x % C ? acc[x / C] : 0.0) + wb[x] * B[x];
-        exchange(acc, [&] {
+        exchange(acc, !nrm, [&] {
             load_lane<L>(V + (long)(j > 0 ? j - 1 : 0) * n, n, A);
             load_lane<L>(Vbar + (long)j * n, n, vb);
         });
@@ -591,7 +894,7 @@ __global__ __launch_bounds__(kPT) void k_mgs_rev_resident(const double* wsrc, co
             }
             store_lane<L>(Vbar + (long)i * n, n, vb);
             if (i == 0) return;
-            exchange(acc, [&] {
+            exchange(acc, false, [&] {
                 load_lane<L>(V + (long)(i > 1 ? i - 2 : 0) * n, n, cur);
                 load_lane<L>(Vbar + (long)(i - 1) * n, n, vb);
             });
@@ -612,20 +915,18 @@ __global__ __launch_bounds__(kPT) void k_mgs_rev_resident(const double* wsrc, co
     if (L::NB > 1 && blockIdx.x == 0 && threadIdx.x == 0) bar[kBarPhase] = (unsigned)phase;
     return;
 fail:
+    if constexpr (L::NB == kBigGrid) {
+        if (failed == kExClosed) {
+            gang_start(X.gang, slots, phase);
+            if (gang_reverse<L>(wsrc, V, Vbar, s_h, s_hb, n, j, nrm, wbar_out, slots, bar, X)) return;
+        }
+    }
     exchange_failed(ints, false);
 }
 
-// Cooperative for the big grid (all its blocks must be resident together), plain for the small ones.
-template <class L>
-static hipError_t launch_grid(const void* f, void** args, hipStream_t st) {
-    if (L::NB == kBigGrid) return hipLaunchCooperativeKernel(f, dim3(L::NB), dim3(kPT), args, 0, st);
-    return hipLaunchKernel(f, dim3(L::NB), dim3(kPT), args, 0, st);
-}
-
 // The shape of a vector of n elements (n <= 16 * 262144): fn(Lanes<...>{}).  MAXE: most elements per thread
-// the kernel holds.  The lines: one block streams a basis vector of 8192 elements in about the time of an
-// exchange; eight blocks hold 8 elements per thread at 65536 (a pass there takes about 3 us, against 2.2 us plus
-// the cooperative launch's 15 us a column on 256 blocks); past that, 256.
+// the kernel holds.  The lines, in us a column of a basis of 24 columns: one block 25.4 at 8192 and eight blocks 26.7 at
+// 16384; eight blocks 28.1 at 32768 (256: 32.6) and 35.1 at 65536 (256: 32.7).
 template <int MAXE, typename Fn>
 static hipError_t with_shape(long n, Fn fn) {
     if (n <= 1024) return fn(Lanes<1, 1, 1>{});
@@ -634,7 +935,6 @@ static hipError_t with_shape(long n, Fn fn) {
     if (n <= 8192) return fn(Lanes<1, 8, 1>{});
     if (n <= 16384) return fn(Lanes<kMidGrid, 2, 1>{});
     if (n <= 32768) return fn(Lanes<kMidGrid, 4, 1>{});
-    if (n <= 65536) return fn(Lanes<kMidGrid, 8, 1>{});
     if (n <= kLanes) return fn(Lanes<kBigGrid, 1, 1>{});
     if (n <= 2L * kLanes) return fn(Lanes<kBigGrid, 1, 2>{});
     if (n <= 4L * kLanes) return fn(Lanes<kBigGrid, 1, 4>{});
@@ -647,36 +947,35 @@ static hipError_t with_shape(long n, Fn fn) {
 // Whether the resident kernel takes vectors of n elements.
 bool mgs_resident_fits(long n) { return n <= 16L * kLanes; }
 
-// True if the device can host kernel f's cooperative grid.
-static bool coop_available(const void* f) {
-    int dev = 0, coop = 0, cus = 0, nb = 0;
+// True if the device holds kernel f's 256 blocks at once.
+static bool grid_resident(const void* f) {
+    int dev = 0, cus = 0, nb = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, kPT, 0) != hipSuccess)
         return false;
-    return coop && (long)nb * cus >= kBigGrid;
+    return (long)nb * cus >= kBigGrid;
 }
 
-static int g_coop_ok = -1;
+static int g_fwd_ok = -1;
 
-// True if the device can host the cooperative grid (checked once).
+// True if the device can host the forward kernels' grid (checked once).
 bool mgs_resident_available() {
-    if (g_coop_ok < 0) g_coop_ok = coop_available((const void*)k_mgs_resident<Lanes<kBigGrid, 1, 16>>) ? 1 : 0;
-    return g_coop_ok == 1;
+    if (g_fwd_ok < 0) g_fwd_ok = grid_resident((const void*)k_mgs_resident<Lanes<kBigGrid, 1, 16>>) ? 1 : 0;
+    return g_fwd_ok == 1;
 }
 
-hipError_t launch_mgs_resident(const Work& W, const double* w, const double* V, long n, int M, int j, double* vnext,
-                               hipStream_t st) {
+hipError_t launch_mgs_resident(const Work& W, double* w, const double* V, long n, int M, int j, double* vnext,
+                               hipStream_t st, int hold) {
     double* H = W.H;
     int* ints = W.ints;
     double* slots = W.gpart;
     unsigned* bar = W.bar;
     void* args[] = {(void*)&w, (void*)&V, (void*)&n, (void*)&M, (void*)&j, (void*)&H, (void*)&vnext,
-                    (void*)&ints, (void*)&slots, (void*)&bar};
+                    (void*)&ints, (void*)&slots, (void*)&bar, (void*)&hold};
     return with_shape<16>(n, [&](auto shape) {
         using L = decltype(shape);
-        return launch_grid<L>((const void*)k_mgs_resident<L>, args, st);
+        return hipLaunchKernel((const void*)k_mgs_resident<L>, dim3(L::NB), dim3(kPT), args, 0, st);
     });
 }
 
@@ -685,12 +984,12 @@ static int g_rev_ok = -1;
 // The resident reverse keeps five lane vectors in registers: up to 8 elements per lane.
 bool mgs_rev_resident_available(long n) {
     if (n > 8L * kLanes) return false;
-    if (g_rev_ok < 0) g_rev_ok = coop_available((const void*)k_mgs_rev_resident<Lanes<kBigGrid, 1, 8>>) ? 1 : 0;
+    if (g_rev_ok < 0) g_rev_ok = grid_resident((const void*)k_mgs_rev_resident<Lanes<kBigGrid, 1, 8>>) ? 1 : 0;
     return g_rev_ok == 1;
 }
 
-hipError_t launch_mgs_rev_resident(const Work& W, const AdjWork& A, int M, int j, long n, hipStream_t st) {
-    const double* wsrc = W.w;
+hipError_t launch_mgs_rev_resident(const Work& W, const AdjWork& A, int M, int j, long n, hipStream_t st, int hold) {
+    double* wsrc = W.w;
     const double* V = W.V;
     double* Vbar = A.Vbar;
     const double* H = W.H;
@@ -700,10 +999,10 @@ hipError_t launch_mgs_rev_resident(const Work& W, const AdjWork& A, int M, int j
     double* slots = W.gpart;
     unsigned* bar = W.bar;
     void* args[] = {(void*)&wsrc, (void*)&V,  (void*)&Vbar, (void*)&H,    (void*)&Hbar,  (void*)&n,
-                    (void*)&M,    (void*)&j,  (void*)&wbar, (void*)&ints, (void*)&slots, (void*)&bar};
+                    (void*)&M,    (void*)&j,  (void*)&wbar, (void*)&ints, (void*)&slots, (void*)&bar, (void*)&hold};
     return with_shape<8>(n, [&](auto shape) {
         using L = decltype(shape);
-        return launch_grid<L>((const void*)k_mgs_rev_resident<L>, args, st);
+        return hipLaunchKernel((const void*)k_mgs_rev_resident<L>, dim3(L::NB), dim3(kPT), args, 0, st);
     });
 }
 
