@@ -219,7 +219,7 @@ hipError_t step_adjoint(const rok_ctx* c, const rok_tableau* tab, int M, double 
             if (e != hipSuccess) return e;
         }
         double* Fbar = (i == 0) ? A.Fbar0 : A.FB;
-        e = rok::launch_vbar_stage(W, A, Mm, i, h, Fbar, N, i == s - 1, st);
+        e = rok::launch_fbar_stage(W, A, Mm, i, h, Fbar, N, st);
         if (e != hipSuccess) return e;
         if (i > 0) {   // Y_i = y_n + sum_j alpha_ij k_j;  ybar += J(Y_i)^T Fbar, kbar_j += alpha_ij (...)
             const double* arow = tab->alpha + i * ROK_MAX_STAGES;
@@ -232,6 +232,8 @@ hipError_t step_adjoint(const rok_ctx* c, const rok_tableau* tab, int M, double 
         }
     }
     if (M > 0) {
+        e = rok::launch_vbar(W, A, Mm, s, h, N, st);   // every kbar_i is final now
+        if (e != hipSuccess) return e;
         e = rok::launch_abar_to_hbar(W, A, Mm, h * tab->gamma, st);
         if (e != hipSuccess) return e;
         const bool resident = c->mgs_path != ROK_MGS_PER_PASS && rok::mgs_rev_resident_available(N);

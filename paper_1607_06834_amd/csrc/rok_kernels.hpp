@@ -140,9 +140,9 @@ hipError_t launch_scatter(const AdjWork& A, const double* Ybar, double* ybar, co
                           hipStream_t st);
 hipError_t launch_small_rev(const Work& W, const AdjWork& A, int M, int i, const double* gam_row, double h, long n,
                             hipStream_t st);
-// first: initialise Vbar (the first stage reversed) instead of accumulating.
-hipError_t launch_vbar_stage(const Work& W, const AdjWork& A, int M, int i, double h, double* Fbar, long n,
-                             bool first, hipStream_t st);
+hipError_t launch_fbar_stage(const Work& W, const AdjWork& A, int M, int i, double h, double* Fbar, long n,
+                             hipStream_t st);
+hipError_t launch_vbar(const Work& W, const AdjWork& A, int M, int s, double h, long n, hipStream_t st);
 hipError_t launch_abar_to_hbar(const Work& W, const AdjWork& A, int M, double hg, hipStream_t st);
 // resident: one kernel for the column (mgs_rev_resident_available(n)), else per-pass kernels
 hipError_t launch_arnoldi_rev_col(const Work& W, const AdjWork& A, int M, int j, long n, bool resident,
