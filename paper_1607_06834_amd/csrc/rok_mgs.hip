@@ -603,6 +603,10 @@ __global__ __launch_bounds__(kPT) void k_mgs_resident(double* wsrc, const double
     __shared__ ExLds<K> X;
     __shared__ double s_w[LDSW ? E * kPT : 1];
     __shared__ int s_stop, s_phase;
+    // w and v_0 are on their way while the gate answers
+    double x0[E], A[E], B[E];
+    load_lane<L>(wsrc, n, x0);
+    load_lane<L, Fetch<L>::kHint>(V, n, A);
     if (threadIdx.x == 0) {
         if constexpr (L::NB == kBigGrid) X.gang = gate_enter(bar, hold);
         s_stop = ints[1];
@@ -620,14 +624,8 @@ __global__ __launch_bounds__(kPT) void k_mgs_resident(double* wsrc, const double
     // to a lane sum that starts at +0.0 leaves it unchanged.
     LaneVec<E, LDSW> w;
     w.l = s_w;
-    {
-        double x[E];
-        load_lane<L>(wsrc, n, x);
 #pragma unroll
-        for (int i = 0; i < E; ++i) w.set(i, x[i]);
-    }
-    double A[E], B[E];
-    load_lane<L, Fetch<L>::kHint>(V, n, A);
+    for (int i = 0; i < E; ++i) w.set(i, x0[i]);
     __shared__ double s_hcol[kMaxM + 1];
     double h = 0.0;
     int failed = 0;
