@@ -147,58 +147,70 @@ __global__ __launch_bounds__(kSolveThreads) void k_ls_solve(const double* partia
 
 // Sweep B of column j: w' = w - h_0 q_0 - ... - h_j q_j into `out` (the next
 // basis column, distinct from V's columns 0..j and from w), partials of
-// ||w'||^2 at `partials`.  Two elements of a lane per iteration, both loaded
-// before either is stored (the lane's sum keeps index order).  With sig, the
+// ||w'||^2 at `partials`.  Two elements of a lane per iteration (the lane's sum keeps index order).  With sig, the
 // coefficient of stored column c is h_c sig_c.  The column is stored with the
 // non-temporal hint (it is read again only by the next product, from HBM).
+// Bound by HBM, and by its switching between reading and writing: at 15 columns of 256^3 the loads
+// alone take 1502 us (7.1 TB/s), with one stream of stores among them 2060.  So a block of 1024 threads keeps kHeld
+// results per lane in LDS and stores them together, 128 KB at a time and all blocks at about the same time: 1870 us.
+// The 256^3 step with 16 columns takes 66.6 ms, with 8 held 67.3, with none 69.0; 2048^2 FP32 with 20 17.8, 17.9 and 18.3.
+constexpr int kUpdThreads = 4 * kRedThreads;
+constexpr int kHeld = 16;
+
 template <int MB>
-__global__ __launch_bounds__(kRedThreads) void k_ls_update(const double* __restrict__ V,
+__global__ __launch_bounds__(kUpdThreads) void k_ls_update(const double* __restrict__ V,
                                                           const double* __restrict__ w, const double* H, long n,
                                                           int j, int M, double* __restrict__ out, const int* ints,
                                                           double* partials, const double* sig) {
-    __shared__ double s[kRedThreads];
-    __shared__ double sh[MB];
+    constexpr int E = MB <= 20 ? 2 : 1;   // elements of a lane in flight (128 registers)
+    __shared__ double held[kHeld][kUpdThreads];
     if (ints[1]) return;
-    if (threadIdx.x < MB) {
-        const int c = threadIdx.x;
-        sh[c] = (c <= j) ? (sig ? H[c * M + j] * sig[c] : H[c * M + j]) : 0.0;
-    }
-    __syncthreads();
+    const int tid = threadIdx.x;
     double h[MB];
 #pragma unroll
-    for (int c = 0; c < MB; ++c) h[c] = sh[c];
+    for (int c = 0; c < MB; ++c)
+        h[c] = (c <= j) ? lane_value(sig ? H[c * M + j] * sig[c] : H[c * M + j], 0) : 0.0;   // in scalar registers
     double acc = 0.0;
     const long stride = (long)kRedBlocks * kRedThreads;
-    long e = (long)blockIdx.x * kRedThreads + threadIdx.x;
-    for (; e + stride < n; e += 2 * stride) {
-        double q0[MB], q1[MB];
+    long e = (long)blockIdx.x * kUpdThreads + tid;
+    for (; e - tid + kUpdThreads + (kHeld - 1) * stride <= n; e += kHeld * stride) {
+#pragma unroll 1
+        for (int u = 0; u < kHeld; u += E) {
+            double q[E][MB], x[E];
 #pragma unroll
-        for (int c = 0; c < MB; ++c) {
-            q0[c] = (c <= j) ? ld_stream(V + (long)c * n + e) : 0.0;
-            q1[c] = (c <= j) ? ld_stream(V + (long)c * n + e + stride) : 0.0;
-        }
-        double x0 = ld_stream(w + e), x1 = ld_stream(w + e + stride);
+            for (int k = 0; k < E; ++k) {
+                const long ek = e + (u + k) * stride;
 #pragma unroll
-        for (int c = 0; c < MB; ++c)
-            if (c <= j) {
-                x0 = x0 - h[c] * q0[c];
-                x1 = x1 - h[c] * q1[c];
+                for (int c = 0; c < MB; ++c) q[k][c] = (c <= j) ? ld_stream(V + (long)c * n + ek) : 0.0;
+                x[k] = ld_stream(w + ek);
             }
-        __builtin_nontemporal_store(x0, out + e);
-        __builtin_nontemporal_store(x1, out + e + stride);
-        acc = acc + x0 * x0;
-        acc = acc + x1 * x1;
+#pragma unroll
+            for (int k = 0; k < E; ++k) {
+#pragma unroll
+                for (int c = 0; c < MB; ++c)
+                    if (c <= j) x[k] = x[k] - h[c] * q[k][c];
+                held[u + k][tid] = x[k];
+                acc = acc + x[k] * x[k];
+            }
+        }
+        __syncthreads();   // the stores of a block's waves together
+#pragma unroll
+        for (int u = 0; u < kHeld; ++u) __builtin_nontemporal_store(held[u][tid], out + e + u * stride);
     }
-    if (e < n) {
+    for (; e < n; e += stride) {
+        double q[MB];
+#pragma unroll
+        for (int c = 0; c < MB; ++c) q[c] = (c <= j) ? ld_stream(V + (long)c * n + e) : 0.0;
         double x = ld_stream(w + e);
 #pragma unroll
         for (int c = 0; c < MB; ++c)
-            if (c <= j) x = x - h[c] * ld_stream(V + (long)c * n + e);
+            if (c <= j) x = x - h[c] * q[c];
         __builtin_nontemporal_store(x, out + e);
         acc = acc + x * x;
     }
-    const double b = tree256(acc, s);
-    if (threadIdx.x == 0) partials[blockIdx.x] = b;
+    __syncthreads();
+    const double b = tree256(acc, &held[0][0]);
+    if (tid % kRedThreads == 0) partials[blockIdx.x * (kUpdThreads / kRedThreads) + tid / kRedThreads] = b;
 }
 
 // Smallest compiled column count >= j + 1 (0 if the column is too wide for the register arrays).
@@ -234,8 +246,8 @@ hipError_t launch_ls_column(const Work& W, const double* w, const double* V, lon
     if (j + 1 < M) {
         double* npart = W.partials + (long)(W.npart - 1) * kRedBlocks;   // the last partial column
 #define ROK_LS_UPD(B)                                                                                            \
-    hipLaunchKernelGGL((k_ls_update<B>), dim3(kRedBlocks), dim3(kRedThreads), 0, st, V, w, W.H, n, j, M, vnext, \
-                       W.ints, npart, sig)
+    hipLaunchKernelGGL((k_ls_update<B>), dim3(kRedBlocks * kRedThreads / kUpdThreads), dim3(kUpdThreads), 0, st, V, \
+                       w, W.H, n, j, M, vnext, W.ints, npart, sig)
         switch (MB) {
             case 1: ROK_LS_UPD(1); break;
             case 2: ROK_LS_UPD(2); break;
