@@ -450,6 +450,29 @@ struct BRow {
 // a_q k_q (a = row i + 1 of alpha; terms with a_q = 0 skipped, k_i from
 // registers), in the order the residual forms it from y and the k_q
 // (sum in stage order, terms with b_i = 0 skipped).
+// Element e from its column sums a = (V lambda)_e and b = (V phi)_e: returns the value of `k`; *next: that of ynext.
+template <bool FINAL>
+__device__ __forceinline__ double recover_one(double a, double b, double fe, double ye, double h, const double* K, long n, long e, int s,
+                                              const BRow& br, bool with_next, int stage, const BRow& ar, double* next) {
+    const double ke = a + h * (fe - b);
+    if constexpr (FINAL) {
+        double acc = ye;
+        for (int i = 0; i < s - 1; ++i)
+            if (br.b[i] != 0.0) acc = acc + br.b[i] * ld_stream(K + (long)i * n + e);
+        if (br.b[s - 1] != 0.0) acc = acc + br.b[s - 1] * ke;
+        return acc;
+    } else {
+        if (with_next) {
+            double acc = ye;
+            for (int q = 0; q < stage; ++q)
+                if (ar.b[q] != 0.0) acc = acc + ar.b[q] * ld_stream(K + (long)q * n + e);
+            if (ar.b[stage] != 0.0) acc = acc + ar.b[stage] * ke;
+            *next = acc;
+        }
+        return ke;
+    }
+}
+
 template <int MB, bool FINAL>
 __global__ __launch_bounds__(256) void k_recover(const double* __restrict__ V, const double* __restrict__ F, long n,
                                                 const int* ints, const double* lam, const double* phi, double h,
@@ -487,26 +510,74 @@ __global__ __launch_bounds__(256) void k_recover(const double* __restrict__ V, c
                 b = b + vc * phic(c);
             }
         }
-        double ke = a + h * (ld_stream(F + e) - b);
-        if constexpr (FINAL) {
-            double acc = ld_stream(y + e);
-            for (int i = 0; i < s - 1; ++i)
-                if (br.b[i] != 0.0) acc = acc + br.b[i] * ld_stream(K + (long)i * n + e);
-            if (br.b[s - 1] != 0.0) acc = acc + br.b[s - 1] * ke;
-            k[e] = acc;
-        } else {
-            k[e] = ke;
-            if (ynext) {
-                double acc = ld_stream(y + e);
-                for (int q = 0; q < stage; ++q)
-                    if (ar.b[q] != 0.0) acc = acc + ar.b[q] * ld_stream(K + (long)q * n + e);
-                if (ar.b[stage] != 0.0) acc = acc + ar.b[stage] * ke;
-                ynext[e] = acc;
-            }
-        }
+        double next = 0.0;
+        k[e] = recover_one<FINAL>(a, b, ld_stream(F + e), FINAL || ynext ? ld_stream(y + e) : 0.0, h, K, n, e, s, br,
+                                  ynext, stage, ar, &next);
+        if (!FINAL && ynext) ynext[e] = next;
     }
 }
 
+// k_recover for vectors of many elements per lane: bound by HBM, which loses a fifth of its rate to switching between
+// the loads of 19 vectors and two streams of stores.  As in the one-reduce form's update sweep, a block of
+// 1024 threads holds its results in LDS and stores kRecHeld of each stream per lane at a
+// time: 16 columns of 256^3 2674 us, now 2329, the last stage 2893, now 2338; 20 columns of 2048^2 587, now 560, and 629,
+// now 554.
+constexpr int kRecThreads = 1024;
+constexpr int kRecHeld = 8;
+
+template <int MB, bool FINAL>
+__global__ __launch_bounds__(kRecThreads) void k_recover_held(const double* __restrict__ V, const double* __restrict__ F,
+                                                             long n, const int* ints, const double* lam, const double* phi,
+                                                             double h, double* __restrict__ k,
+                                                             const double* __restrict__ y, const double* __restrict__ K,
+                                                             int s, BRow br, const double* sig,
+                                                             double* __restrict__ ynext, int stage, BRow ar) {
+    constexpr int U = FINAL ? 2 * kRecHeld : kRecHeld;
+    __shared__ double held[2 * kRecHeld][kRecThreads];
+    const int m = ints[0], tid = threadIdx.x;
+    double lm[MB], ph[MB];   // uniform: kept in scalar registers
+#pragma unroll
+    for (int c = 0; c < MB; ++c) {
+        lm[c] = lane_value(c < m ? (sig ? lam[c] * sig[c] : lam[c]) : 0.0, 0);
+        ph[c] = lane_value(c < m ? (sig ? phi[c] * sig[c] : phi[c]) : 0.0, 0);
+    }
+    auto one = [&](long e, double* next) {
+        double vc[MB];
+        const double fe = ld_stream(F + e), ye = FINAL || ynext ? ld_stream(y + e) : 0.0;
+#pragma unroll
+        for (int c = 0; c < MB; ++c) vc[c] = c < m ? ld_stream(V + (long)c * n + e) : 0.0;
+        double a = 0.0, b = 0.0;
+#pragma unroll
+        for (int c = 0; c < MB; ++c)
+            if (c < m) {
+                a = a + vc[c] * lm[c];
+                b = b + vc[c] * ph[c];
+            }
+        return recover_one<FINAL>(a, b, fe, ye, h, K, n, e, s, br, ynext, stage, ar, next);
+    };
+    const long stride = (long)gridDim.x * kRecThreads;
+    long e = (long)blockIdx.x * kRecThreads + tid;
+    for (; e - tid + kRecThreads + (U - 1) * stride <= n; e += U * stride) {
+#pragma unroll 1
+        for (int u = 0; u < U; ++u) {
+            double next = 0.0;
+            held[u][tid] = one(e + u * stride, &next);
+            if (!FINAL && ynext) held[U + u][tid] = next;
+        }
+        __syncthreads();   // the stores of a block's waves together
+#pragma unroll
+        for (int u = 0; u < U; ++u) __builtin_nontemporal_store(held[u][tid], k + e + u * stride);
+        if (!FINAL && ynext) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) __builtin_nontemporal_store(held[U + u][tid], ynext + e + u * stride);
+        }
+    }
+    for (; e < n; e += stride) {
+        double next = 0.0;
+        k[e] = one(e, &next);
+        if (!FINAL && ynext) ynext[e] = next;
+    }
+}
 
 // ---------------------------------------------------------------------------
 // Workspace: a 256-byte header (status ints, scalars) at offset 0 for every M
@@ -793,12 +864,24 @@ hipError_t launch_recover(const Work& W, const double* V, const double* F, long 
     const double* lam = W.lam + (long)i * Mm;
     const double* phi = W.phi + (long)i * Mm;
     const unsigned g = grid_for(n, 256);
-#define ROK_REC(MB)                                                                                             \
-    if (fin) hipLaunchKernelGGL((k_recover<MB, true>), dim3(g), dim3(256), 0, st, V, F, n, W.ints, lam, phi, h,  \
-                                k, y, K, s, br, sig, nullptr, 0, ar);                                         \
-    else hipLaunchKernelGGL((k_recover<MB, false>), dim3(g), dim3(256), 0, st, V, F, n, W.ints, lam, phi, h, k,  \
-                            y, K, s, br, sig, ynext, i, ar)
+    // at 4194304 elements a lane holds 16, two bursts, and most of the basis is in the last-level cache, where the
+    // plain form runs at 5.9 TB/s already; the next size of vectors up is out of it
+    const long kHeldFrom = 16L * kRedBlocks * kRedThreads;
+#define ROK_REC_ARGS V, F, n, W.ints, lam, phi, h, k, y, K, s, br, sig
+#define ROK_REC(MB)                                                                                                  \
+    if (MB <= 24 && n > kHeldFrom) {                                                                                 \
+        constexpr int B = MB <= 24 ? MB : 24;                                                                        \
+        if (fin) hipLaunchKernelGGL((k_recover_held<B, true>), dim3(256), dim3(kRecThreads), 0, st, ROK_REC_ARGS,    \
+                                    nullptr, 0, ar);                                                                 \
+        else hipLaunchKernelGGL((k_recover_held<B, false>), dim3(256), dim3(kRecThreads), 0, st, ROK_REC_ARGS,       \
+                                ynext, i, ar);                                                                       \
+    } else if (fin) {                                                                                                \
+        hipLaunchKernelGGL((k_recover<MB, true>), dim3(g), dim3(256), 0, st, ROK_REC_ARGS, nullptr, 0, ar);          \
+    } else {                                                                                                         \
+        hipLaunchKernelGGL((k_recover<MB, false>), dim3(g), dim3(256), 0, st, ROK_REC_ARGS, ynext, i, ar);           \
+    }
     ROK_MB_SWITCH(mbucket(M > 0 ? M : 1), ROK_REC)
+#undef ROK_REC_ARGS
 #undef ROK_REC
     return hipGetLastError();
 }
