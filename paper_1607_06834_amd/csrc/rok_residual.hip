@@ -112,8 +112,15 @@ __device__ constexpr typename Stage<D, TX, TY, TZ, HW, NSV>::Cells kStageCells =
 template <int D, typename S, int MODE>
 constexpr int kTileThreads = (D == 3 && MODE == MODE_TAN && sizeof(S) == 16) ? 768 : kThreads;
 
-template <int D, int RECON, bool NSV, int FLUX, int GEO, typename S, int MODE, typename OUT, int TX, int TY, int TZ>
-__global__ __launch_bounds__((kTileThreads<D, S, MODE>)) void k_residual(Geom G, ResArgs A, int nt0, int nt1) {
+// A 2-D FP64 tile that has a CU to itself (a grid of at most kLoneTiles) is bound by the latency of its chain of steps, not by issue:
+// ten waves take the faces of both directions (272 each in 16 x 16, 264 and 288 in 32 x 8) in one round where
+// four take two rounds per direction.  128 x 64 O-grid step 302 us, now 256; 32 x 32 step 183, 176.  With more
+// tiles than CUs the extra waves only crowd each other: FD product at 512^2 13.6 us with four, 16.2 with ten.
+constexpr int kLoneThreads = 640;
+constexpr long kLoneTiles = 256;
+
+template <int D, int RECON, bool NSV, int FLUX, int GEO, typename S, int MODE, typename OUT, int TX, int TY, int TZ, int NT>
+__global__ __launch_bounds__(NT) void k_residual(Geom G, ResArgs A, int nt0, int nt1) {
     using T = Tile<D, TX, TY, TZ, (RECON == 0 ? 1 : 2)>;
     using R = typename Sc<S>::R;
     constexpr int NV = D + 2;
@@ -123,7 +130,6 @@ __global__ __launch_bounds__((kTileThreads<D, S, MODE>)) void k_residual(Geom G,
     constexpr int OFF_VEL = CONS ? NV : 1;
     constexpr int OFF_P = OFF_VEL + D;
     constexpr int OFF_T = OFF_P + 1;
-    constexpr int NT = kTileThreads<D, S, MODE>;
     constexpr bool MERGED = NT > T::CELLS;
     constexpr int CPT = MERGED ? 1 : T::CELLS / NT;
     static_assert(MERGED || T::CELLS % NT == 0, "tile must be a multiple of the block size");
@@ -152,7 +158,7 @@ __global__ __launch_bounds__((kTileThreads<D, S, MODE>)) void k_residual(Geom G,
         if constexpr (MODE == MODE_TAN) return x.d;
         else return x;
     };
-    __shared__ FB fb[NV][MERGED ? T::NF0 + T::NF1 + T::NF2 : T::NFMAX];
+    __shared__ FB fb[NV][MERGED ? T::NF0 + T::NF1 + (D == 3 ? T::NF2 : 0) : T::NFMAX];
     __shared__ unsigned short s_slot[PACKED ? T::BOX : 1];
     // FP32 form: the tile's reference state (float, and as doubles)
     __shared__ RefState<D, R> s_ref;
@@ -345,7 +351,7 @@ __global__ __launch_bounds__((kTileThreads<D, S, MODE>)) void k_residual(Geom G,
         for (int k = 0; k < CPT; ++k) {
             const int cell = tid + k * NT;
             const int gx = x0 + cell % TX, gy = y0 + (cell / TX) % TY, gz = z0 + cell / (TX * TY);
-            const bool in = gx < n0 && gy < n1 && (D != 3 || gz < n2);
+            const bool in = gx < n0 && gy < n1 && (D != 3 || gz < n2) && (!MERGED || cell < T::CELLS);
             const long gi = in ? ((long)gz * n1 + gy) * n0 + gx : 0;
 #pragma unroll
             for (int m = 0; m < NV; ++m) f0pre[k][m] = in ? A.f0[(long)m * G.ncell + gi] : 0.0;
@@ -670,7 +676,7 @@ __global__ __launch_bounds__((kTileThreads<D, S, MODE>)) void k_residual(Geom G,
     using Z = std::integral_constant<int, 2>;
     if constexpr (MERGED) {
         // waves take 64 faces at a time, of whichever direction
-        constexpr int W0 = (T::NF0 + 63) / 64, W1 = W0 + (T::NF1 + 63) / 64, W2 = W1 + (T::NF2 + 63) / 64;
+        constexpr int W0 = (T::NF0 + 63) / 64, W1 = W0 + (T::NF1 + 63) / 64, W2 = W1 + (D == 3 ? (T::NF2 + 63) / 64 : 0);
         const int lane = tid & 63;
 #pragma unroll 1
         for (int t = __builtin_amdgcn_readfirstlane(tid >> 6); t < W2; t += NT / 64) {
@@ -680,7 +686,7 @@ __global__ __launch_bounds__((kTileThreads<D, S, MODE>)) void k_residual(Geom G,
             } else if (t < W1) {
                 const int f = 64 * (t - W0) + lane;
                 if (f < T::NF1) face(Y(), f, T::NF0);
-            } else {
+            } else if constexpr (D == 3) {
                 const int f = 64 * (t - W1) + lane;
                 if (f < T::NF2) face(Z(), f, T::NF0 + T::NF1);
             }
@@ -689,7 +695,7 @@ __global__ __launch_bounds__((kTileThreads<D, S, MODE>)) void k_residual(Geom G,
         if (tid < T::CELLS) {
             difference(X(), 0);
             difference(Y(), T::NF0);
-            difference(Z(), T::NF0 + T::NF1);
+            if constexpr (D == 3) difference(Z(), T::NF0 + T::NF1);
         }
     } else {
         // one direction after the other through the same columns (plain FP64: two faces
@@ -1172,8 +1178,16 @@ static hipError_t launch_t(const Geom& G, const ResArgs& A, hipStream_t st) {
     int nt2 = (D == 3) ? (G.n[2] + TZ - 1) / TZ : 1;
     long nb = (long)nt0 * nt1 * nt2;
     if (nb <= 0 || nb > 0x7fffffffL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_residual<D, RECON, NSV, FLUX, GEO, S, MODE, OUT, TX, TY, TZ>), dim3((unsigned)nb), dim3(kTileThreads<D, S, MODE>), 0, st,
-                       G, A, nt0, nt1);
+    if constexpr (D == 2 && sizeof(typename Sc<S>::R) == 8) {
+        if (nb <= kLoneTiles) {
+            hipLaunchKernelGGL((k_residual<D, RECON, NSV, FLUX, GEO, S, MODE, OUT, TX, TY, TZ, kLoneThreads>),
+                               dim3((unsigned)nb), dim3(kLoneThreads), 0, st, G, A, nt0, nt1);
+            return hipGetLastError();
+        }
+    }
+    constexpr int NT = kTileThreads<D, S, MODE>;
+    hipLaunchKernelGGL((k_residual<D, RECON, NSV, FLUX, GEO, S, MODE, OUT, TX, TY, TZ, NT>), dim3((unsigned)nb), dim3(NT),
+                       0, st, G, A, nt0, nt1);
     return hipGetLastError();
 }
 
