@@ -112,11 +112,12 @@ __device__ constexpr typename Stage<D, TX, TY, TZ, HW, NSV>::Cells kStageCells =
 template <int D, typename S, int MODE>
 constexpr int kTileThreads = (D == 3 && MODE == MODE_TAN && sizeof(S) == 16) ? 768 : kThreads;
 
-// A 2-D FP64 tile that has a CU to itself (a grid of at most kLoneTiles) is bound by the latency of its chain of steps, not by issue:
-// ten waves take the faces of both directions (272 each in 16 x 16, 264 and 288 in 32 x 8) in one round where
-// four take two rounds per direction.  128 x 64 O-grid step 302 us, now 256; 32 x 32 step 183, 176.  With more
+// A tile that has a CU to itself (a grid of at most kLoneTiles) is bound by the latency of its chain of steps, not by issue:
+// in 2-D (FP64) ten waves take the faces of both directions (272 each in 16 x 16, 264 and 288 in 32 x 8) in one round, in 3-D
+// fifteen those of all three, where four take two rounds per direction.  128 x 64 O-grid step 302 us, now 256; 32 x 32 step 183, 176; 3-D residual at 31 x 28 x 27
+// 11.1, 7.9, FP32 tangent 16.0, 11.0.  With more
 // tiles than CUs the extra waves only crowd each other: FD product at 512^2 13.6 us with four, 16.2 with ten.
-constexpr int kLoneThreads = 640;
+template <int D> constexpr int kLoneThreads = D == 2 ? 640 : 960;
 constexpr long kLoneTiles = 256;
 
 template <int D, int RECON, bool NSV, int FLUX, int GEO, typename S, int MODE, typename OUT, int TX, int TY, int TZ, int NT>
@@ -1178,10 +1179,10 @@ static hipError_t launch_t(const Geom& G, const ResArgs& A, hipStream_t st) {
     int nt2 = (D == 3) ? (G.n[2] + TZ - 1) / TZ : 1;
     long nb = (long)nt0 * nt1 * nt2;
     if (nb <= 0 || nb > 0x7fffffffL) return hipErrorInvalidValue;
-    if constexpr (D == 2 && sizeof(typename Sc<S>::R) == 8) {
+    if constexpr ((D == 2 && sizeof(typename Sc<S>::R) == 8) || (D == 3 && kTileThreads<D, S, MODE> == kThreads)) {
         if (nb <= kLoneTiles) {
-            hipLaunchKernelGGL((k_residual<D, RECON, NSV, FLUX, GEO, S, MODE, OUT, TX, TY, TZ, kLoneThreads>),
-                               dim3((unsigned)nb), dim3(kLoneThreads), 0, st, G, A, nt0, nt1);
+            hipLaunchKernelGGL((k_residual<D, RECON, NSV, FLUX, GEO, S, MODE, OUT, TX, TY, TZ, kLoneThreads<D>>),
+                               dim3((unsigned)nb), dim3(kLoneThreads<D>), 0, st, G, A, nt0, nt1);
             return hipGetLastError();
         }
     }
