@@ -67,7 +67,7 @@ namespace rok {
 
 constexpr int kPT = 1024;                       // threads per block
 constexpr int kLanes = kRedBlocks * kRedThreads;     // canonical lanes (262144)
-constexpr int kBigGrid = kLanes / kPT;               // 256 blocks: the cooperative grid
+constexpr int kBigGrid = kLanes / kPT;               // 256 blocks: the grid that holds every canonical lane
 constexpr int kMidGrid = 8;                          // the plain grid (see above)
 constexpr int kCopies = kExchangeCopies;             // copies of the exchange slots
 constexpr double kBreakdownTolR = 1e-13;
