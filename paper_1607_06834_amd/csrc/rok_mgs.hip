@@ -829,13 +829,18 @@ __global__ __launch_bounds__(kPT) void k_mgs_rev_resident(double* wsrc, const do
     int phase = s_phase;
     double d = 0.0;
     int failed = 0;
-    // canonical sum of the lane sums acc; loads(): the caller's prefetch, issued
-    // by the waves 1-15 when the block's value is out and by wave 0 after its polls
-    auto exchange = [&](double (&acc)[K], bool first, auto loads) {
+    // canonical sum of the lane sums acc; the caller's prefetch: early() by the waves 1-15 before the block's tree,
+    // late() by them when the block's value is out, both by wave 0 after its polls.  (v early and vbar late: gradient at 512^2
+    // 7550 us; the other way round 7583, both late 7693, both early 7682.)
+    auto exchange = [&](double (&acc)[K], bool first, auto early, auto late) {
 #pragma unroll
         for (int k = 0; k < K; ++k) asm volatile("" : "+v"(acc[k]) : : "memory");
-        if constexpr (L::NB == 1) loads();
-        failed = grid_sum<L>(acc, X, slots, phase, bar, first, &d, loads, loads);
+        if (L::NB == 1 || threadIdx.x >= 64) early();
+        if constexpr (L::NB == 1) late();
+        failed = grid_sum<L>(acc, X, slots, phase, bar, first, &d, late, [&] {
+            early();
+            late();
+        });
     };
     if (nrm) {
         load_lane<L>(V + (long)(j + 1) * n, n, A);      // v_{j+1}
@@ -843,7 +848,7 @@ __global__ __launch_bounds__(kPT) void k_mgs_rev_resident(double* wsrc, const do
         double acc[K];
 #pragma unroll
         for (int x = 0; x < E; ++x) acc[x / C] = (x % C ? acc[x / C] : 0.0) + vb[x] * A[x];
-        exchange(acc, true, [&] { load_lane<L>(V + (long)j * n, n, B); });
+        exchange(acc, true, [&] { load_lane<L>(V + (long)j * n, n, B); }, [] {});
         if (failed) goto fail;
         const double rho = s_h[j + 1];
         const double coef = s_hb[j + 1] - d / rho;
@@ -867,10 +872,8 @@ __global__ __launch_bounds__(kPT) void k_mgs_rev_resident(double* wsrc, const do
         double acc[K];
 #pragma unroll
         for (int x = 0; x < E; ++x) acc[x / C] = (x % C ? acc[x / C] : 0.0) + wb[x] * B[x];
-        exchange(acc, !nrm, [&] {
-            load_lane<L>(V + (long)(j > 0 ? j - 1 : 0) * n, n, A);
-            load_lane<L>(Vbar + (long)j * n, n, vb);
-        });
+        exchange(acc, !nrm, [&] { load_lane<L>(V + (long)(j > 0 ? j - 1 : 0) * n, n, A); },
+                 [&] { load_lane<L>(Vbar + (long)j * n, n, vb); });
         if (failed) goto fail;
     }
     {
@@ -892,10 +895,8 @@ __global__ __launch_bounds__(kPT) void k_mgs_rev_resident(double* wsrc, const do
             }
             store_lane<L>(Vbar + (long)i * n, n, vb);
             if (i == 0) return;
-            exchange(acc, false, [&] {
-                load_lane<L>(V + (long)(i > 1 ? i - 2 : 0) * n, n, cur);
-                load_lane<L>(Vbar + (long)(i - 1) * n, n, vb);
-            });
+            exchange(acc, false, [&] { load_lane<L>(V + (long)(i > 1 ? i - 2 : 0) * n, n, cur); },
+                     [&] { load_lane<L>(Vbar + (long)(i - 1) * n, n, vb); });
         };
         int i = j;
         for (;;) {
