@@ -556,8 +556,7 @@ __global__ __launch_bounds__(256) void k_vjp(Geom G, const double* y, const doub
 // Bound by FP64 arithmetic and its latency (the 96 bytes per cell take a tenth of the time).  A face is
 // reversed once (1.19 times with the tile's overhang), where a cell on its own
 // reverses the 2 (first order) or 4 (MUSCL) faces per direction whose stencil
-// holds it; sound speeds and velocities take reciprocals, shared by a state's
-// quotients; the viscous part is a sweep back instead of 4 forward-mode
+// holds it; a state's quotients share a reciprocal; the viscous part is a sweep back instead of 4 forward-mode
 // evaluations of each of 12 faces.  Measured: Navier-Stokes MUSCL, 700 x 450,
 // 312 -> 47.5 us; first-order Euler, 512^2, 22.6 -> 14.9 us, with the
 // second-order adjoint 39.5 -> 32.5 us.
@@ -571,14 +570,13 @@ struct Side {
     T q[4], c, cr, cp;
 };
 
-// c, dc/dr and dc/dp of a state: one reciprocal and a root with its own (dual numbers by the chain rule)
+// c (the residual's own sequence, so that the two sides' speeds compare as they did there), dc/dr and dc/dp of a state
 template <typename T>
 __device__ __forceinline__ void sound_speed(const Geom& G, T r, T p, T& c, T& cr, T& cp) {
-    const T ir = recip(r);
-    T h;   // 1 / (2 c)
-    c = Sc<T>::sqrt_(G.g * (p * ir), h);
-    cr = -0.5 * (c * ir);
-    cp = (G.g * ir) * h;
+    const auto qr = over(r);
+    c = Sc<T>::sqrt_(G.g * p / qr);
+    cr = -0.5 * (c / qr);
+    cp = (Sc<T>::make(G.g) / qr) / over(c + c);
 }
 
 // Adjoint of one side of Rusanov's flux along d: the physical flux with weight
@@ -686,15 +684,16 @@ __global__ __launch_bounds__(256) void k_vjp_tile(Geom G, const double* y, const
             if constexpr (SECOND) U[m] = T{y[m * ncell + c], v[m * ncell + c]};
             else U[m] = y[m * ncell + c];
         }
-        const T ir = recip(U[0]), v0 = U[1] * ir, v1 = U[2] * ir;
-        const T p = G.gm1 * (U[3] - (0.5 * U[0]) * (v0 * v0 + v1 * v1));
-        sq[0][i] = U[0];
-        sq[1][i] = v0;
-        sq[2][i] = v1;
+        // the forward's own rounding: limiters and wave speeds take the branches that the residual took
+        T r, vel[2], p;
+        primitives<2>(G, U, r, vel, p);
+        sq[0][i] = r;
+        sq[1][i] = vel[0];
+        sq[2][i] = vel[1];
         sq[3][i] = p;
         if constexpr (CS) {
             T cc, cr, cp;
-            sound_speed(G, U[0], p, cc, cr, cp);
+            sound_speed(G, r, p, cc, cr, cp);
             sq[4][i] = cc;
             sq[5][i] = cr;
             sq[6][i] = cp;
