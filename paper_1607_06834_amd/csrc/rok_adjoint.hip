@@ -13,11 +13,11 @@
 // (first order: faces c-1/2, c+1/2; MUSCL: the four faces c-3/2 .. c+3/2).
 // Each thread owns one cell and gathers its own contributions, so the result
 // is deterministic without atomics.
-//   2-D Cartesian grids (k_vjp_tile): a tile's face fluxes are reversed once
+//   most 2-D Cartesian grids (k_vjp_tile): a tile's face fluxes are reversed once
 //   each, down to the adjoints of the two reconstructed states, and its cells
 //   gather those from LDS;
-//   3-D and curvilinear grids (k_vjp): each cell reverses the faces whose
-//   stencil holds it.
+//   3-D and curvilinear grids, and 2-D ones where that is the faster (k_vjp):
+//   each cell reverses the faces whose stencil holds it.
 // A face's reverse is one sweep back through Rusanov's flux (the transpose of the tangent of the
 // residual's flux code); Roe's takes forward-mode evaluations.
 // With a dual scalar (y + t v) the same kernels return
@@ -1049,31 +1049,50 @@ static hipError_t launch_vjp_ogrid(const Geom& G, const double* y, const double*
     return launch_vjp_og<RECON, 0, false>(G, y, v, wbar, ybar, ybar2, accumulate, gate, col, st);
 }
 
-template <int D, int RECON, int FLUX, bool NSV, int GEO = 0>
-static hipError_t launch_vjp_f(const Geom& G, const double* y, const double* v, const double* wbar, double* ybar,
+// Whether a 2-D Cartesian product is gathered cell by cell (k_vjp) instead of from the faces of tiles (k_vjp_tile).
+// A tile's arithmetic is that of its 16 x 16 cells however many of them the grid has, and first order a tile saves
+// little: a cell has two faces per direction, which it reverses without the staging.  Measured, tile and cells:
+//   first order, Roe: the dual evaluations are the whole time and a tile's second round of faces holds 16 of 272
+//     (Euler second-order adjoint 318 and 201 us at 700 x 450, 70 and 40 at 100^2; product 82 and 73, 29 and 20);
+//     only the Navier-Stokes product has more to share from 256^2 on (36 and 42 us there, 38 and 31 at 100^2);
+//   first order, Euler, Rusanov, second-order adjoint: 36 and 32 us at 700 x 450, 30 and 28 at 512^2, 12 and 10 at 17^2;
+//   thin grids of more tiles than CUs: first order the lines cross near five eighths of a tile's cells in the grid
+//     (Euler product 20 and 16 us at 30000 x 8, 12 and 11 at 16384 x 12, 13 and 17 at 512^2), with MUSCL near five
+//     sixteenths (Euler product 59 and 46 us at 65536 x 4, 22 and 29 at 20000 x 5; Navier-Stokes 84 and 73, 37 and 44),
+//     Roe's second-order adjoint nine (533 and 460 at 30000 x 8, 264 and 346 at 16384 x 12).
+//     Up to one tile per CU the time is a tile's latency, whatever it holds.
+template <int RECON, int FLUX, bool NSV, bool SECOND>
+static bool vjp_by_cells(long ncell, long tiles) {
+    constexpr int sixteenths = RECON == 0 ? 10 : (FLUX == 1 && SECOND ? 9 : 5);
+    const bool thin = tiles > 256 && 16 * ncell < sixteenths * 256 * tiles;
+    if (RECON == 0 && FLUX == 1) return thin || SECOND || !NSV || ncell < (1L << 16);
+    return thin || (RECON == 0 && !NSV && SECOND);
+}
+
+template <int D, int RECON, int FLUX, bool NSV, int GEO, bool SECOND>
+static hipError_t launch_vjp_s(const Geom& G, const double* y, const double* v, const double* wbar, double* ybar,
                                double* ybar2, int accumulate, const int* gate, int col, hipStream_t st) {
     if constexpr (D == 2 && GEO == 0) {
         const int nt0 = (G.n[0] + kVT - 1) / kVT, nt1 = (G.n[1] + kVT - 1) / kVT;
         const long nb = (long)nt0 * nt1;
-        if (nb > 0x7fffffffL) return hipErrorInvalidValue;
-        if (v)
-            hipLaunchKernelGGL((k_vjp_tile<RECON, true, FLUX, NSV>), dim3((unsigned)nb), dim3(256), 0, st, G, y, v, wbar,
+        if (nb <= 0x7fffffffL && !vjp_by_cells<RECON, FLUX, NSV, SECOND>(G.ncell, nb)) {
+            hipLaunchKernelGGL((k_vjp_tile<RECON, SECOND, FLUX, NSV>), dim3((unsigned)nb), dim3(256), 0, st, G, y, v, wbar,
                                ybar, ybar2, accumulate, gate, col, nt0);
-        else
-            hipLaunchKernelGGL((k_vjp_tile<RECON, false, FLUX, NSV>), dim3((unsigned)nb), dim3(256), 0, st, G, y, v,
-                               wbar, ybar, ybar2, accumulate, gate, col, nt0);
-        return hipGetLastError();
-    } else {
-        long g = (G.ncell + 255) / 256;
-        if (g > 16384) g = 16384;
-        if (v)
-            hipLaunchKernelGGL((k_vjp<D, RECON, true, FLUX, NSV, GEO>), dim3((unsigned)g), dim3(256), 0, st, G, y, v, wbar,
-                               ybar, ybar2, accumulate, gate, col);
-        else
-            hipLaunchKernelGGL((k_vjp<D, RECON, false, FLUX, NSV, GEO>), dim3((unsigned)g), dim3(256), 0, st, G, y, v, wbar,
-                               ybar, ybar2, accumulate, gate, col);
-        return hipGetLastError();
+            return hipGetLastError();
+        }
     }
+    long g = (G.ncell + 255) / 256;
+    if (g > 16384) g = 16384;
+    hipLaunchKernelGGL((k_vjp<D, RECON, SECOND, FLUX, NSV, GEO>), dim3((unsigned)g), dim3(256), 0, st, G, y, v, wbar, ybar,
+                       ybar2, accumulate, gate, col);
+    return hipGetLastError();
+}
+
+template <int D, int RECON, int FLUX, bool NSV, int GEO = 0>
+static hipError_t launch_vjp_f(const Geom& G, const double* y, const double* v, const double* wbar, double* ybar,
+                               double* ybar2, int accumulate, const int* gate, int col, hipStream_t st) {
+    if (v) return launch_vjp_s<D, RECON, FLUX, NSV, GEO, true>(G, y, v, wbar, ybar, ybar2, accumulate, gate, col, st);
+    return launch_vjp_s<D, RECON, FLUX, NSV, GEO, false>(G, y, v, wbar, ybar, ybar2, accumulate, gate, col, st);
 }
 
 template <int D, int RECON, bool NSV>
