@@ -152,11 +152,11 @@ __device__ __forceinline__ void prim_adjoint(const Geom& G, T r, const T* vel, T
     for (int e = 1; e < D; ++e) ke = ke + vel[e] * vel[e];
     const T tb = -(G.gm1 * pb);
     const T keb = half * r * tb;
-    const T ir = recip(r);
+    const auto qr = over(r);
     rb = rb + half * ke * tb;
 #pragma unroll
     for (int e = 0; e < D; ++e) {
-        const T m = (vb[e] + (vel[e] + vel[e]) * keb) * ir;
+        const T m = (vb[e] + (vel[e] + vel[e]) * keb) / qr;
         Ub[1 + e] = m;
         rb = rb - m * vel[e];
     }
@@ -585,10 +585,11 @@ __device__ __forceinline__ void sound_speed(const Geom& G, T r, T p, T& c, T& cr
 // m = r u, E = p / (gamma - 1) + r |u|^2 / 2.
 template <typename T>
 __device__ __forceinline__ void rusanov_side_vjp(const Geom& G, int d, const Side<T>& s, const T* Fb, T* ub, T ab, T* qb) {
-    const double half = 0.5, igm1 = 1.0 / G.gm1;
+    const double half = 0.5;
+    const auto qg = over(G.gm1, G.gm1_inv);
     const T r = s.q[0], p = s.q[3], un = s.q[1 + d];
     const T ke = s.q[1] * s.q[1] + s.q[2] * s.q[2];
-    const T E = p * igm1 + (half * r) * ke;
+    const T E = p / qg + (half * r) * ke;
     T unb = Sc<T>::make(0.0);
     ub[1 + d] = ub[1 + d] + half * Fb[0];
 #pragma unroll
@@ -604,7 +605,7 @@ __device__ __forceinline__ void rusanov_side_vjp(const Geom& G, int d, const Sid
     qb[0] = ub[0] + ub[1] * s.q[1] + ub[2] * s.q[2] + half * ke * ub[3] + ab * s.cr;
     qb[1] = ub[1] * r + (s.q[1] + s.q[1]) * keb;
     qb[2] = ub[2] * r + (s.q[2] + s.q[2]) * keb;
-    qb[3] = half * Fb[1 + d] + fe * un + ub[3] * igm1 + ab * s.cp;
+    qb[3] = half * Fb[1 + d] + fe * un + ub[3] / qg + ab * s.cp;
     qb[1 + d] = qb[1 + d] + unb;
 }
 

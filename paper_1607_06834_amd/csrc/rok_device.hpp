@@ -165,21 +165,12 @@ template <typename T> struct Quot<Dual<T>> {
     Quot<T> r;
 };
 template <typename T> __device__ __forceinline__ Quot<Dual<T>> over(Dual<T> b) { return {b, over(b.v)}; }
-// x / b to about an ulp
-__device__ __forceinline__ double times(double x, Quot<double> r) { return x * r.y; }
-__device__ __forceinline__ float times(float x, Quot<float> r) { return x * r.y; }
 template <typename T> __device__ __forceinline__ Dual<T> operator/(Dual<T> a, Quot<Dual<T>> q) {
     const T v = a.v / q.r;
     return {v, (a.d - v * q.b.d) / q.r};
 }
-template <typename T> __device__ __forceinline__ Dual<T> times(Dual<T> x, Quot<Dual<T>> q) {
-    const T v = times(x.v, q.r);
-    return {v, times(x.d - v * q.b.d, q.r)};
-}
 template <typename T> __device__ __forceinline__ Dual<T> operator/(Dual<T> a, Dual<T> b) { return a / over(b); }
 // a constant divisor (any nesting depth)
-template <typename T, typename R, typename = typename std::enable_if<std::is_floating_point<R>::value>::type>
-__device__ __forceinline__ Dual<T> times(Dual<T> x, Quot<R> r) { return {times(x.v, r), times(x.d, r)}; }
 template <typename T, typename R, typename = typename std::enable_if<std::is_floating_point<R>::value>::type>
 __device__ __forceinline__ Dual<T> operator/(Dual<T> a, Quot<R> r) { return {a.v / r, a.d / r}; }
 // products and quotients with a plain floating-point constant (any nesting depth)
@@ -239,10 +230,10 @@ template <typename T> struct Sc<Dual<T>> {
     template <typename U> static __device__ __forceinline__ Dual<U> root_tangent(Dual<U> d, Dual<U> s, Dual<U>) { return d / over(s + s); }
 };
 
-// 1 / b to about an ulp (one reciprocal; the dual number's tangent by the chain rule)
-__device__ __forceinline__ double recip(double b) { return over(b).y; }
+// 1 / b, correctly rounded (the dual number's tangent by the chain rule)
+__device__ __forceinline__ double recip(double b) { return 1.0 / over(b); }
 __device__ __forceinline__ Dual<double> recip(Dual<double> b) {
-    const double y = over(b.v).y;
+    const double y = 1.0 / over(b.v);
     return {y, -(b.d * y) * y};
 }
 

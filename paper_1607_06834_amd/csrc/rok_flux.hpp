@@ -271,9 +271,8 @@ __device__ __forceinline__ void prim_rev(const Geom& G, const T* U, T rb, const 
     // vel_e = U[1+e] / r
 #pragma unroll
     for (int e = 0; e < D; ++e) {
-        const T m = times(vb[e], qr);
-        Ub[1 + e] = Ub[1 + e] + m;
-        rb = rb - m * vel[e];
+        Ub[1 + e] = Ub[1 + e] + vb[e] / qr;
+        rb = rb - vb[e] * vel[e] / qr;
     }
     Ub[0] = Ub[0] + rb;
 }
@@ -293,7 +292,7 @@ __device__ __forceinline__ void cons_rev(const Geom& G, T r, const T* vel, const
         rb = rb + Ub[1 + e] * vel[e];
         vb[e] = vb[e] + Ub[1 + e] * r + (vel[e] + vel[e]) * keb;
     }
-    pb = pb + times(Ub[D + 1], over((R)G.gm1, G.gm1_inv));
+    pb = pb + Ub[D + 1] / over((R)G.gm1, G.gm1_inv);
 }
 
 // One side of the reverse of rusanov(): the Euler flux of that side carries
@@ -320,9 +319,10 @@ __device__ __forceinline__ void rusanov_side_rev(const Geom& G, int d, const T* 
     unb = unb + fe * (U[D + 1] + p);
     if (taken) {
         unb = (Sc<T>::val(un) >= 0) ? unb + ab : unb - ab;
-        const T xb = times(ab / over(c + c), over(r));
-        pb = pb + g * xb;
-        rb = rb - xb * x;
+        const T xb = ab / over(c + c);
+        const auto qr = over(r);
+        pb = pb + g * xb / qr;
+        rb = rb - xb * x / qr;
     }
     vb[d] = vb[d] + unb;
 }
