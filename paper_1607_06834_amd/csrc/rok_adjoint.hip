@@ -580,11 +580,13 @@ __device__ __forceinline__ void sound_speed(const Geom& G, T r, T p, T& c, T& cr
 }
 
 // Adjoint of one side of Rusanov's flux along d: the physical flux with weight
-// 1/2, the jump term's state (ub = +-ha Fbar, its adjoint in conserved variables), and the wave speed |u_d| + c
-// where this side's is the maximum (ab, else zero).  Conserved in terms of primitive variables:
+// 1/2, the jump term's state (ub = +-ha Fbar, its adjoint in conserved variables), and, where this side's wave
+// speed |u_d| + c is the maximum (taken), its adjoint ab (c's derivatives are not finite where p <= 0, and do not
+// enter from the other side).  Conserved in terms of primitive variables:
 // m = r u, E = p / (gamma - 1) + r |u|^2 / 2.
 template <typename T>
-__device__ __forceinline__ void rusanov_side_vjp(const Geom& G, int d, const Side<T>& s, const T* Fb, T* ub, T ab, T* qb) {
+__device__ __forceinline__ void rusanov_side_vjp(const Geom& G, int d, const Side<T>& s, const T* Fb, T* ub, bool taken, T ab,
+                                                 T* qb) {
     const double half = 0.5;
     const auto qg = over(G.gm1, G.gm1_inv);
     const T r = s.q[0], p = s.q[3], un = s.q[1 + d];
@@ -600,12 +602,13 @@ __device__ __forceinline__ void rusanov_side_vjp(const Geom& G, int d, const Sid
     }
     const T fe = half * Fb[3];
     ub[3] = ub[3] + fe * un;
-    unb = unb + fe * (E + p) + ((Sc<T>::val(un) >= 0) ? ab : -ab);
+    const T none = Sc<T>::make(0.0);
+    unb = unb + fe * (E + p) + (taken ? ((Sc<T>::val(un) >= 0) ? ab : -ab) : none);
     const T keb = half * r * ub[3];
-    qb[0] = ub[0] + ub[1] * s.q[1] + ub[2] * s.q[2] + half * ke * ub[3] + ab * s.cr;
+    qb[0] = ub[0] + ub[1] * s.q[1] + ub[2] * s.q[2] + half * ke * ub[3] + (taken ? ab * s.cr : none);
     qb[1] = ub[1] * r + (s.q[1] + s.q[1]) * keb;
     qb[2] = ub[2] * r + (s.q[2] + s.q[2]) * keb;
-    qb[3] = half * Fb[1 + d] + fe * un + ub[3] / qg + ab * s.cp;
+    qb[3] = half * Fb[1 + d] + fe * un + ub[3] / qg + (taken ? ab * s.cp : none);
     qb[1 + d] = qb[1 + d] + unb;
 }
 
@@ -630,11 +633,10 @@ __device__ __forceinline__ void face_states_vjp(const Geom& G, int d, const Side
             ur[m] = -ul[m];
         }
         ab = half * ab;
-        const T none = Sc<T>::make(0.0);
-        rusanov_side_vjp<T>(G, d, L, Fb, ul, left ? ab : none, qb);
+        rusanov_side_vjp<T>(G, d, L, Fb, ul, left, ab, qb);
 #pragma unroll
         for (int k = 0; k < NV; ++k) store(0, k, qb[k]);
-        rusanov_side_vjp<T>(G, d, R, Fb, ur, left ? none : ab, qb);
+        rusanov_side_vjp<T>(G, d, R, Fb, ur, !left, ab, qb);
 #pragma unroll
         for (int k = 0; k < NV; ++k) store(1, k, qb[k]);
     } else {
