@@ -865,11 +865,14 @@ hipError_t launch_recover(const Work& W, const double* V, const double* F, long 
     const double* phi = W.phi + (long)i * Mm;
     const unsigned g = grid_for(n, 256);
     // at 4194304 elements a lane holds 16, two bursts, and most of the basis is in the last-level cache, where the
-    // plain form runs at 5.9 TB/s already; the next size of vectors up is out of it
+    // plain form runs at 5.9 TB/s already; the next size of vectors up is out of it.  With a basis of few columns the
+    // held form's 16 waves per CU have too few loads in flight: steps at 1300^2 with 0, 1, 2, 4, 8 and 10 columns take
+    // 313, 536, 670, 1042, 2058 and 2841 us held, 273, 490, 642, 1016, 2032 and 2945 plain; at 2048^2 the last four 1611,
+    // 2546, 4978 and 6875 against 1582, 2537, 5112 and 7215
     const long kHeldFrom = 16L * kRedBlocks * kRedThreads;
 #define ROK_REC_ARGS V, F, n, W.ints, lam, phi, h, k, y, K, s, br, sig
 #define ROK_REC(MB)                                                                                                  \
-    if (MB <= 24 && n > kHeldFrom) {                                                                                 \
+    if (MB <= 24 && M > 4 && n > kHeldFrom) {                                                                                 \
         constexpr int B = MB <= 24 ? MB : 24;                                                                        \
         if (fin) hipLaunchKernelGGL((k_recover_held<B, true>), dim3(256), dim3(kRecThreads), 0, st, ROK_REC_ARGS,    \
                                     nullptr, 0, ar);                                                                 \
