@@ -47,11 +47,12 @@
 //   n <= 8192            one block, no exchange: up to 8 elements per thread
 //   n <= 32768           eight blocks, up to 4 elements per thread
 //   n <= 4194304         256 blocks, up to 16 elements per thread
-// An exchange needs all blocks of its grid running.  Eight blocks always get there: a device
-// runs at most one kernel per hardware queue at a time (streams on one queue
-// are serialised; 4 queues by default, 32 at most), so at most 32 x 8 = 256
-// blocks wait in exchanges, one per CU, and every other kernel drains.  256
-// blocks fill the chip, and settle first who takes part (Gang below).  Launched
+// An exchange needs all blocks of its grid running.  Eight blocks get there: one process
+// has at most one kernel per hardware queue on the device at a time (streams on one queue
+// are serialised; 4 queues by default, 32 at most), so at most 32 x 8 = 256 of its
+// blocks wait in exchanges of eight, one per CU, and every other kernel drains.  (Several processes on one device could exceed that; the wait is
+// bounded and sets ROK_FLAG_BARRIER.)  256
+// blocks fill the chip, and settle first who takes part (rok_gate.hpp).  Launched
 // cooperatively instead, which drains the stream around the kernel, a column cost 12 to 15 us more:
 // 611 x 389 step 909 us, now 710; 1024^2 step 2867, 2632; gradient at 512^2 9892, 8166;
 // adaptive 512^2 5649, 4552; 24 columns at 64^3 2386, 2072.
@@ -61,6 +62,7 @@
 // in reverse order, with the forward iterate and its adjoint resident.
 #include "rok.h"
 #include "rok_device.hpp"
+#include "rok_gate.hpp"
 #include "rok_kernels.hpp"
 
 namespace rok {
@@ -129,66 +131,32 @@ __device__ __forceinline__ double wave_tree(double (&v)[K]) {
     return r;
 }
 
-// The gang of a launch of 256 blocks.  Its blocks wait for each other, and a plain launch does not promise
-// that all of them get onto the chip together: another stream's blocks may hold CUs, in the worst case while they
-// wait themselves.  So who takes part is settled by one word, the gate: every block adds 1 to its
-// lower half when it starts (a launch adds 256 in all, so the count says which launch it is in and
-// how many of its blocks have started), and a block that has waited long with no one coming (kGateIdle) may close the gate by
-// a compare-and-swap that writes the launch's mark and the count into the upper half, unless the
-// count is complete.  A block that finds the gate closed when it starts leaves.  With all 256 in, nobody
-// can close any more, and every block is running, so the waits end.  Closed, the blocks that are in do
-// the whole column by themselves (gang_column, gang_reverse), dealing the 256 blocks' work out among them: the same bits,
-// slower.  Nothing of this costs a launch but the one atomic, under the first loads.
-struct Gang {
-    unsigned base;   // the count before this launch
-    unsigned mark;   // this launch's mark: upper half of a closed gate without the count
-    int rank;        // this block's order of arrival, or -1: came to a closed gate
-    int size;        // blocks that take part (once closed)
-};
+// The gang of a launch of 256 blocks: who takes part is settled by the gate (rok_gate.hpp).  The blocks of a closed
+// gang do the whole column by themselves (gang_column, gang_reverse), dealing the 256 blocks' work out among them: the same bits,
+// slower.  Nothing of this costs a launch but one atomic, under the first loads.
+static_assert(kBigGrid == kGateBlocks, "the gate counts these");
 constexpr int kGateSpins = 64;    // polls between two looks at the gate (about 50 us)
-constexpr int kGateIdle = 20;     // looks without an arrival before a block closes (about 1 ms)
 constexpr int kGateHold = 1 << 16;
 
-__device__ __forceinline__ unsigned long long* gate_word(unsigned* bar) { return (unsigned long long*)(bar + kBarGate); }
-
-// The launch's state in the gate's value g: 0 open, 256 complete, else the size of the closed gang.
-__device__ __forceinline__ int gate_state(const Gang& q, unsigned long long g) {
-    const unsigned hi = (unsigned)(g >> 32);
-    if ((hi & ~0xffu) == q.mark) return (int)(hi & 0xff);
-    return (unsigned)g - q.base == (unsigned)kBigGrid ? kBigGrid : 0;
-}
-
-// Closes the gate unless the count is complete; returns the state (each failed exchange is an arrival or a closure).
-__device__ __forceinline__ int gate_close(const Gang& q, unsigned* bar) {
-    unsigned long long g = __hip_atomic_load(gate_word(bar), __ATOMIC_RELAXED, AGENT);
-    for (;;) {
-        const int s = gate_state(q, g);
-        if (s) return s;
-        const unsigned n = (unsigned)g - q.base;
-        const unsigned long long want = (g & 0xffffffffull) | ((unsigned long long)(q.mark | n) << 32);
-        if (__hip_atomic_compare_exchange_strong(gate_word(bar), &g, want, __ATOMIC_RELAXED, __ATOMIC_RELAXED, AGENT))
-            return (int)n;
+struct DeviceAtomics {
+    static __device__ __forceinline__ GateWord load(const GateWord* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, AGENT); }
+    static __device__ __forceinline__ GateWord add(GateWord* p, GateWord x) { return __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, AGENT); }
+    static __device__ __forceinline__ bool cas(GateWord* p, GateWord* e, GateWord d) {
+        return __hip_atomic_compare_exchange_strong(p, e, d, __ATOMIC_RELAXED, __ATOMIC_RELAXED, AGENT);
     }
-}
+};
 
-// This block enters (one thread).  hold > 0 (tests): the gang closes with that many blocks, the others coming late.
-__device__ __forceinline__ Gang gate_enter(unsigned* bar, int hold) {
-    auto mark_of = [](unsigned count) { return ((count / kBigGrid + 1) & 0xffffffu) << 8; };
+__device__ __forceinline__ GateWord* gate_word(unsigned* bar) { return (GateWord*)(bar + kBarGate); }
+
+// This block enters (one thread).  hold > 0 (tests): the blocks from `hold` on come late, after the others have closed the gate.
+__device__ __forceinline__ Gang enter(unsigned* bar, int hold) {
     if (hold > 0 && (int)blockIdx.x >= hold) {
         for (int i = 0; i < kGateHold; ++i) {
-            const unsigned long long g = __hip_atomic_load(gate_word(bar), __ATOMIC_RELAXED, AGENT);
-            if (((unsigned)(g >> 32) & ~0xffu) == mark_of((unsigned)g)) break;
+            const GateWord g = DeviceAtomics::load(gate_word(bar));
+            if (gate_closed(gate_base(g), g)) break;
         }
     }
-    const unsigned long long g = __hip_atomic_fetch_add(gate_word(bar), 1ull, __ATOMIC_RELAXED, AGENT);
-    const unsigned count = (unsigned)g;
-    Gang q;
-    q.base = count - count % kBigGrid;
-    q.mark = mark_of(count);
-    q.rank = ((unsigned)(g >> 32) & ~0xffu) == q.mark ? -1 : (int)(count - q.base);
-    q.size = 0;
-    if (hold > 0 && q.rank == hold - 1) gate_close(q, bar);
-    return q;
+    return gate_enter<DeviceAtomics>(gate_word(bar));
 }
 
 // LDS of one exchange: the block trees' cross-wave levels (SK values per thread), the group sums, the result
@@ -313,8 +281,8 @@ __device__ __forceinline__ int grid_sum(double (&acc)[L::K], ExLds<L::K>& X, dou
             constexpr int Q = (NB + 63) / 64;
             unsigned long long u[Q];
             long spins = 0;
-            int err = 0, idle = 0;
-            unsigned seen = 0;
+            int err = 0;
+            Waiting wait;
             for (;;) {
                 bool miss = false;
 #pragma unroll
@@ -332,15 +300,12 @@ __device__ __forceinline__ int grid_sum(double (&acc)[L::K], ExLds<L::K>& X, dou
                     break;
                 }
                 if (NB == kBigGrid && first && spins % kGateSpins == 0) {
-                    // (a complete gate stays complete: then only the slots are waited for)
-                    const unsigned long long g = __hip_atomic_load(gate_word(bar), __ATOMIC_RELAXED, AGENT);
-                    int s = gate_state(X.gang, g);
-                    if (s == 0) {
-                        idle = (unsigned)g == seen ? idle + 1 : 0;
-                        seen = (unsigned)g;
-                        if (idle >= kGateIdle) s = gate_close(X.gang, bar);   // (every lane: the first one closes)
+                    int s = 0;
+                    if constexpr (NB == kBigGrid) {
+                        // (a complete gate stays complete: then only the slots are waited for)
+                        if (tid == 0) s = gate_look<DeviceAtomics>(wait, X.gang, gate_word(bar));
+                        s = __builtin_amdgcn_readfirstlane(s);
                     }
-                    s = __builtin_amdgcn_readfirstlane(s);
                     if (s > 0 && s < kBigGrid) {
                         if (tid == 0) X.gang.size = s;
                         err = kExClosed;
@@ -608,7 +573,7 @@ __global__ __launch_bounds__(kPT) void k_mgs_resident(double* wsrc, const double
     load_lane<L>(wsrc, n, x0);
     load_lane<L, Fetch<L>::kHint>(V, n, A);
     if (threadIdx.x == 0) {
-        if constexpr (L::NB == kBigGrid) X.gang = gate_enter(bar, hold);
+        if constexpr (L::NB == kBigGrid) X.gang = enter(bar, hold);
         s_stop = ints[1];
         s_phase = L::NB > 1 ? (int)bar[kBarPhase] : 0;
     }
@@ -812,7 +777,7 @@ __global__ __launch_bounds__(kPT) void k_mgs_rev_resident(double* wsrc, const do
     __shared__ int s_m, s_bad, s_phase;
     __shared__ double s_h[kMaxM + 1], s_hb[kMaxM + 1];   // column j of H and Hbar
     if (threadIdx.x == 0) {
-        if constexpr (L::NB == kBigGrid) X.gang = gate_enter(bar, hold);
+        if constexpr (L::NB == kBigGrid) X.gang = enter(bar, hold);
         s_m = ints[0];
         s_bad = (ints[2] & ROK_FLAG_BARRIER) != 0;
         s_phase = L::NB > 1 ? (int)bar[kBarPhase] : 0;
