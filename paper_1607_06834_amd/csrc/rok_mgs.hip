@@ -50,7 +50,8 @@
 // An exchange needs all blocks of its grid running.  Eight blocks get there: one process
 // has at most one kernel per hardware queue on the device at a time (streams on one queue
 // are serialised; 4 queues by default, 32 at most), so at most 32 x 8 = 256 of its
-// blocks wait in exchanges of eight, one per CU, and every other kernel drains.  (Several processes on one device could exceed that; the wait is
+// blocks wait in exchanges of eight, one per CU, every other kernel drains, and a gang of 256 that holds their place
+// closes when they are stuck.  (Several processes on one device could exceed that; the wait is
 // bounded and sets ROK_FLAG_BARRIER.)  256
 // blocks fill the chip, and settle first who takes part (rok_gate.hpp).  Launched
 // cooperatively instead, which drains the stream around the kernel, a column cost 12 to 15 us more:
@@ -140,21 +141,30 @@ constexpr int kGateHold = 1 << 16;
 
 struct DeviceAtomics {
     static __device__ __forceinline__ GateWord load(const GateWord* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, AGENT); }
+    static __device__ __forceinline__ unsigned load_first(const unsigned* p) { return __hip_atomic_load(p, __ATOMIC_ACQUIRE, AGENT); }
     static __device__ __forceinline__ GateWord add(GateWord* p, GateWord x) { return __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, AGENT); }
+    static __device__ __forceinline__ unsigned add(unsigned* p, unsigned x) { return __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, AGENT); }
     static __device__ __forceinline__ bool cas(GateWord* p, GateWord* e, GateWord d) {
         return __hip_atomic_compare_exchange_strong(p, e, d, __ATOMIC_RELAXED, __ATOMIC_RELAXED, AGENT);
     }
 };
 
+// blocks of all launches on this device that are stuck in their first exchange (Waiting)
+static __device__ unsigned g_waiting;
+
 __device__ __forceinline__ GateWord* gate_word(unsigned* bar) { return (GateWord*)(bar + kBarGate); }
 
-// This block enters (one thread).  hold > 0 (tests): the blocks from `hold` on come late, after the others have closed the gate.
+// This block enters (one thread).  hold > 0 (tests): the blocks from `hold` on come late, counted as stuck meanwhile.
 __device__ __forceinline__ Gang enter(unsigned* bar, int hold) {
     if (hold > 0 && (int)blockIdx.x >= hold) {
+        Waiting w;
+        w.idle = kGateIdle;
+        wait_count<DeviceAtomics>(w, &g_waiting);
         for (int i = 0; i < kGateHold; ++i) {
             const GateWord g = DeviceAtomics::load(gate_word(bar));
             if (gate_closed(gate_base(g), g)) break;
         }
+        wait_end<DeviceAtomics>(w, &g_waiting);
     }
     return gate_enter<DeviceAtomics>(gate_word(bar));
 }
@@ -299,12 +309,15 @@ __device__ __forceinline__ int grid_sum(double (&acc)[L::K], ExLds<L::K>& X, dou
                     err = kExFailed;
                     break;
                 }
-                if (NB == kBigGrid && first && spins % kGateSpins == 0) {
+                if (first && spins % kGateSpins == 0) {
                     int s = 0;
                     if constexpr (NB == kBigGrid) {
                         // (a complete gate stays complete: then only the slots are waited for)
-                        if (tid == 0) s = gate_look<DeviceAtomics>(wait, X.gang, gate_word(bar));
+                        if (tid == 0) s = gate_look<DeviceAtomics>(wait, X.gang, gate_word(bar), &g_waiting);
                         s = __builtin_amdgcn_readfirstlane(s);
+                    } else if (tid == 0) {
+                        ++wait.idle;
+                        wait_count<DeviceAtomics>(wait, &g_waiting);
                     }
                     if (s > 0 && s < kBigGrid) {
                         if (tid == 0) X.gang.size = s;
@@ -313,6 +326,7 @@ __device__ __forceinline__ int grid_sum(double (&acc)[L::K], ExLds<L::K>& X, dou
                     }
                 }
             }
+            if (tid == 0) wait_end<DeviceAtomics>(wait, &g_waiting);
             after();
             if constexpr (Q == 4) {
                 v = final_value(u);

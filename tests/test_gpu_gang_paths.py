@@ -70,6 +70,26 @@ def test_held_blocks_close_the_gang(dev, n, hold):
     assert torch.equal(V, V2) and torch.equal(H, H2) and not status & BARRIER
 
 
+@pytest.mark.parametrize("n", [(129, 128), (1000, 1000)])
+def test_waits_for_running_kernels(dev, n):
+    """A product of 64-bit matrices on another stream holds the CUs for several milliseconds; nothing else waits, so
+    the columns wait for it (20 ms at most) and run complete."""
+    say("gang behind a running kernel", n)
+    R = problem(n)[0]
+    V, H, _, _ = columns(R, dev)
+    a = torch.rand(4096, 8192, dtype=torch.float64, device=dev)
+    side, c = torch.cuda.Stream(), torch.empty(4096, 4096, dtype=torch.float64, device=dev)
+    torch.mm(a, a.t(), out=c)   # (workspaces and kernels are there before the streams run together)
+
+    def busy():
+        with torch.cuda.stream(side):
+            torch.mm(a, a.t(), out=c)
+
+    V2, H2, changed, status = columns(R, dev, before=busy)
+    assert changed == [False] * M
+    assert torch.equal(V, V2) and torch.equal(H, H2) and not status & BARRIER
+
+
 # one block, eight blocks and 256 blocks a column, alone and against each other
 @pytest.mark.parametrize("sizes", [((40, 40), (40, 40)), ((64, 100), (64, 100)), ((129, 128), (129, 128)),
                                    ((64, 100), (300, 300)), ((701, 701), (40, 40)), ((1000, 1000), (64, 100)),
