@@ -26,16 +26,18 @@ template <typename S> __device__ __forceinline__ S minmod(S a, S b) {
 // base - mm(a, b) / 2: the branch that limits the slope to zero takes the factor 0 instead of
 // 1/2, one select on a constant's upper word instead of two on the slope (the same
 // values for finite slopes; a cell between two infinite ones, whose faces are not finite
-// anyway, gets NaN).
-template <typename T> __device__ __forceinline__ T axpy(T f, T x, T y) { return mad(f, x, y); }
-template <typename R, typename T> __device__ __forceinline__ Dual<T> axpy(R f, Dual<T> x, Dual<T> y) {
-    return {axpy(f, x.v, y.v), axpy(f, x.d, y.d)};
+// anyway, gets NaN).  A tangent that a limited slope drops is dropped whatever it holds.
+template <typename R> __device__ __forceinline__ R limited(R f, R, bool, R slope, R base) { return mad(f, slope, base); }
+template <typename R, typename T>
+__device__ __forceinline__ Dual<T> limited(R f, R half, bool flat, Dual<T> slope, Dual<T> base) {
+    const T d = flat ? Sc<T>::make(0.0) : slope.d;
+    return {limited(f, half, flat, slope.v, base.v), limited(half, half, false, d, base.d)};
 }
 template <typename S> __device__ __forceinline__ S muscl(S base, S a, S b, typename Sc<S>::R half) {
     using R = typename Sc<S>::R;
     const R x = Sc<S>::val(a), y = Sc<S>::val(b);
-    const R f = (x * y <= (R)0) ? (R)0 : half;
-    return axpy(f, (sabs(x) <= sabs(y)) ? a : b, base);
+    const bool flat = x * y <= (R)0;
+    return limited(flat ? (R)0 : half, half, flat, (sabs(x) <= sabs(y)) ? a : b, base);
 }
 
 template <int D, typename S>
