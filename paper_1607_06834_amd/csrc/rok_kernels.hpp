@@ -59,7 +59,7 @@ Work carve(void* base, long N, int M, int s, bool step);
 
 // Krylov / step kernels (rok_krylov.hip)
 hipError_t launch_init(const Work& W, int M, int s, hipStream_t st);
-// scal[0] = ||y||, scal[1] = sqrt((1 + ||y||) u) / (v ? ||v|| : 1)  (scal[3] = ||v||)
+// scal[0] = ||y||, scal[1] = sqrt((1 + ||y||) u) / ||v||  (scal[3] = ||v||)
 hipError_t launch_norm_eps(const Work& W, const double* y, const double* v, long n, hipStream_t st);
 // *out = sqrt(sum_i q_i^2 / n), q_i = (a_i - b_i) / (c (atol + rtol max(|y_i|, |a_i|)))
 hipError_t launch_error_norm(const Work& W, const double* y, const double* a, const double* b, long n, double rtol,

@@ -96,7 +96,7 @@ enum { FIN_SQRT_TO = 0, FIN_STORE = 1, FIN_EPS = 2 };
 
 // One block: finishes a sum and applies the bookkeeping of `op`.
 __global__ __launch_bounds__(kRedThreads) void k_finish(const double* partials, int op, double* out, double* scal,
-                                                       int* ints, int has_v) {
+                                                       int* ints) {
     __shared__ double s[kRedThreads];
     if (op == FIN_STORE && ints[1]) return;
     double tot = final_sum(partials, s);
@@ -106,12 +106,11 @@ __global__ __launch_bounds__(kRedThreads) void k_finish(const double* partials, 
     } else if (op == FIN_STORE) {
         *out = tot;
         if (nonfinite(tot)) ints[2] |= ROK_FLAG_NONFINITE;
-    } else {  // FIN_EPS: eps = sqrt((1 + ||y||) u) [/ ||v||]
+    } else {  // FIN_EPS: eps = sqrt((1 + ||y||) u) / ||v||
         double ny = sqrt(tot);
         scal[0] = ny;
         double e = sqrt((1.0 + ny) * kEpsMach);
-        if (has_v) e = e / scal[3];
-        scal[1] = e;
+        scal[1] = e / scal[3];
     }
 }
 
@@ -709,14 +708,12 @@ hipError_t launch_init(const Work& W, int M, int s, hipStream_t st) {
 }
 
 hipError_t launch_norm_eps(const Work& W, const double* y, const double* v, long n, hipStream_t st) {
-    if (v) {
-        ROK_RED(false, true, (double*)v, nullptr, nullptr, nullptr, nullptr, n, nullptr, mgs_part(W, 1));
-        hipLaunchKernelGGL(k_finish, dim3(1), dim3(kRedThreads), 0, st, mgs_part(W, 1), (int)FIN_SQRT_TO, W.scal + 3,
-                           W.scal, W.ints, 0);
-    }
+    ROK_RED(false, true, (double*)v, nullptr, nullptr, nullptr, nullptr, n, nullptr, mgs_part(W, 1));
+    hipLaunchKernelGGL(k_finish, dim3(1), dim3(kRedThreads), 0, st, mgs_part(W, 1), (int)FIN_SQRT_TO, W.scal + 3,
+                       W.scal, W.ints);
     ROK_RED(false, true, (double*)y, nullptr, nullptr, nullptr, nullptr, n, nullptr, mgs_part(W, 0));
     hipLaunchKernelGGL(k_finish, dim3(1), dim3(kRedThreads), 0, st, mgs_part(W, 0), (int)FIN_EPS, nullptr, W.scal,
-                       W.ints, v ? 1 : 0);
+                       W.ints);
     return hipGetLastError();
 }
 
@@ -764,7 +761,7 @@ hipError_t launch_mgs_column(const Work& W, double* w, const double* V, long n, 
                            mgs_part(W, j + 1), W.H, M, j, vnext, n, W.ints);
     } else {
         hipLaunchKernelGGL(k_finish, dim3(1), dim3(kRedThreads), 0, st, mgs_part(W, j), (int)FIN_STORE,
-                           W.H + (long)j * M + j, W.scal, W.ints, 0);
+                           W.H + (long)j * M + j, W.scal, W.ints);
     }
     return hipGetLastError();
 }
