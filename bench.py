@@ -235,7 +235,7 @@ def _mgs_roofline(args, g, y, M, mode, stream, ms_step):
     The basis of the step's Arnoldi process at y and the products w_j = J v_j
     are prepared first; the timed loop then runs the M columns j = 0..M-1 as
     the step does, one HIP event pair per column.
-    * Resident path (N <= 4.19 M: one cooperative kernel per column, w held
+    * Resident path (N <= 4.19 M: one kernel per column, w held
       on chip): a launch is a column; algorithmic bytes of column j: w and
       v_0..v_j read, v_{j+1} written.
     * One-reduce path (the default for larger N: w does not fit on chip):

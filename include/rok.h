@@ -96,6 +96,12 @@ enum { ROK_MGS_AUTO = 0, ROK_MGS_PER_PASS = 1, ROK_MGS_RESIDENT = 2, ROK_MGS_ONE
  * `prandtl`, ratio of specific heats `gamma`.  With precision =
  * ROK_FP32_RESIDUAL the residual and tangent kernels compute in float while
  * Arnoldi, the reduced solve and all state accumulation stay in double.
+ * Quotients and square roots in f and its products are correctly rounded
+ * for operands and results between 2^-900 and 2^900 (arguments of roots from
+ * 2^-767; in float 2^-100 to 2^100); outside, where the scaling that a general
+ * division makes is left out, they may lose accuracy or give NaN.  A MUSCL
+ * slope between two infinite differences gives NaN (f is not finite in such a
+ * cell either way).
  */
 typedef struct {
     int ndim;
@@ -137,7 +143,7 @@ void rok_destroy(rok_ctx* ctx);
 /* Selects how the modified Gram-Schmidt passes of rok_arnoldi / rok_step
  * run: ROK_MGS_PER_PASS launches one kernel per pass (the work vector is
  * streamed through memory); ROK_MGS_RESIDENT runs one kernel per
- * Arnoldi column with the work vector held in registers (N up to 16 * 2^18 = 4194304);
+ * Arnoldi column with the work vector held on chip (N up to 16 * 2^18 = 4194304);
  * ROK_MGS_AUTO (default) takes the resident kernel when the device and N
  * allow it.  Both produce bit-identical results.  The setting also selects
  * the reverse of the Arnoldi columns in rok_step_vjp: one resident kernel per
@@ -161,11 +167,6 @@ void rok_destroy(rok_ctx* ctx);
  * Changes the context: not to be called while other calls on the same
  * context are being made.  ROK_EINVAL for an unknown path. */
 rok_status rok_set_mgs_path(rok_ctx* ctx, int path);
-
-/* For tests: the resident kernels of 256 blocks behave as if only the first
- * `blocks` of them had found room on the device in time (0, the default: off).
- * The results do not change.  ROK_EINVAL outside 0 .. 256. */
-rok_status rok_set_gang_hold(rok_ctx* ctx, int blocks);
 
 /* The orthogonalisation rok_arnoldi, rok_step and rok_mgs_column take on this
  * context for Krylov dimension M (1..ROK_MAX_M): ROK_MGS_PER_PASS,

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "rok.h"
+#include "rok_testing.h"
 #include "rok_device.hpp"
 #include "rok_kernels.hpp"
 
@@ -18,7 +19,7 @@ struct rok_ctx {
     rok_problem pb;
     rok::Geom G;
     int mgs_path;
-    int gang_hold;   // see rok_set_gang_hold
+    int gang_hold;   // tests (rok_testing.h)
 };
 
 namespace {

@@ -24,7 +24,7 @@ JVP_FD, JVP_TANGENT = 0, 1
 FLAG_NONFINITE, FLAG_BREAKDOWN, FLAG_ZERO_RHS, FLAG_BARRIER, FLAG_NONPHYSICAL = 1, 2, 4, 8, 16
 MAX_STAGES, MAX_M = 8, 64
 
-SYMBOLS = ["rok_create", "rok_destroy", "rok_set_mgs_path", "rok_set_gang_hold", "rok_arnoldi_path", "rok_state_size", "rok_workspace_bytes", "rok_residual", "rok_residual_split",
+SYMBOLS = ["rok_create", "rok_destroy", "rok_set_mgs_path", "rok_arnoldi_path", "rok_state_size", "rok_workspace_bytes", "rok_residual", "rok_residual_split",
            "rok_jvp", "rok_jvp_noalloc", "rok_arnoldi", "rok_step", "rok_residual_vjp", "rok_residual_vjp2", "rok_step_vjp",
            "rok_step_vjp_workspace_bytes", "rok_step_vjp_stored", "rok_step_vjp_adjoint_bytes", "rok_mgs_column",
            "rok_eigs", "rok_eigs_workspace_bytes", "rok_set_grid", "rok_grid_metric_bytes", "rok_set_ogrid",
