@@ -38,7 +38,7 @@ struct Work {
     double* partials; // npart x kRedBlocks reduction partials
     int npart;
     double* gpart;    // the exchange slots of the resident MGS kernels (kExchangeSlots, emptied by launch_init; M > 0)
-    unsigned* bar;    // exchange words of the resident MGS kernels (kBarWords unsigned, zeroed by launch_init)
+    unsigned* bar;    // exchange words of the resident MGS kernels (kBarWords unsigned, zeroed by launch_init; M > 0)
     // full-length vectors (double, N each)
     double* w;        // Arnoldi work vector
     double* V;        // M columns (rok_step only; rok_arnoldi uses the caller's V)

@@ -216,10 +216,10 @@ __global__ __launch_bounds__(kRedThreads) void k_norm_scale(const double* partia
 }
 
 __global__ void k_init(double* H, int nh, double* phi, double* lam, int nsm, double* scal, int* ints, int meff0,
-                       unsigned* bar, unsigned long long* slots, int nslot, double* sig, int nsig) {
+                       unsigned* bar, int nbar, unsigned long long* slots, int nslot, double* sig, int nsig) {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
     for (int e = t; e < nslot; e += gridDim.x * blockDim.x) slots[e] = kExchangeEmpty;
-    for (int e = t; e < kBarWords; e += gridDim.x * blockDim.x) bar[e] = 0u;
+    for (int e = t; e < nbar; e += gridDim.x * blockDim.x) bar[e] = 0u;
     for (int e = t; e < nsig; e += gridDim.x * blockDim.x) sig[e] = 1.0;
     for (int e = t; e < nh; e += gridDim.x * blockDim.x) H[e] = 0.0;
     for (int e = t; e < nsm; e += gridDim.x * blockDim.x) {
@@ -702,8 +702,11 @@ __global__ __launch_bounds__(kRedThreads) void k_err_finish(const double* partia
 hipError_t launch_init(const Work& W, int M, int s, hipStream_t st) {
     int Mm = M > 0 ? M : 1;
     int ss = s > 0 ? s : 1;
+    // without a basis nothing is exchanged, and the words' place may hold the slots of a larger layout (rok_jvp's
+    // default increment in a workspace that rok_mgs_column uses)
     hipLaunchKernelGGL(k_init, dim3(16), dim3(256), 0, st, W.H, (Mm + 1) * Mm, W.phi, W.lam, ss * Mm, W.scal, W.ints,
-                       M, W.bar, (unsigned long long*)W.gpart, M > 0 ? kExchangeSlots : 0, W.sig, Mm + 1);
+                       M, W.bar, M > 0 ? kBarWords : 0, (unsigned long long*)W.gpart, M > 0 ? kExchangeSlots : 0, W.sig,
+                       Mm + 1);
     return hipGetLastError();
 }
 
