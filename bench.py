@@ -81,7 +81,7 @@ def parse():
 
 
 RESIDUAL_SOURCES = ("rok_residual.hip", "rok_flux.hpp", "rok_device.hpp")
-MGS_SOURCES = ("rok_mgs.hip", "rok_kernels.hpp", "rok_device.hpp")
+MGS_SOURCES = ("rok_mgs.hip", "rok_gate.hpp", "rok_kernels.hpp", "rok_device.hpp")
 KRED_SOURCES = ("rok_krylov.hip", "rok_kernels.hpp", "rok_device.hpp")
 LS_SOURCES = ("rok_lowsync.hip", "rok_krylov.hip", "rok_kernels.hpp", "rok_device.hpp")
 

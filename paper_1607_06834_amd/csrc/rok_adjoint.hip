@@ -558,8 +558,7 @@ __global__ __launch_bounds__(256) void k_vjp(Geom G, const double* y, const doub
 // reverses the 2 (first order) or 4 (MUSCL) faces per direction whose stencil
 // holds it; a state's quotients share a reciprocal; the viscous part is a sweep back instead of 4 forward-mode
 // evaluations of each of 12 faces.  Measured: Navier-Stokes MUSCL, 700 x 450,
-// 312 -> 47.5 us; first-order Euler, 512^2, 22.6 -> 14.9 us, with the
-// second-order adjoint 39.5 -> 32.5 us.
+// 312 -> 45.0 us; first-order Euler, 512^2, 22.6 -> 13.4 us.  (vjp_by_cells: where the cells' kernel is faster.)
 // ---------------------------------------------------------------------------
 constexpr int kVT = 16;
 

@@ -809,8 +809,8 @@ __global__ __launch_bounds__(kPT) void k_mgs_rev_resident(double* wsrc, const do
     double d = 0.0;
     int failed = 0;
     // canonical sum of the lane sums acc; the caller's prefetch: early() by the waves 1-15 before the block's tree,
-    // late() by them when the block's value is out, both by wave 0 after its polls.  (v early and vbar late: gradient at 512^2
-    // 7550 us; the other way round 7583, both late 7693, both early 7682.)
+    // late() by them when the block's value is out, both by wave 0 after its polls.  (Gradient at 512^2 on one card: v early and
+    // vbar late 7550 us, the other way round 7583, both late 7693, both early 7682; from card to card the first varies from 7550 to 7660.)
     auto exchange = [&](double (&acc)[K], bool first, auto early, auto late) {
 #pragma unroll
         for (int k = 0; k < K; ++k) asm volatile("" : "+v"(acc[k]) : : "memory");
